@@ -320,7 +320,7 @@ int moe_layer_forward(const moe_config* cfg, const void* x, const void* Wg, cons
 /* moe_layer_forward that also returns the second value of Algorithm 1, the auxiliary balance loss
  * (formula and conventions: see moe_aux_loss), without a second pass over the tokens: the gating
  * kernel adds up the softmax probabilities and the first picks per expert while it scores the tokens
- * (per block of tokens, in token order) and the permutation's scan launch adds the blocks' sums in
+ * (per block of tokens, in token order) and the permutation's launch adds the blocks' sums in
  * order, so the loss is bitwise reproducible and no [T, E] logits are written.  (float32 input, more
  * than 64 experts, or a router matrix too large for the LDS: the logits go through the workspace and
  * the kernels of moe_aux_loss run after the gate.)

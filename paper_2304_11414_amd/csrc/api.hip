@@ -723,7 +723,7 @@ int moe_layer_forward_aux(const moe_config* cfg, const void* x, const void* Wg, 
 
   // Gating.  Where the router runs in the kernel that holds Wg in LDS, that kernel also counts the
   // picks per segment of the permutation (one launch less below) and, when the balance loss is
-  // wanted, leaves its partial sums; the permutation's scan launch then finishes the loss.
+  // wanted, leaves its partial sums; the permutation's last launch then finishes the loss.
   const bool want_aux = l_aux != nullptr;
   const bool fused_gate = gate_is_fused_kernel(c);
   GateFusion fusion = {};

@@ -8,7 +8,8 @@
 //      them; the tokens of one block when the gating kernel has already counted them on the way)
 //      and counts, per local expert, how many of them it holds (ballot + popcount, counts kept in
 //      registers);
-//   2. one wavefront per expert turns the per-segment counts into exclusive prefix sums;
+//   2. the per-segment counts are turned into exclusive prefix sums per expert (by every block of step 3
+//      for its own segments; by a launch of its own when there are many);
 //   3. every wavefront walks its segment again, 64 assignments at a time: rank inside the step by
 //      ballot/popcount, plus the running count carried in registers, plus the segment's prefix.
 // counts/offsets (capacity-clamped, exclusive scan over the local experts) are rebuilt by every
@@ -50,6 +51,7 @@ hipError_t static_scratch_of_current_device(void** ptr) {
 }
 
 constexpr int kRegs = kMaxExperts / kWave;  // lane i holds experts i, i+64, i+128, i+192
+constexpr int kPlaceThreads = 1024, kPlaceWaves = kPlaceThreads / kWave;   // placing kernel: segments per block
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
@@ -110,14 +112,71 @@ __global__ __launch_bounds__(256) void segment_count_kernel(const int32_t* __res
     count_segment(expert_idx, seg_count, seg, n_assign, n_seg, seg_assign, local_begin, n_local);
 }
 
-// Step 2.  One block per local expert: seg_base = exclusive scan of seg_count over segments (may be
-// done in place), totals[i] = queue length of expert i before any capacity clamp.  A thread adds up a
-// run of consecutive segments, the 256 run sums are scanned (butterfly inside a wavefront, the four
-// wavefront totals in order), and every thread then writes the prefixes of its run.
+// The balance loss (Algorithm 1's l_aux; see aux.hip for the formula) from the per-segment partial sums the
+// gating kernel left: one block adds them up and writes the loss.  The threads form slices of E (thread
+// slice * E + e: neighbouring threads on neighbouring experts of one segment), every slice adds up its
+// share of the segments, the slices are added in order: a fixed order, bitwise reproducible.  (One thread
+// per expert walking all the segments, two dependent loads at a time, took 80 us for 512 segments; the
+// slices finish inside the placing kernel's 10 us.)
+__device__ __forceinline__ void finish_balance_loss(const AuxOut& aux) {
+  __shared__ float prob[kPlaceThreads];
+  __shared__ int32_t cnt[kPlaceThreads];
+  __shared__ float term[kMaxExperts];
+  const int slices = static_cast<int>(blockDim.x) / aux.E;
+  const int slice = threadIdx.x / aux.E, e = threadIdx.x - slice * aux.E;
+  if (slice < slices) {
+    float p = 0.f;
+    int n = 0;
+    for (int g0 = slice; g0 < aux.n_part; g0 += slices * 8) {
+      float pv[8];
+      int nv[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int g = g0 + j * slices;
+        const size_t at = static_cast<size_t>(min(g, aux.n_part - 1)) * aux.E + e;
+        pv[j] = aux.part_prob[at];
+        nv[j] = aux.part_cnt[at];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        p += g0 + j * slices < aux.n_part ? pv[j] : 0.f;
+        n += g0 + j * slices < aux.n_part ? nv[j] : 0;
+      }
+    }
+    prob[threadIdx.x] = p;
+    cnt[threadIdx.x] = n;
+  }
+  __syncthreads();
+  if (static_cast<int>(threadIdx.x) < aux.E) {
+    float p = 0.f;
+    int n = 0;
+    for (int sl = 0; sl < slices; ++sl) {
+      p += prob[sl * aux.E + threadIdx.x];
+      n += cnt[sl * aux.E + threadIdx.x];
+    }
+    const float mp = aux.T > 0 ? p / static_cast<float>(aux.T) : 0.f;
+    if (aux.mean_prob != nullptr) aux.mean_prob[threadIdx.x] = mp;
+    if (aux.first_counts != nullptr) aux.first_counts[threadIdx.x] = n;
+    term[threadIdx.x] = aux.T > 0 ? mp * (static_cast<float>(n) / static_cast<float>(aux.T)) : 0.f;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float sum = 0.f;
+    for (int i = 0; i < aux.E; ++i) sum += term[i];   // ascending expert order
+    *aux.l_aux = static_cast<float>(aux.E) * sum;
+  }
+}
+
+// Step 2 as a launch of its own (many segments, see launch_permute).  One block per local expert:
+// seg_base = exclusive scan of seg_count over segments (may be done in place), totals[i] = queue length
+// of expert i before any capacity clamp.  A thread adds up a run of consecutive segments, the run sums
+// are scanned (butterfly inside a wavefront, the wavefront totals in order), and every thread then
+// writes the prefixes of its run.
 constexpr int kScanThreads = 256;
-__device__ __forceinline__ void scan_expert(const int32_t* seg_count, int32_t* seg_base,
-                                            int32_t* totals, int i, int n_seg) {
-  __shared__ int wave_total[4];
+__global__ __launch_bounds__(kScanThreads) void segment_scan_kernel(const int32_t* seg_count, int32_t* seg_base,
+                                                                    int32_t* __restrict__ totals, int n_seg) {
+  __shared__ int wave_total[kScanThreads / kWave];
+  const int i = blockIdx.x;
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int32_t* in = seg_count + static_cast<int64_t>(i) * n_seg;
   int32_t* out = seg_base + static_cast<int64_t>(i) * n_seg;
@@ -143,44 +202,51 @@ __device__ __forceinline__ void scan_expert(const int32_t* seg_count, int32_t* s
   if (threadIdx.x == kScanThreads - 1) totals[i] = before;
 }
 
-// Blocks 0 .. n_local-1 scan one expert each.  One more block, when the gating kernel has left
-// per-segment partial sums for the balance loss (Algorithm 1's l_aux; see aux.hip for the formula),
-// adds them up in segment order (fixed order: bitwise reproducible) and writes the loss.
-__global__ __launch_bounds__(kScanThreads) void segment_scan_kernel(const int32_t* __restrict__ seg_count,
-                                                          int32_t* __restrict__ seg_base,
-                                                          int32_t* __restrict__ totals, int n_seg,
-                                                          int n_local, AuxOut aux) {
-  if (static_cast<int>(blockIdx.x) < n_local) {
-    scan_expert(seg_count, seg_base, totals, blockIdx.x, n_seg);
-    return;
-  }
-  __shared__ float term[kMaxExperts];
-  for (int e = threadIdx.x; e < aux.E; e += kScanThreads) {
-    float prob = 0.f;
-    int cnt = 0;
-    for (int g = 0; g < aux.n_part; ++g) {
-      prob += aux.part_prob[static_cast<size_t>(g) * aux.E + e];
-      cnt += aux.part_cnt[static_cast<size_t>(g) * aux.E + e];
+// Step 2 folded into step 3: the block's wavefronts share the local experts; for each, a wavefront reads
+// the counts of all the segments (64 at a time, the loads independent of each other) and leaves in LDS the
+// expert's total and the prefix of each of the block's own segments.
+__device__ __forceinline__ void scan_for_block(const int32_t* __restrict__ seg_count, int n_seg, int n_local,
+                                               int32_t (&base)[kPlaceWaves][kMaxExperts],
+                                               int32_t (&total)[kMaxExperts]) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  const int s0 = blockIdx.x * kPlaceWaves;
+  for (int i = wave; i < n_local; i += kPlaceWaves) {
+    const int32_t* in = seg_count + static_cast<int64_t>(i) * n_seg;
+    const int own = (lane < kPlaceWaves && s0 + lane < n_seg) ? in[s0 + lane] : 0;
+    int before = 0, all = 0;
+    for (int s = lane; s < n_seg; s += kWave * 8) {
+      int v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = s + j * kWave < n_seg ? in[s + j * kWave] : 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        all += v[j];
+        before += s + j * kWave < s0 ? v[j] : 0;
+      }
     }
-    const float mp = aux.T > 0 ? prob / static_cast<float>(aux.T) : 0.f;
-    if (aux.mean_prob != nullptr) aux.mean_prob[e] = mp;
-    if (aux.first_counts != nullptr) aux.first_counts[e] = cnt;
-    term[e] = aux.T > 0 ? mp * (static_cast<float>(cnt) / static_cast<float>(aux.T)) : 0.f;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float sum = 0.f;
-    for (int e = 0; e < aux.E; ++e) sum += term[e];   // ascending expert order
-    *aux.l_aux = static_cast<float>(aux.E) * sum;
+    int incl = own;
+#pragma unroll
+    for (int off = 1; off < kPlaceWaves; off <<= 1) {
+      const int up = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += up;
+    }
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) {
+      before += __shfl_xor(before, off, 64);
+      all += __shfl_xor(all, off, 64);
+    }
+    if (lane < kPlaceWaves) base[lane][i] = before + incl - own;
+    if (lane == 0) total[i] = all;
   }
 }
 
-// Step 3.
+// Step 3.  first_pick: expert_idx of this lane's assignment in the segment's first 64.  totals[i]: queue length of local expert i; seg_base[i * stride]: assignments to it before this
+// segment.
 __device__ __forceinline__ void rank_segment(
-    const int32_t* __restrict__ expert_idx, const int32_t* seg_base, const int32_t* totals,
+    const int32_t* __restrict__ expert_idx, const int32_t* seg_base, int64_t stride, const int32_t* totals,
     int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
-    int32_t* __restrict__ inv_perm, int seg, int64_t n_assign, int n_seg, int seg_assign,
-    int local_begin, int n_local, int cap /* INT_MAX when unlimited */) {
+    int32_t* __restrict__ inv_perm, int seg, int64_t n_assign, int seg_assign,
+    int local_begin, int n_local, int cap /* INT_MAX when unlimited */, int first_pick) {
   const int lane = lane_id();
 
   // Kept queue lengths and their exclusive scan over the local experts (ascending expert id).
@@ -189,6 +255,8 @@ __device__ __forceinline__ void rank_segment(
 #pragma unroll
   for (int c = 0; c < kRegs; ++c) {
     int i = c * kWave + lane;
+    kept[c] = off[c] = run[c] = 0;
+    if (c * kWave >= n_local) continue;   // (uniform: up to 64 local experts take one pass)
     kept[c] = i < n_local ? min(totals[i], cap) : 0;
     int incl = kept[c];
 #pragma unroll
@@ -198,7 +266,7 @@ __device__ __forceinline__ void rank_segment(
     }
     off[c] = carry + incl - kept[c];
     carry += __shfl(incl, kWave - 1, 64);
-    run[c] = i < n_local ? seg_base[static_cast<int64_t>(i) * n_seg + seg] : 0;
+    run[c] = i < n_local ? seg_base[i * stride] : 0;
     if (seg == 0 && i < n_local) {
       counts[i] = kept[c];
       offsets[i] = off[c];
@@ -212,7 +280,7 @@ __device__ __forceinline__ void rank_segment(
     int64_t a = base + step * kWave + lane;
     int e = -1;
     if (a < end) {
-      unsigned le = static_cast<unsigned>(expert_idx[a] - local_begin);
+      unsigned le = static_cast<unsigned>((step == 0 ? first_pick : expert_idx[a]) - local_begin);
       if (le < static_cast<unsigned>(n_local)) e = static_cast<int>(le);
     }
     int row = -1;
@@ -238,15 +306,31 @@ __device__ __forceinline__ void rank_segment(
   }
 }
 
-__global__ __launch_bounds__(256) void rank_kernel(
-    const int32_t* __restrict__ expert_idx, const int32_t* __restrict__ seg_base,
-    const int32_t* __restrict__ totals, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm, int64_t n_assign, int n_seg,
-    int seg_assign, int local_begin, int n_local, int cap) {
-  const int seg = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (seg < n_seg)
-    rank_segment(expert_idx, seg_base, totals, counts, offsets, perm, inv_perm, seg, n_assign, n_seg,
-                 seg_assign, local_begin, n_local, cap);
+// A wavefront per segment.  seg_base != nullptr: the scan has been a launch of its own; else the block does
+// it from seg_count.  One more block, when the balance loss is wanted, finishes it.
+__global__ __launch_bounds__(kPlaceThreads) void place_kernel(
+    const int32_t* __restrict__ expert_idx, const int32_t* __restrict__ seg_count,
+    const int32_t* __restrict__ seg_base, const int32_t* __restrict__ totals, int32_t* __restrict__ counts,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm, int64_t n_assign,
+    int n_seg, int seg_assign, int local_begin, int n_local, int cap, int blocks, AuxOut aux) {
+  if (static_cast<int>(blockIdx.x) == blocks) {
+    finish_balance_loss(aux);
+    return;
+  }
+  __shared__ int32_t base[kPlaceWaves][kMaxExperts];
+  __shared__ int32_t total[kMaxExperts];
+  const int wave = threadIdx.x >> 6, seg = blockIdx.x * kPlaceWaves + wave;
+  // (this lane's first pick: its load is out before the scan's)
+  const int64_t a0 = static_cast<int64_t>(seg) * seg_assign + lane_id();
+  const int first_pick = a0 < n_assign ? expert_idx[a0] : -1;
+  const bool folded = seg_base == nullptr;
+  if (folded) {
+    scan_for_block(seg_count, n_seg, n_local, base, total);
+    __syncthreads();
+  }
+  if (seg < n_seg || seg == 0)   // (n_seg == 0: counts and offsets are still defined, all zero)
+    rank_segment(expert_idx, folded ? base[wave] : seg_base + seg, folded ? 1 : n_seg, folded ? total : totals, counts,
+                 offsets, perm, inv_perm, seg, n_assign, seg_assign, local_begin, n_local, cap, first_pick);
 }
 
 hipError_t launch_permute(const moe_config& c, int64_t cap, const int32_t* expert_idx,
@@ -257,25 +341,27 @@ hipError_t launch_permute(const moe_config& c, int64_t cap, const int32_t* exper
   const int n_seg = static_cast<int>((n_assign + seg_assign - 1) / seg_assign);
   const int N = c.local_count;
   int32_t* seg_count = seg_scratch;
-  int32_t* seg_base = seg_scratch + static_cast<int64_t>(N) * n_seg;
-  int32_t* totals = seg_base + static_cast<int64_t>(N) * n_seg;
   const int cap_i = (cap < 0 || cap > 0x7fffffff) ? 0x7fffffff : static_cast<int>(cap);
-  const int blocks = n_seg > 0 ? (n_seg + 3) / 4 : 0;
-  if (blocks > 0 && !counted)
-    segment_count_kernel<<<blocks, 256, 0, s>>>(expert_idx, seg_count, n_assign, n_seg, seg_assign,
-                                                c.local_begin, N);
-  AuxOut no_aux = {};
-  const bool with_aux = aux != nullptr && aux->l_aux != nullptr;
-  segment_scan_kernel<<<N + (with_aux ? 1 : 0), kScanThreads, 0, s>>>(seg_count, seg_base, totals, n_seg, N,
-                                                            with_aux ? *aux : no_aux);
-  if (blocks > 0) {
-    rank_kernel<<<blocks, 256, 0, s>>>(expert_idx, seg_base, totals, counts, offsets, perm,
-                                       inv_perm, n_assign, n_seg, seg_assign, c.local_begin, N, cap_i);
-  } else {
-    // T == 0: counts and offsets are still defined (all zero); one wavefront writes them.
-    rank_kernel<<<1, 64, 0, s>>>(expert_idx, seg_base, totals, counts, offsets, perm, inv_perm, 0, 1,
-                                 seg_assign, c.local_begin, N, cap_i);
+  if (n_seg > 0 && !counted)
+    segment_count_kernel<<<(n_seg + 3) / 4, 256, 0, s>>>(expert_idx, seg_count, n_assign, n_seg, seg_assign,
+                                                         c.local_begin, N);
+  // The scan over the segments is done by every block of the placing kernel while a wavefront has at most 64
+  // loads to make for it (8 local experts: up to 4096 segments).  A launch costs 4-5 us whatever it does, those
+  // loads 1 us at 512 segments (8192 tokens) and, growing with the segments, about as much as the launch where
+  // the line is; beyond it the scan is a launch of its own.  (8192 tokens, 8 experts: scan + rank 4.9 + 6.5 us,
+  // this kernel 8.6; 16 tokens: 4.6 + 5.2, 6.4.)
+  const int64_t loads = static_cast<int64_t>((N + kPlaceWaves - 1) / kPlaceWaves) * ((n_seg + kWave - 1) / kWave);
+  int32_t *seg_base = nullptr, *totals = nullptr;
+  if (loads > 64) {
+    seg_base = seg_scratch + static_cast<int64_t>(N) * n_seg;
+    totals = seg_base + static_cast<int64_t>(N) * n_seg;
+    segment_scan_kernel<<<N, kScanThreads, 0, s>>>(seg_count, seg_base, totals, n_seg);
   }
+  const bool with_aux = aux != nullptr && aux->l_aux != nullptr;
+  const int blocks = n_seg > 0 ? (n_seg + kPlaceWaves - 1) / kPlaceWaves : 1;
+  place_kernel<<<blocks + (with_aux ? 1 : 0), kPlaceThreads, 0, s>>>(
+      expert_idx, seg_count, seg_base, totals, counts, offsets, perm, inv_perm, n_assign, n_seg, seg_assign,
+      c.local_begin, N, cap_i, blocks, with_aux ? *aux : AuxOut{});
   return hipGetLastError();
 }
 
