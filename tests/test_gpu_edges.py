@@ -6,6 +6,7 @@ import pytest
 
 from oracle import ppmoe_oracle as O
 from paper_2304_11414_amd import synth
+from tests.gpu_util import GRAD_ELEM_FACTOR, TOL, DeviceLayer, assert_close
 from tests.test_gpu_parity import check_dispatch, compare_layer_full, small_cfg
 
 pytestmark = pytest.mark.gpu
@@ -33,3 +34,31 @@ def test_dispatch_at_the_lines_of_the_scan(kw):
 def test_balance_loss_inside_the_layer(kw):
     lc = small_cfg(**kw)
     compare_layer_full(lc, synth.make_inputs(lc))
+
+
+# ---------------------------------------------------------------- router gradients
+
+@pytest.mark.parametrize("kw", [
+    dict(T=1, d=8, F=64, E=1, top_k=1, seed=70),                        # one token, one 16-byte piece of columns
+    dict(T=257, d=136, F=128, E=17, top_k=1, seed=71),                  # second group of 16 experts, nine pieces
+    dict(T=149, d=1032, F=64, E=33, top_k=8, renorm_topk=True, seed=70),    # as many picks as are allowed
+    dict(T=133, d=64, F=64, E=200, top_k=4, local_begin=0, local_count=200, seed=70),   # four rounds of 64 experts
+])
+def test_router_gradients(kw):
+    """dx, dWg and dbias only.  (With two or three rows per expert an element of an expert weight gradient is a
+    single product of two factors with heavy tails, which the elementwise bound of a sum over many rows does not
+    cover; those products are tested on layers with many rows.)"""
+    lc = small_cfg(**kw)
+    inp = synth.make_inputs(lc)
+    mv = synth.math_views(inp)
+    d_out = np.random.default_rng(lc.seed).standard_normal((lc.T, lc.d)).astype(np.float32)
+    synth.round_to_bf16(d_out)
+    ref = O.layer_backward(inp["x"], mv["Wg"], inp["bias"], mv["W1"], mv["W2"], d_out, E=lc.E, k=lc.top_k,
+                           local_begin=lc.local_begin, local_count=lc.n_local,
+                           capacity_factor=lc.capacity_factor, renorm=lc.renorm_topk)
+    got = DeviceLayer(lc, inp).run_layer_backward(d_out)
+    tol = TOL[lc.in_dtype]
+    et = GRAD_ELEM_FACTOR * tol
+    assert_close(got["dWg"], ref["dWg"].T, tol, "dWg", et)
+    assert_close(got["dbias"], ref["dbias"], tol, "dbias", et)
+    assert_close(got["dx"], ref["dx"], tol, "dx", et)
