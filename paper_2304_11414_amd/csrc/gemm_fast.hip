@@ -316,8 +316,11 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
   // phase of the whole chip at the end (measured on four workloads: up to 9 % of a launch).
   const int stream_slot = ((7 - xcd) * (rounds + 1)) >> 3;
   int round = 0;
-  int64_t u = share_begin(cu);
-  const int64_t u_end = share_begin(cu + 1);
+  // The partial round's tiles go to the first CUs of an XCD, so the shares are dealt out from the last one:
+  // where there are fewer shares than CUs, a CU with a tile of that round is the last to get one as well.
+  const int share = cus - 1 - cu;
+  int64_t u = share_begin(share);
+  const int64_t u_end = share_begin(share + 1);
 
   // Staging: a tile is 512 rows (256 token, 256 weight) of 128 bytes; one load instruction covers 8
   // rows, so a tile is 64 instructions, 16 per wavefront.  Wavefronts 0,1 fetch token rows, 2,3
@@ -611,12 +614,12 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
       n_contrib = 1;   // (this CU's own stores, complete since the barrier that followed them)
     } else if (mode == 0 && ke < KT) {
       if (tid == 0) {
-        // One thread lists the CUs after this one whose share begins inside this tile (skipping empty
+        // One thread lists the CUs of the shares after this one that begin inside this tile (skipping empty
         // shares) and polls their flags (relaxed loads that go to L2, no cache maintenance in the loop).
         int n = 0, failed = 0;
-        for (int c2 = cu + 1; c2 < cus && share_begin(c2) < static_cast<int64_t>(tl + 1) * KT; ++c2) {
+        for (int c2 = share + 1; c2 < cus && share_begin(c2) < static_cast<int64_t>(tl + 1) * KT; ++c2) {
           if (share_begin(c2 + 1) == share_begin(c2)) continue;
-          const int b2 = (c2 << 3) | xcd;
+          const int b2 = ((cus - 1 - c2) << 3) | xcd;
           contrib[++n] = b2;
           int spins = 0;
           uint32_t f = 0;
