@@ -218,14 +218,14 @@ hipError_t launch_dwg(const moe_config& c, const void* x, const float* dlogits, 
                       void* scratch, hipStream_t s);
 
 inline bool grouped_gemm_is_fast(int in_dtype, int K) {
-  return is_16bit(in_dtype) && (K % 64) == 0 && K < (1 << 22);   // 32-bit panel offsets in the fast kernel
+  return is_16bit(in_dtype) && K < (1 << 22);   // 32-bit panel offsets in the fast kernel
 }
 // Can A be read through a row list?  Its byte offsets must fit the 32-bit offsets of the loads.
 inline bool grouped_gemm_can_fuse(int in_dtype, int K, int64_t a_rows) {
   return grouped_gemm_is_fast(in_dtype, K) && a_rows * K * 2 < 0x7fffffffLL;
 }
 
-// bf16 fast path of the above (K a multiple of 64): persistent, at most kMaxPersistentBlocks blocks.
+// 16-bit fast path of the above: persistent, at most kMaxPersistentBlocks blocks.
 constexpr int kMaxPersistentBlocks = 256;
 size_t grouped_gemm_fast_workspace_bytes();
 // The fast GEMM leaves kGemmErrorMagic | code in one word of its workspace when a hand-over of

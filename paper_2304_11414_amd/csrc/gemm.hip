@@ -82,7 +82,7 @@ __device__ __forceinline__ int xcd_remap(int bid, int total) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// bf16 MFMA kernel
+// 16-bit MFMA kernel for contractions too long for the fast path's 32-bit panel offsets (K >= 2^22)
 // ---------------------------------------------------------------------------------------------
 
 constexpr int kBM = 256, kBN = 256, kBK = 64;

@@ -1,5 +1,5 @@
 // Fast path of the grouped expert GEMMs (Section 3.3.2; FFN = GeLU(X A) B, Section 3.1.3) for bf16
-// with K a multiple of 64:
+// and fp16:
 //
 //   C[r, n] = act( sum_k A[r, k] * B[i][n, k] ),  offsets[i] <= r < offsets[i+1]
 //
@@ -236,7 +236,10 @@ __global__ __launch_bounds__(kThreads) void xcc_probe_kernel() {
 // entry >= 0; always so with aux_div == 1) it is multiplied by aux_w[a] and stored as row `token` of
 // C, which nobody else writes; otherwise it is stored unweighted as packed row r of C2 and left to
 // the combine kernel, which has to add it to the token's other picks.
-template <bool GELU, int FUSE, int DT>
+// RAGGED: K is not a multiple of 64 (it is one of 8).  The pieces of the last k-tile that lie past the
+// end of a row belong to the next row: their loads get an offset no descriptor covers and read zeros,
+// which costs one vector OR per load (a variant of its own, so that the other one does not pay it).
+template <bool GELU, int FUSE, int DT, bool RAGGED>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, int n_exp, int Nout, int K, float* __restrict__ slots,
@@ -277,7 +280,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
   //    than the chip has CUs, does not cost a whole tile slot and every CU has work.  A tile cut
   //    this way is finished by the CU that holds its first k-tile.
   const int n_tiles = (Nout + BN - 1) / BN;
-  const int KT = K / BK;
+  const int KT = (K + BK - 1) / BK;
   int total_big, total_small;
   const int small_rows = kSmallRows;
   count_tiles(offsets, n_exp, n_tiles, small_rows, total_big, total_small);
@@ -469,6 +472,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
         is_b ? B + (static_cast<size_t>(tc.expert) * Nout + tc.col0) * K
              : A + (gathered ? 0 : static_cast<size_t>(tc.row0) * K));
     const int row_lim = (is_b ? cols : tc.rows) - 1;
+    const uint32_t past_row = RAGGED && (KT - 1) * BK + piece * 8 >= K ? 0x80000000u : 0u;   // in the last k-tile
     if (gathered) {
 #pragma unroll
       for (int n = 0; n < 16; ++n) {
@@ -510,7 +514,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
       auto gload = [&](int set, int n, int t) {   // t: tile index along K
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<unsigned char*>(gbase), 0, t <= last ? n_records : 0, 0x00020000);
-        stage[set * 16 + n] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[n], t * (BK * 2), 0);
+        const uint32_t off = RAGGED ? goff[n] | (t == KT - 1 ? past_row : 0u) : goff[n];
+        stage[set * 16 + n] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, t * (BK * 2), 0);
       };
       typename Elem16<DT>::vec8 f0[8], f1[8];
       // Small tile: every wavefront reads the token rows from row 0 and its own 64 weight rows.
@@ -920,15 +925,14 @@ std::atomic<int> g_spin_limit{fast::kDefaultSpinLimit};
 hipError_t setup_attrs(FastSetup& st, int dev) {
   using namespace fast;
   if (st.attrs) return hipSuccess;
-  const void* kernels[] = {
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<true, 0, MOE_BF16>),
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<false, 0, MOE_BF16>),
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<true, 1, MOE_BF16>),
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<false, 2, MOE_BF16>),
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<true, 0, MOE_F16>),
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<false, 0, MOE_F16>),
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<true, 1, MOE_F16>),
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<false, 2, MOE_F16>)};
+#define PPMOE_KERNELS(DT, R)                                                               \
+  reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<true, 0, DT, R>),            \
+      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<false, 0, DT, R>),       \
+      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<true, 1, DT, R>),        \
+      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<false, 2, DT, R>)
+  const void* kernels[] = {PPMOE_KERNELS(MOE_BF16, false), PPMOE_KERNELS(MOE_BF16, true),
+                           PPMOE_KERNELS(MOE_F16, false), PPMOE_KERNELS(MOE_F16, true)};
+#undef PPMOE_KERNELS
   for (const void* k : kernels) {
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
@@ -1019,6 +1023,7 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
   uint32_t* flags = reinterpret_cast<uint32_t*>(
       slots + static_cast<size_t>(kSlotsPerBlock) * kMaxPersistentBlocks * kSlotFloats);
   (void)max_rows;
+  const bool ragged = K % BK != 0;
   // fuse: 0 none; 1 rows of A through aux_rows (first GEMM only); 2 rows of the result placed through
   // aux_rows (second GEMM only; with aux_div > 1 it needs the inverse permutation and a place for
   // the rows it cannot place)
@@ -1026,14 +1031,16 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
       (fuse != 0 && aux_rows == nullptr) || (fuse == 2 && aux_w == nullptr) || aux_div < 1 ||
       (fuse == 2 && aux_div != 1 && (aux_inv == nullptr || C2 == nullptr)))
     return hipErrorInvalidValue;
-#define PPMOE_LAUNCH_DT(G, F, DT)                                                     \
-  grouped_gemm_bf16_fast_kernel<G, F, DT><<<blocks, kThreads, kLdsBytes, s>>>(        \
+#define PPMOE_LAUNCH_DT(G, F, DT, R)                                                  \
+  grouped_gemm_bf16_fast_kernel<G, F, DT, R><<<blocks, kThreads, kLdsBytes, s>>>(     \
       A, B, C, offsets, n_exp, Nout, K, slots, flags, epoch, same_l2, spin_limit, aux_rows, aux_w, aux_div, \
       aux_inv, C2)
 #define PPMOE_LAUNCH(G, F)                            \
   do {                                                \
-    if (in_dtype == MOE_F16) PPMOE_LAUNCH_DT(G, F, MOE_F16); \
-    else PPMOE_LAUNCH_DT(G, F, MOE_BF16);             \
+    if (in_dtype == MOE_F16 && ragged) PPMOE_LAUNCH_DT(G, F, MOE_F16, true); \
+    else if (in_dtype == MOE_F16) PPMOE_LAUNCH_DT(G, F, MOE_F16, false);     \
+    else if (ragged) PPMOE_LAUNCH_DT(G, F, MOE_BF16, true);                  \
+    else PPMOE_LAUNCH_DT(G, F, MOE_BF16, false);                             \
   } while (0)
   if (fuse == 1) PPMOE_LAUNCH(true, 1);
   else if (fuse == 2) PPMOE_LAUNCH(false, 2);

@@ -62,3 +62,16 @@ def test_router_gradients(kw):
     assert_close(got["dWg"], ref["dWg"].T, tol, "dWg", et)
     assert_close(got["dbias"], ref["dbias"], tol, "dbias", et)
     assert_close(got["dx"], ref["dx"], tol, "dx", et)
+
+
+# ---------------------------------------------------------------- rows that are not whole k-tiles of 64
+
+@pytest.mark.parametrize("kw", [
+    dict(T=300, d=8, F=72, E=2, top_k=1, in_dtype="f16", out_dtype="f16", seed=80),         # one piece, one past a tile
+    dict(T=515, d=200, F=824, E=3, top_k=2, renorm_topk=True, seed=81),                     # gathered rows and placed rows
+    dict(T=700, d=136, F=1000, E=5, top_k=1, out_dtype="f32", seed=82),                     # cut tiles, packed results
+    dict(T=1100, d=1000, F=4000, E=4, top_k=2, local_begin=2, local_count=2, in_dtype="f16", out_dtype="f16", seed=83),
+])
+def test_layer_with_rows_of_no_whole_tiles(kw):
+    lc = small_cfg(**kw)
+    compare_layer_full(lc, synth.make_inputs(lc))
