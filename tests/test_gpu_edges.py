@@ -8,6 +8,7 @@ from oracle import ppmoe_oracle as O
 from paper_2304_11414_amd import synth
 from tests.gpu_util import GRAD_ELEM_FACTOR, TOL, DeviceLayer, assert_close
 from tests.test_gpu_parity import check_dispatch, compare_layer_full, small_cfg
+from tests.test_gpu_parity import test_expert_ffn_on_oracle_rows as check_ffn
 
 pytestmark = pytest.mark.gpu
 
@@ -75,3 +76,15 @@ def test_router_gradients(kw):
 def test_layer_with_rows_of_no_whole_tiles(kw):
     lc = small_cfg(**kw)
     compare_layer_full(lc, synth.make_inputs(lc))
+
+
+# ---------------------------------------------------------------- float32 products
+
+@pytest.mark.parametrize("d,F,counts", [
+    (8, 40, [1, 0, 33]),                  # one piece per half-wavefront, partial column tile
+    (264, 136, [31, 32, 65]),             # contraction past two rounds of the four wavefronts, remainders
+    (256, 2048, [1000, 0, 25]),           # split form (F = 2048) beside wide tiles in one layer
+    (72, 4104, [513, 64, 63]),            # wide tiles with a partial quarter along rows and columns
+])
+def test_expert_ffn_in_float32(d, F, counts):
+    check_ffn("f32", d, F, counts)
