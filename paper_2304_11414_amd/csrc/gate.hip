@@ -119,6 +119,57 @@ __device__ __forceinline__ void softmax_topk_row_regs(float* lg, const float* __
   }
 }
 
+// The same routine with a wavefront on a row of at most 64 logits in LDS, a lane per expert: the
+// exponentials, the maximum and the selections are one element per lane; the sum of the exponentials stays
+// the sum in ascending order (every lane adds them up from LDS), so the bits are those of the routines above.
+// p: 64 floats of LDS of this wavefront's own.
+__device__ __forceinline__ void softmax_topk_row_wave(float* lg, float* p, int lane, const float* __restrict__ bias,
+                                                      float* __restrict__ logits_out, int E, int k, int renorm,
+                                                      int32_t* idx_out, float* w_out, int32_t* idx_copy,
+                                                      bool probs_out) {
+  const bool in = lane < E;
+  float v = in ? lg[lane] : 0.f;
+  if (in && bias != nullptr) v += bias[lane];
+  if (in && logits_out != nullptr) logits_out[lane] = v;
+  float m = in ? v : -__builtin_inff();
+  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  const float pe_own = in ? expf(v - m) : 0.f;
+  p[lane] = pe_own;
+  __builtin_amdgcn_wave_barrier();
+  float sum = 0.f;
+  for (int e = 0; e < E; ++e) sum += p[e];
+  float pv = __builtin_inff(), wsum = 0.f, my_w = 0.f;
+  int pe = -1, my_idx = 0;
+  for (int j = 0; j < k; ++j) {
+    // the largest element after the previous pick in (value descending, index ascending) order; 64: none
+    int best = in && ((v < pv) || (v == pv && lane > pe)) ? lane : 64;
+    float bv = v;
+    for (int off = 32; off >= 1; off >>= 1) {
+      const int ob = __shfl_xor(best, off, 64);
+      const float ov = __shfl_xor(bv, off, 64);
+      if (ob < 64 && (best == 64 || ov > bv || (ov == bv && ob < best))) {
+        best = ob;
+        bv = ov;
+      }
+    }
+    const bool none = best == 64;
+    const float w = (none ? 0.f : p[none ? 0 : best]) / sum;
+    pv = none ? 0.f : bv;
+    pe = none ? -1 : best;
+    if (lane == j) {
+      my_idx = pe;
+      my_w = w;
+    }
+    wsum += w;
+  }
+  if (lane < k) {
+    idx_out[lane] = my_idx;
+    w_out[lane] = renorm ? my_w / wsum : my_w;
+    if (idx_copy != nullptr) idx_copy[lane] = my_idx;
+  }
+  if (probs_out && in) lg[lane] = pe_own / sum;
+}
+
 // What a block adds once it has scored its tokens (one segment of the permutation that follows):
 // its picks per local expert (seg_count), and the sums of the softmax probabilities and of the first
 // picks per expert (part_prob, part_cnt: partial sums of the balance loss).  One thread per expert
@@ -180,20 +231,22 @@ __device__ __forceinline__ void score_token(float* lg, int t, int T, int E, int 
   }
 }
 
-// 16-bit router, direct operand loads (used for more than 64 experts): a block owns 16*MT tokens; its 4 wavefronts split d between them (span-interleaved)
+// 16-bit router, direct operand loads (used for more than 64 experts and for few tokens): a block owns
+// 16*MT tokens; its W wavefronts split d between them (span-interleaved)
 // and their partial logits are added in wavefront order through LDS, so the float32 sum order is
 // fixed.  MFMA operands come straight from global memory: lane (r = lane%16, g = lane/16) holds 8
 // consecutive k of row r, which is exactly a 16-byte load; four such loads cover 64 contiguous
 // bytes of each of the 16 rows.
-template <int NT, int MT, int DT>
-__global__ __launch_bounds__(256) void gate_bf16_kernel(
+template <int NT, int MT, int DT, int W>
+__global__ __launch_bounds__(64 * W) void gate_bf16_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wg, const float* __restrict__ bias,
     float* __restrict__ logits_out, int32_t* __restrict__ expert_idx, float* __restrict__ gate_w,
     int32_t* __restrict__ seg_count, float* __restrict__ part_prob, int32_t* __restrict__ part_cnt,
     int T, int d, int E, int k, int renorm, int local_begin, int n_local) {
   constexpr int kTok = 16 * MT;
   constexpr int kLd = NT * 16 + 1;
-  __shared__ float red[kTok * kLd];
+  constexpr bool kAllAtOnce = W > 4;   // every wavefront's partial logits fit LDS side by side
+  __shared__ float red[(kAllAtOnce ? W : 1) * kTok * kLd];
   __shared__ int32_t picks[kTok * kMaxTopK];
   const bool extras = seg_count != nullptr || part_prob != nullptr;
 
@@ -223,15 +276,15 @@ __global__ __launch_bounds__(256) void gate_bf16_kernel(
 
   // U spans of 128 k-values per iteration: all their loads are issued before the first MFMA, so a
   // wavefront keeps U * (MT + NT) * 4 16-byte loads in flight.
-  constexpr int U = (NT * MT == 1) ? 4 : (NT * MT <= 4) ? 2 : 1;
+  constexpr int U = W > 4 ? 1 : (NT * MT == 1) ? 4 : (NT * MT <= 4) ? 2 : 1;
   const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
-  for (int c0 = wave * 16; c0 < nchunk; c0 += 64 * U) {
+  for (int c0 = wave * 16; c0 < nchunk; c0 += 16 * W * U) {
     u32x4 a[U][MT][4], b[U][NT][4];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int c = c0 + u * 64 + i * 4 + g;
+        const int c = c0 + u * 16 * W + i * 4 + g;
         const bool ok = c < nchunk;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) a[u][mt][i] = ok ? __builtin_nontemporal_load(xrow[mt] + c) : zero;
@@ -252,26 +305,60 @@ __global__ __launch_bounds__(256) void gate_bf16_kernel(
   }
 
   // D layout of the 16x16 MFMA: lane holds column (lane % 16), rows (lane / 16) * 4 + i.
-  for (int w = 0; w < 4; ++w) {
-    if (wave == w) {
+  if constexpr (kAllAtOnce) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            float* p = &red[(mt * 16 + g * 4 + i) * kLd + nt * 16 + r];
-            *p = (w == 0) ? acc[mt][nt][i] : (*p + acc[mt][nt][i]);
-          }
+        for (int i = 0; i < 4; ++i)
+          red[(wave * kTok + mt * 16 + g * 4 + i) * kLd + nt * 16 + r] = acc[mt][nt][i];
+    __syncthreads();
+    for (int p = threadIdx.x; p < kTok * kLd; p += 64 * W) {   // (an element is read and written by one thread)
+      float v = red[p];
+#pragma unroll
+      for (int w = 1; w < W; ++w) v += red[w * kTok * kLd + p];
+      red[p] = v;
     }
     __syncthreads();
+  } else {
+    for (int w = 0; w < 4; ++w) {
+      if (wave == w) {
+  #pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+  #pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+  #pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              float* p = &red[(mt * 16 + g * 4 + i) * kLd + nt * 16 + r];
+              *p = (w == 0) ? acc[mt][nt][i] : (*p + acc[mt][nt][i]);
+            }
+      }
+      __syncthreads();
+    }
   }
 
-  // The tail: one thread per token (rows of up to 64 experts go through registers).
-  if (threadIdx.x < kTok)
+  if constexpr (kAllAtOnce) {   // the tail: a wavefront per token
+    __shared__ float prob[W][64];
+    for (int i = wave; i < kTok; i += W) {
+      const int t = t0 + i;
+      float* lg = &red[i * kLd];
+      if (t < T) {
+        softmax_topk_row_wave(lg, prob[wave], lane, bias,
+                              logits_out != nullptr ? logits_out + static_cast<size_t>(t) * E : nullptr, E, k, renorm,
+                              expert_idx + static_cast<size_t>(t) * k, gate_w + static_cast<size_t>(t) * k,
+                              extras ? picks + i * k : nullptr, part_prob != nullptr);
+      } else if (extras) {
+        if (lane < k) picks[i * k + lane] = -1;
+        if (lane < E) lg[lane] = 0.f;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  } else if (threadIdx.x < kTok) {   // one thread per token
     score_token<(NT <= 4 ? NT * 16 : 0)>(&red[threadIdx.x * kLd], t0 + threadIdx.x, T, E, k, renorm, bias,
                                          logits_out, expert_idx, gate_w, picks + threadIdx.x * k, extras,
                                          part_prob != nullptr);
+  }
   if (extras) {   // the block's tokens are one segment of the permutation that follows
     __syncthreads();
     block_segment_sums(red, kLd, picks, kTok, k, E, local_begin, n_local, blockIdx.x, gridDim.x,
@@ -454,6 +541,10 @@ __global__ __launch_bounds__(256) void gate_from_logits_kernel(
                    gate_w + static_cast<size_t>(t) * k);
 }
 
+// At most one block of 16 tokens per CU; measured up to there (64 experts, d = 4096): 16 tokens 39 -> 21 us,
+// 4096 tokens 42 -> 26 us, against the whole-row kernel's blocks of 64 tokens; 32 experts 19 -> 14 and 23 -> 18 us.
+constexpr int kGateFewTokens = 4096;
+
 template <int NT, int MT>
 static hipError_t launch_bf16(const moe_config& c, const void* x, const void* Wg, const float* bias,
                               float* logits_out, int32_t* expert_idx, float* gate_w, hipStream_t s,
@@ -491,14 +582,14 @@ static hipError_t launch_bf16(const moe_config& c, const void* x, const void* Wg
 }
 
 // The direct-operand kernel (more than 64 experts: the whole-row kernel's register budget does not
-// reach that far).
-template <int NT, int MT>
+// reach that far; or few tokens).
+template <int NT, int MT, int W = 4>
 static hipError_t launch_bf16_direct(const moe_config& c, const void* x, const void* Wg, const float* bias,
                                      float* logits_out, int32_t* expert_idx, float* gate_w, hipStream_t s,
                                      GateFusion* fusion) {
   int blocks = (c.T + 16 * MT - 1) / (16 * MT);
 #define PPMOE_GATE(DT)                                                                                 \
-  gate_bf16_kernel<NT, MT, DT><<<blocks, 256, 0, s>>>(                                                 \
+  gate_bf16_kernel<NT, MT, DT, W><<<blocks, 64 * W, 0, s>>>(                                           \
       static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(Wg), bias, logits_out, expert_idx,     \
       gate_w, fusion != nullptr ? fusion->seg_count : nullptr,                                         \
       fusion != nullptr ? fusion->part_prob : nullptr, fusion != nullptr ? fusion->part_cnt : nullptr, \
@@ -533,6 +624,13 @@ hipError_t launch_gate(const moe_config& c, const void* x, const void* Wg, const
                                                   expert_idx, gate_w, c.T, c.d, c.E, c.top_k,
                                                   c.renorm_topk);
     return hipGetLastError();
+  }
+  // Few tokens: the time is that of the memory latencies one after another and of the tail, so 16
+  // wavefronts split the contraction of 16 tokens and then take a token each.  (Up to 16 experts the
+  // whole-row kernel has all its loads in flight as well, and a short tail.)
+  if (c.E > 16 && c.E <= 64 && c.T <= kGateFewTokens) {
+    if (c.E <= 32) return launch_bf16_direct<2, 1, 16>(c, x, Wg, bias, logits_out, expert_idx, gate_w, s, fusion);
+    return launch_bf16_direct<4, 1, 16>(c, x, Wg, bias, logits_out, expert_idx, gate_w, s, fusion);
   }
   // Up to 16 experts: more tokens per block where that still leaves two blocks per compute unit -- the
   // router rows, fetched once per block, then cost a half or a quarter of the L2 -> CU traffic.

@@ -9,6 +9,7 @@ from paper_2304_11414_amd import synth
 from tests.gpu_util import GRAD_ELEM_FACTOR, TOL, DeviceLayer, assert_close
 from tests.test_gpu_parity import check_dispatch, compare_layer_full, small_cfg
 from tests.test_gpu_parity import test_expert_ffn_on_oracle_rows as check_ffn
+from tests.test_gpu_parity import test_gate_router as check_router
 
 pytestmark = pytest.mark.gpu
 
@@ -88,3 +89,17 @@ def test_layer_with_rows_of_no_whole_tiles(kw):
 ])
 def test_expert_ffn_in_float32(d, F, counts):
     check_ffn("f32", d, F, counts)
+
+
+# ---------------------------------------------------------------- router on few tokens
+
+@pytest.mark.parametrize("T,d,E,k,dtype", [
+    (1, 8, 16, 1, "bf16"),                # most wavefronts without a span
+    (17, 1032, 17, 2, "f16"),             # two blocks, a span past the end of the row
+    (16, 4104, 33, 8, "bf16"),            # a second round of spans
+    (4096, 136, 64, 1, "bf16"),           # the last size the kernel of few tokens takes
+    (4097, 136, 64, 1, "f16"),            # the first of the next
+    (4097, 136, 20, 2, "bf16"),
+])
+def test_router_on_few_tokens(T, d, E, k, dtype):
+    check_router(dict(T=T, d=d, F=64, E=E, top_k=k, renorm_topk=k > 1, in_dtype=dtype, out_dtype=dtype, seed=101))
