@@ -41,6 +41,30 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// GeLU, tanh form: 0.5 u (1 + tanh(z)) = u / (1 + exp(-2 z)),  z = sqrt(2/pi) (u + 0.044715 u^3).
+// exp2 and the reciprocal are single hardware instructions (about 1 ulp each), ample for a bf16
+// result.  Four at a time, stage by stage: the four dependency chains (mul, fma, mul, exp2, add,
+// rcp, mul) interleave, so the latency of each instruction is hidden by the other three elements.
+__device__ __forceinline__ f32x4 gelu_tanh4(f32x4 u) {
+  // (the sched_barriers keep the compiler from folding the stages back into four serial chains)
+  f32x4 z, e, r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) z[i] = fmaf(0.044715f * u[i], u[i], 1.0f);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) z[i] = (-2.302208198f * u[i]) * z[i];   // -2 sqrt(2/pi) log2(e) (u + 0.044715 u^3)
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) e[i] = __builtin_amdgcn_exp2f(z[i]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) e[i] = 1.0f + e[i];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = __builtin_amdgcn_rcpf(e[i]);
+  __builtin_amdgcn_sched_barrier(0);
+  return u * r;
+}
+
 // Where the balance loss (Algorithm 1's l_aux) goes, and the per-segment partial sums it is made of:
 // part_prob / part_cnt [n_part, E] (sum of the softmax probabilities and number of first picks per
 // expert over the tokens of a segment).  l_aux == nullptr: no loss wanted.
@@ -223,6 +247,25 @@ inline bool grouped_gemm_is_fast(int in_dtype, int K) {
 // Can A be read through a row list?  Its byte offsets must fit the 32-bit offsets of the loads.
 inline bool grouped_gemm_can_fuse(int in_dtype, int K, int64_t a_rows) {
   return grouped_gemm_is_fast(in_dtype, K) && a_rows * K * 2 < 0x7fffffffLL;
+}
+
+// The 16-bit GEMM on few rows (any K, same `fuse` contract): right for any row counts, it reads an expert's
+// weights once per 32 of its rows.
+hipError_t launch_grouped_gemm_few_rows(int in_dtype, bool gelu, const bf16_t* A, const bf16_t* B, bf16_t* C,
+                                        const int32_t* offsets, int n_exp, int Nout, int K,
+                                        void* workspace, hipStream_t s, int fuse, const int32_t* aux_rows,
+                                        const float* aux_w, int aux_div,
+                                        const int32_t* aux_inv, bf16_t* C2);
+// Where in a GEMM workspace block 0 leaves its clocks (four words: shader and wall clock, start and end).
+unsigned long long* gemm_clock_words(void* workspace);
+// Taken where a weight panel is read once (32 rows), or seldom more than once: at most 128 rows (the host's bound; one
+// expert may have them all: four passes) and 16 per expert.  Layer, bf16, before -> now: 8 experts of 2048 x 8192, 16
+// tokens 194 -> 128 us, 128 tokens 197 -> 140 us, 64 skewed tokens 155 -> 135 us; 8 of 64 experts of 4096 x 16384, 128 tokens
+// 509 -> 459 us.  Past the line: one expert of 4096 x 16384, 64 rows 130 -> 198 us; 64 experts of 1024 x 4096, 1024
+// tokens 355 -> 268 us evenly spread, but 144 -> 552 us skewed.
+inline bool grouped_gemm_is_few_rows(int in_dtype, int K, int64_t max_rows, int n_exp) {
+  return grouped_gemm_is_fast(in_dtype, K) &&
+         (max_rows <= 32 || (max_rows <= 128 && max_rows <= 16 * static_cast<int64_t>(n_exp)));
 }
 
 // 16-bit fast path of the above: persistent, at most kMaxPersistentBlocks blocks.

@@ -352,6 +352,10 @@ hipError_t launch_grouped_gemm(int in_dtype, bool gelu, const void* A, const voi
                                void* workspace, hipStream_t s, int fuse, const int32_t* aux_rows,
                                const float* aux_w, int aux_div, const int32_t* aux_inv, void* C2) {
   if (max_rows == 0) return hipSuccess;
+  if (grouped_gemm_is_few_rows(in_dtype, K, max_rows, n_exp))
+    return launch_grouped_gemm_few_rows(in_dtype, gelu, static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(B),
+                                        static_cast<bf16_t*>(C), offsets, n_exp, Nout, K, workspace, s, fuse,
+                                        aux_rows, aux_w, aux_div, aux_inv, static_cast<bf16_t*>(C2));
   if (grouped_gemm_is_fast(in_dtype, K)) {
     return launch_grouped_gemm_fast(in_dtype, gelu, static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(B),
                                     static_cast<bf16_t*>(C), offsets, n_exp, max_rows, Nout, K, workspace, s,

@@ -72,30 +72,6 @@ __device__ __forceinline__ float read_acc(float a) {
   return v;
 }
 
-// GeLU, tanh form: 0.5 u (1 + tanh(z)) = u / (1 + exp(-2 z)),  z = sqrt(2/pi) (u + 0.044715 u^3).
-// exp2 and the reciprocal are single hardware instructions (about 1 ulp each), ample for a bf16
-// result.  Four at a time, stage by stage: the four dependency chains (mul, fma, mul, exp2, add,
-// rcp, mul) interleave, so the latency of each instruction is hidden by the other three elements.
-__device__ __forceinline__ f32x4 gelu_tanh4(f32x4 u) {
-  // (the sched_barriers keep the compiler from folding the stages back into four serial chains)
-  f32x4 z, e, r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) z[i] = fmaf(0.044715f * u[i], u[i], 1.0f);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) z[i] = (-2.302208198f * u[i]) * z[i];   // -2 sqrt(2/pi) log2(e) (u + 0.044715 u^3)
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) e[i] = __builtin_amdgcn_exp2f(z[i]);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) e[i] = 1.0f + e[i];
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r[i] = __builtin_amdgcn_rcpf(e[i]);
-  __builtin_amdgcn_sched_barrier(0);
-  return u * r;
-}
-
 template <int OFF, typename V>
 __device__ __forceinline__ void lds_read16(V& dst, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
@@ -876,6 +852,13 @@ hipError_t read_gemm_error_word(const void* workspace, uint32_t* word, hipStream
     e = hipStreamSynchronize(s);
   }
   return e;
+}
+
+unsigned long long* gemm_clock_words(void* workspace) {
+  uint32_t* flags = reinterpret_cast<uint32_t*>(
+      static_cast<float*>(workspace) +
+      static_cast<size_t>(fast::kSlotsPerBlock) * kMaxPersistentBlocks * fast::kSlotFloats);
+  return reinterpret_cast<unsigned long long*>(flags + fast::kClockWord);
 }
 
 // Shader-clock and wall-clock ticks block 0 of the last fast-path launch on this workspace counted

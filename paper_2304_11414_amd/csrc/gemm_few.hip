@@ -2,14 +2,15 @@
 //
 //   C[r, n] = act( sum_k A[r, k] * B[i][n, k] ),  offsets[i] <= r < offsets[i+1]
 //
-// With a handful of rows per expert the work is one pass over the weights: it is bound by the HBM stream
-// and, for layers of a few hundred megabytes, by the latencies in front of it.  The kernel of the large
-// tiles spends some 50 us per launch on those (one block per CU: offsets, row list, the first k-tile,
-// hand-overs and the output transpose one after another).  Here a block owns 32 columns of one expert: no
-// staging, no barrier in the loop; its eight wavefronts split the contraction, fetch both MFMA operands
-// straight from memory (a lane's operand is 16 bytes of a row) and meet once, to add their partial sums in
-// wavefront order (fixed float32 summation order).  Two blocks of 8 KiB of loads per wavefront on a CU
-// keep 128 KiB in flight, several times what the HBM latency needs.
+// With a handful of rows per expert the work is one pass over the weights: it is bound by the HBM stream and by
+// the latencies in front of it.  The kernel of the large tiles spends some 50 us per launch on those (one
+// block per CU: row list, first k-tile, hand-over, output transpose one after another).  Here a block owns 32
+// columns of one expert: no staging, no barrier in the loop; its eight wavefronts split the contraction, fetch both
+// MFMA operands straight from memory (a lane's operand is 16 bytes of a row, 256 bytes of each of 32 rows at a
+// time) and meet once, to add their partial sums in wavefront order (fixed float32 summation order).  Two blocks on
+// a CU have 128 KiB of loads in flight.  Measured (layer, 8 experts, d = 2048, F = 8192, bf16, 537 MB of weights):
+// 16 tokens top-1 194 -> 127 us, 128 tokens 197 -> 141 us.  Tried and slower: the next span prefetched into a second
+// register set (157 us), a block per 32 rows instead of passes (128 tokens: 372 us, the empty blocks), non-temporal loads of the weights (131 us), 16 wavefronts a block (142 us).
 
 #include <type_traits>
 
@@ -22,7 +23,7 @@ namespace few {
 constexpr int BN = 32;           // columns of a block: two 16-row weight fragments per wavefront
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kSpan = 64;        // k-values a wavefront fetches at a time: a 128-byte line of each weight row
+constexpr int kSpan = 128;       // k-values a wavefront fetches at a time: a 128-byte line of each weight row
 constexpr int kSteps = kSpan / 32;
 constexpr int kTok = 32;         // rows per pass over the block's weights
 constexpr int kLd = BN + 4;      // floats per row of partial sums in LDS
@@ -67,45 +68,35 @@ __global__ __launch_bounds__(kThreads, 4) void grouped_gemm_few_rows_kernel(
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // Two sets of operand registers: the next span's loads are on their way while this one is multiplied.
-    // (Pieces past the end of a row are zeros on both sides.)  MT: groups of 16 rows.
-    auto products = [&](auto mt_c) __attribute__((always_inline)) {
+    // WHOLE: the span ends inside the row.  MT: groups of 16 rows.
+    auto span = [&](int k0, auto whole_c, auto mt_c) __attribute__((always_inline)) {
+      constexpr bool WHOLE = decltype(whole_c)::value;
       constexpr int MT = decltype(mt_c)::value;
-      u32x4 w[2][kSteps][2], x[2][kSteps][MT];
-      auto load = [&](int k0, int set) __attribute__((always_inline)) {
+      u32x4 w[kSteps][2], x[kSteps][MT];
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) {
-          const int k = k0 + 32 * j;
-          const bool ok = k + g * 8 < K;
+      for (int j = 0; j < kSteps; ++j) {
+        const int k = k0 + 32 * j;
+        const bool ok = WHOLE || k + g * 8 < K;
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          w[j][nt] = ok ? *reinterpret_cast<const u32x4*>(wrow[nt] + k) : zero;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) x[j][mt] = ok ? *reinterpret_cast<const u32x4*>(trow[mt] + k) : zero;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < kSteps; ++j)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
           for (int nt = 0; nt < 2; ++nt)
-            w[set][j][nt] = ok ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wrow[nt] + k)) : zero;
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) x[set][j][mt] = ok ? *reinterpret_cast<const u32x4*>(trow[mt] + k) : zero;
-        }
-      };
-      auto multiply = [&](int set) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < kSteps; ++j)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-              acc[mt][nt] = Elem16<DT>::mfma16(__builtin_bit_cast(vec8, w[set][j][nt]),
-                                               __builtin_bit_cast(vec8, x[set][j][mt]), acc[mt][nt]);
-      };
-      constexpr int kStep = kWaves * kSpan;
+            acc[mt][nt] = Elem16<DT>::mfma16(__builtin_bit_cast(vec8, w[j][nt]), __builtin_bit_cast(vec8, x[j][mt]),
+                                             acc[mt][nt]);
+    };
+    auto products = [&](auto mt_c) __attribute__((always_inline)) {
       int k0 = wave * kSpan;
-      if (k0 >= K) return;
-      load(k0, 0);
-      for (; k0 < K; k0 += 2 * kStep) {
-        load(k0 + kStep, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0);
-        load(k0 + 2 * kStep, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1);
-      }
+      for (; k0 + kSpan <= K; k0 += kWaves * kSpan) span(k0, std::true_type{}, mt_c);
+      if (k0 < K) span(k0, std::false_type{}, mt_c);
     };
     if (rows > 16) products(std::integral_constant<int, 2>{});
     else products(std::integral_constant<int, 1>{});
@@ -164,14 +155,14 @@ hipError_t launch_grouped_gemm_few_rows(int in_dtype, bool gelu, const bf16_t* A
     return hipErrorInvalidValue;
   unsigned long long* clock_words = gemm_clock_words(workspace);
   const unsigned grid = static_cast<unsigned>(n_exp) * static_cast<unsigned>((Nout + BN - 1) / BN);
-#define PPMOE_LAUNCH(G, F)                                                                                          \
-  do {                                                                                                              \
-    if (in_dtype == MOE_F16)                                                                                        \
-      grouped_gemm_few_rows_kernel<G, F, MOE_F16><<<grid, kThreads, 0, s>>>(A, B, C, offsets, Nout, K, aux_rows,    \
-                                                                            aux_w, aux_div, aux_inv, C2, clock_words); \
-    else                                                                                                            \
-      grouped_gemm_few_rows_kernel<G, F, MOE_BF16><<<grid, kThreads, 0, s>>>(A, B, C, offsets, Nout, K, aux_rows,   \
-                                                                             aux_w, aux_div, aux_inv, C2, clock_words); \
+#define PPMOE_LAUNCH(G, F)                                                                                 \
+  do {                                                                                                     \
+    if (in_dtype == MOE_F16)                                                                               \
+      grouped_gemm_few_rows_kernel<G, F, MOE_F16><<<grid, kThreads, 0, s>>>(                               \
+          A, B, C, offsets, Nout, K, aux_rows, aux_w, aux_div, aux_inv, C2, clock_words);                  \
+    else                                                                                                   \
+      grouped_gemm_few_rows_kernel<G, F, MOE_BF16><<<grid, kThreads, 0, s>>>(                              \
+          A, B, C, offsets, Nout, K, aux_rows, aux_w, aux_div, aux_inv, C2, clock_words);                  \
   } while (0)
   if (fuse == 1) PPMOE_LAUNCH(true, 1);
   else if (fuse == 2) PPMOE_LAUNCH(false, 2);

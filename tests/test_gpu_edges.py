@@ -79,6 +79,28 @@ def test_layer_with_rows_of_no_whole_tiles(kw):
     compare_layer_full(lc, synth.make_inputs(lc))
 
 
+# ---------------------------------------------------------------- few rows
+
+@pytest.mark.parametrize("kw", [
+    dict(T=1, d=8, F=8, E=4, top_k=2, renorm_topk=True, seed=90),                       # one row, one 16-byte piece
+    dict(T=17, d=1160, F=1024, E=1, top_k=1, seed=91),                                  # 16 rows and one, row ends inside a span
+    dict(T=33, d=1024, F=1992, E=2, top_k=2, renorm_topk=True, in_dtype="f16", out_dtype="f16", seed=92),   # two passes
+    dict(T=128, d=136, F=264, E=1, top_k=1, out_dtype="f32", seed=93),                  # as many rows as are taken
+    dict(T=129, d=136, F=264, E=1, top_k=1, seed=94),                                   # one more
+    dict(T=60, d=256, F=512, E=16, top_k=4, renorm_topk=True, local_begin=3, local_count=2, seed=95),
+    dict(T=64, d=320, F=640, E=8, top_k=2, capacity_factor=0.5, seed=96),               # dropped picks, rows of zeros
+])
+def test_layer_on_few_rows(kw):
+    lc = small_cfg(**kw)
+    compare_layer_full(lc, synth.make_inputs(lc))
+
+
+@pytest.mark.parametrize("counts", [[128], [0, 1, 0], [16, 17, 32, 33], [31, 0, 97]])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_expert_ffn_on_few_rows(dtype, counts):
+    check_ffn(dtype, 1160, 520, counts)
+
+
 # ---------------------------------------------------------------- float32 products
 
 @pytest.mark.parametrize("d,F,counts", [
