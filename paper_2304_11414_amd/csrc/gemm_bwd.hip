@@ -137,7 +137,8 @@ __device__ __forceinline__ int tail_rows_of(int n, int threshold) {
   const int t = n & 255;
   return t <= threshold ? t : 0;
 }
-__device__ __forceinline__ int tail_threshold(const int32_t* __restrict__ offsets, int n_exp, int N, int tail_cus) {
+__device__ __forceinline__ int tail_threshold(const int32_t* __restrict__ offsets, int n_exp, int N, int tail_cus,
+                                              int pick_cus) {
   if (tail_cus <= 0) return 0;   // (the launcher has not provided for the two extra launches)
   const int n_tiles = (N + 255) / 256;
   int all = 0, big[2] = {0, 0}, blocks[2] = {0, 0};   // candidates 128 and 255
@@ -151,6 +152,7 @@ __device__ __forceinline__ int tail_threshold(const int32_t* __restrict__ offset
       blocks[c] += (t + 31) / 32;
     }
   }
+  if (2 * all < pick_cus) return 0;   // (the 128 x 128 launch has all the rows)
   const int rounds_all = (all + tail_cus - 1) / tail_cus;
   int saved[2];
 #pragma unroll
@@ -166,11 +168,21 @@ __device__ __forceinline__ int tail_threshold(const int32_t* __restrict__ offset
   return saved[1] > 0 ? 255 : 0;
 }
 
+// The data gradient's tile shape where the host's bound on the rows is loose (a rank with some of the
+// experts may get any share of the assignments): pick_cus = number of CUs says that both shapes are
+// launched and the row counts decide; the 256 x 256 launch leaves when it would leave more than half of the
+// CUs without a tile, else the 128 x 128 launch does.  0: no such choice.
+__device__ __forceinline__ bool few_big_tiles(const int32_t* __restrict__ offsets, int n_exp, int N, int pick_cus) {
+  int all = 0;
+  for (int i = 0; i < n_exp; ++i) all += (offsets[i + 1] - offsets[i] + 255) / 256;
+  return 2 * all * ((N + 255) / 256) < pick_cus;
+}
+
 // tail_cus (MODE 0 only): 0, or the number of CUs when the launcher runs the tail launches as well.
 template <int MODE, int BM, int BN>
 __device__ __forceinline__ bool locate_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                             const int32_t* __restrict__ offsets, int n_exp, int M, int N,
-                                            int K, TileInfo& ti, int tail_cus = 0) {
+                                            int K, TileInfo& ti, int tail_cus = 0, int pick_cus = 0) {
   const int n_tiles = (N + BN - 1) / BN;
   ti.expert = ti.row0 = ti.rows = ti.col0 = ti.m0 = ti.kt_count = 0;
   // Consecutive block ids land on different XCDs (round robin over 8): remap so that each XCD works on
@@ -182,7 +194,7 @@ __device__ __forceinline__ bool locate_tile(const bf16_t* __restrict__ A, const 
   };
   if (MODE == 0) {
     // tiles ordered expert-major, then n-tile, then m-tile; blocks past the last tile leave
-    const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus);
+    const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus, pick_cus);
     int total = 0;
     for (int i = 0; i < n_exp; ++i) {
       const int n = offsets[i + 1] - offsets[i];
@@ -354,9 +366,10 @@ __device__ __forceinline__ void accumulate_tile(const TileInfo& ti, int kt_begin
 template <int MODE, int DT, int BM, int BN>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ C,
-    const int32_t* __restrict__ offsets, int n_exp, int M, int N, int K) {
+    const int32_t* __restrict__ offsets, int n_exp, int M, int N, int K, int pick_cus) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   TileInfo ti;
+  if (MODE == 0 && pick_cus > 0 && !few_big_tiles(offsets, n_exp, N, pick_cus)) return;
   if (!locate_tile<MODE, BM, BN>(A, B, offsets, n_exp, M, N, K, ti)) return;
   f32x16 acc[BM / 64][BN / 64];
   accumulate_tile<MODE, DT, BM, BN, false>(ti, 0, ti.kt_count, acc, lds);
@@ -370,10 +383,11 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_kernel(
 template <int DT>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_tail_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, float* __restrict__ partial,
-    const int32_t* __restrict__ offsets, int n_exp, int N, int K, int splits, int tail_cus) {
+    const int32_t* __restrict__ offsets, int n_exp, int N, int K, int splits, int tail_cus,
+    int pick_cus) {
   constexpr int BM = kTailTile, BN = 128;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus);
+  const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus, pick_cus);
   if (tail_thr == 0) return;
   const int n_tiles = (N + BN - 1) / BN;
   int b = blockIdx.x;
@@ -425,8 +439,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_tail_kernel(
 template <int DT>
 __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restrict__ partial, bf16_t* __restrict__ C,
                                                           const int32_t* __restrict__ offsets, int n_exp, int N,
-                                                          int splits, int tail_cus) {
-  const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus);
+                                                          int splits, int tail_cus, int pick_cus) {
+  const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus, pick_cus);
   if (tail_thr == 0) return;
   const int expert = blockIdx.x >> 8, r = blockIdx.x & 255;
   const int lo = offsets[expert], hi = offsets[expert + 1];
@@ -479,7 +493,7 @@ __device__ __forceinline__ void lds_write16_at(uint32_t addr, const u32x4& v) {
 template <int MODE, int DT>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_pipelined_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ C,
-    const int32_t* __restrict__ offsets, int n_exp, int M, int N, int K, int tail_cus) {
+    const int32_t* __restrict__ offsets, int n_exp, int M, int N, int K, int tail_cus, int pick_cus) {
   constexpr int BM = 256, BN = 256, MI = 4, NI = 4;
   constexpr int kATileBytes = BM * kRowBytes;
   constexpr int kStageBytes = (BM + BN) * kRowBytes;
@@ -487,7 +501,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_pipelined_kernel(
   typedef typename Elem16<DT>::vec8 vec8;
 
   TileInfo ti;
-  if (!locate_tile<MODE, BM, BN>(A, B, offsets, n_exp, M, N, K, ti, MODE == 0 ? tail_cus : 0)) return;
+  if (MODE == 0 && few_big_tiles(offsets, n_exp, N, pick_cus)) return;
+  if (!locate_tile<MODE, BM, BN>(A, B, offsets, n_exp, M, N, K, ti, MODE == 0 ? tail_cus : 0, pick_cus)) return;
   const int kt_count = ti.kt_count;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -924,24 +939,39 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
     const int64_t nt = (n_out + bn - 1) / bn;
     return mode == 0 ? ((m_out + bm - 1) / bm + N) * nt : static_cast<int64_t>(N) * ((m_out + bm - 1) / bm) * nt;
   };
-#define PPMOE_BWD(MODE, a, b, cc, m, n, k, m_out, tail_cus)                                                    \
+  // Where the rank holds some of the experts, `rows` bounds its rows at every assignment there is.  If an even
+  // share of them would be too few tiles for the 256 x 256 kernel, both shapes are launched and the row counts
+  // decide (few_big_tiles; the launch that leaves costs about 5 us).
+  auto pick_of = [&](int n_out) -> int {
+    const int64_t share = rows * N / (c.E > 0 ? c.E : 1);
+    return N < c.E && 2 * tiles_of(0, share, n_out, 256, 256) < n_cus ? n_cus : 0;
+  };
+#define PPMOE_BWD(MODE, a, b, cc, m, n, k, m_out, tail_cus, pick)                                              \
   do {                                                                                                         \
     const bool big = 2 * tiles_of(MODE, m_out, n, 256, 256) >= n_cus && (MODE == 1 || (k) % BK == 0);          \
-    const int t = big ? 256 : 128;                                                                             \
-    const unsigned grid = static_cast<unsigned>((tiles_of(MODE, m_out, n, t, t) + 7) / 8 * 8);                 \
-    const size_t shm = lds_bytes(t, t);                                                                        \
-    if (big && c.in_dtype == MOE_F16)                                                                          \
-      grouped_gemm_bwd_pipelined_kernel<MODE, MOE_F16><<<grid, kThreads, shm, s>>>(a, b, cc, offsets, N, m, n, k, tail_cus); \
-    else if (big)                                                                                              \
-      grouped_gemm_bwd_pipelined_kernel<MODE, MOE_BF16><<<grid, kThreads, shm, s>>>(a, b, cc, offsets, N, m, n, k, tail_cus); \
-    else if (c.in_dtype == MOE_F16)                                                                            \
-      grouped_gemm_bwd_kernel<MODE, MOE_F16, 128, 128><<<grid, kThreads, shm, s>>>(a, b, cc, offsets, N, m, n, k);       \
-    else                                                                                                       \
-      grouped_gemm_bwd_kernel<MODE, MOE_BF16, 128, 128><<<grid, kThreads, shm, s>>>(a, b, cc, offsets, N, m, n, k);      \
+    const int pick_cus = big ? (pick) : 0;                                                                     \
+    if (big) {                                                                                                 \
+      const unsigned grid = static_cast<unsigned>((tiles_of(MODE, m_out, n, 256, 256) + 7) / 8 * 8);           \
+      const size_t shm = lds_bytes(256, 256);                                                                  \
+      if (c.in_dtype == MOE_F16)                                                                               \
+        grouped_gemm_bwd_pipelined_kernel<MODE, MOE_F16><<<grid, kThreads, shm, s>>>(a, b, cc, offsets, N, m, n, k, tail_cus, pick_cus); \
+      else                                                                                                     \
+        grouped_gemm_bwd_pipelined_kernel<MODE, MOE_BF16><<<grid, kThreads, shm, s>>>(a, b, cc, offsets, N, m, n, k, tail_cus, pick_cus); \
+    }                                                                                                          \
+    if (!big || pick_cus > 0) {                                                                                \
+      /* (as a second shape it has fewer than n_cus / 2 tiles of 256 x 256 to do, each four of its own) */     \
+      const int64_t tiles = big ? 2 * n_cus : tiles_of(MODE, m_out, n, 128, 128);                              \
+      const unsigned grid = static_cast<unsigned>((tiles + 7) / 8 * 8);                                        \
+      const size_t shm = lds_bytes(128, 128);                                                                  \
+      if (c.in_dtype == MOE_F16)                                                                               \
+        grouped_gemm_bwd_kernel<MODE, MOE_F16, 128, 128><<<grid, kThreads, shm, s>>>(a, b, cc, offsets, N, m, n, k, pick_cus); \
+      else                                                                                                     \
+        grouped_gemm_bwd_kernel<MODE, MOE_BF16, 128, 128><<<grid, kThreads, shm, s>>>(a, b, cc, offsets, N, m, n, k, pick_cus); \
+    }                                                                                                          \
   } while (0)
 
   // dH = dY B^T  (into the dU buffer), then H = GeLU(U), dU = dH * GeLU'(U) in place
-  PPMOE_BWD(0, dy, w2, dU, 0, c.F, c.d, rows, 0);
+  PPMOE_BWD(0, dy, w2, dU, 0, c.F, c.d, rows, 0, pick_of(c.F));
   {
     const int blocks = static_cast<int>(rows < 256 * 16 ? (rows > 0 ? rows : 1) : 256 * 16);
     if (c.in_dtype == MOE_F16)
@@ -953,26 +983,27 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
   // small launches of their own (every block of the three takes that decision from the row counts)
   const bool dx_big = 2 * tiles_of(0, rows, c.d, 256, 256) >= n_cus && c.F % BK == 0;
   const int tail_cus = (dx_big && c.F >= 4096 && tail_partial_bytes(c) > 0) ? n_cus : 0;
-  PPMOE_BWD(0, dU, w1, dX, 0, c.d, c.F, rows, tail_cus);
+  const int dx_pick = dx_big ? pick_of(c.d) : 0;
+  PPMOE_BWD(0, dU, w1, dX, 0, c.d, c.F, rows, tail_cus, dx_pick);
   if (tail_cus > 0) {
     int splits = c.F / BK / 16;
     splits = splits < 1 ? 1 : splits > kTailSplitsMax ? kTailSplitsMax : splits;
     const unsigned tail_grid = static_cast<unsigned>(N * 2 * ((c.d + 127) / 128) * splits);
     if (c.in_dtype == MOE_F16) {
       grouped_gemm_bwd_tail_kernel<MOE_F16><<<tail_grid, kThreads, lds_bytes(kTailTile, 128), s>>>(
-          dU, w1, tail_partial, offsets, N, c.d, c.F, splits, tail_cus);
+          dU, w1, tail_partial, offsets, N, c.d, c.F, splits, tail_cus, dx_pick);
       tail_reduce_kernel<MOE_F16><<<N * 256, 256, 0, s>>>(tail_partial, static_cast<bf16_t*>(dX), offsets, N,
-                                                                c.d, splits, tail_cus);
+                                                                c.d, splits, tail_cus, dx_pick);
     } else {
       grouped_gemm_bwd_tail_kernel<MOE_BF16><<<tail_grid, kThreads, lds_bytes(kTailTile, 128), s>>>(
-          dU, w1, tail_partial, offsets, N, c.d, c.F, splits, tail_cus);
+          dU, w1, tail_partial, offsets, N, c.d, c.F, splits, tail_cus, dx_pick);
       tail_reduce_kernel<MOE_BF16><<<N * 256, 256, 0, s>>>(tail_partial, static_cast<bf16_t*>(dX), offsets, N,
-                                                                 c.d, splits, tail_cus);
+                                                                 c.d, splits, tail_cus, dx_pick);
     }
   }
   // dB^T[i] = dY_i^T H_i  ([d, F]);  dA^T[i] = dU_i^T X_i  ([F, d])
-  PPMOE_BWD(1, dy, H, dW2, c.d, c.F, 0, c.d, 0);
-  PPMOE_BWD(1, dU, xs, dW1, c.F, c.d, 0, c.F, 0);
+  PPMOE_BWD(1, dy, H, dW2, c.d, c.F, 0, c.d, 0, 0);
+  PPMOE_BWD(1, dU, xs, dW1, c.F, c.d, 0, c.F, 0, 0);
 #undef PPMOE_BWD
   return hipGetLastError();
 }

@@ -125,3 +125,28 @@ def test_expert_ffn_in_float32(d, F, counts):
 ])
 def test_router_on_few_tokens(T, d, E, k, dtype):
     check_router(dict(T=T, d=d, F=64, E=E, top_k=k, renorm_topk=k > 1, in_dtype=dtype, out_dtype=dtype, seed=101))
+
+
+# ---------------------------------------------------------------- data gradient of a rank with some of the experts
+
+@pytest.mark.parametrize("counts", [
+    [60, 0, 300, 33],        # an even share and less: the 128 x 128 launch has the rows
+    [4000, 60, 0, 36],       # one expert with nearly all: the 256 x 256 launch has them
+    [3840, 0, 0, 0],         # 15 row tiles x 8 column tiles: one fewer than would fill half of 256 CUs
+    [3841, 0, 0, 0],
+])
+def test_data_gradient_tiles_follow_the_rows(counts):
+    d, F = 2048, 256
+    lc = small_cfg(T=4096, d=d, F=F, E=64, top_k=1, local_begin=4, local_count=4, seed=110)
+    inp = synth.make_inputs(lc, parts=("x", "W1_t", "W2_t"))
+    inp["W1_t"] *= 8.0
+    inp["W2_t"] *= 8.0
+    mv = synth.math_views(inp)
+    A = sum(counts)
+    x = inp["x"][:A]
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    dY = np.random.default_rng(7).standard_normal((A, d)).astype(np.float32)
+    synth.round_to_bf16(dY)
+    ref = O.expert_ffn_backward(x, offsets, mv["W1"], mv["W2"], dY)
+    dX = DeviceLayer(lc, inp).run_ffn_backward(x, offsets, dY)[0]
+    assert_close(dX, ref["dX"], TOL["bf16"], "dX_sliced", GRAD_ELEM_FACTOR * TOL["bf16"])
