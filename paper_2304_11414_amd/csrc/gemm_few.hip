@@ -10,7 +10,8 @@
 // time) and meet once, to add their partial sums in wavefront order (fixed float32 summation order).  Two blocks on
 // a CU have 128 KiB of loads in flight.  Measured (layer, 8 experts, d = 2048, F = 8192, bf16, 537 MB of weights):
 // 16 tokens top-1 194 -> 127 us, 128 tokens 197 -> 141 us.  Tried and slower: the next span prefetched into a second
-// register set (157 us), a block per 32 rows instead of passes (128 tokens: 372 us, the empty blocks), non-temporal loads of the weights (131 us), 16 wavefronts a block (142 us).
+// register set (157 us), a block per 32 rows instead of passes (128 tokens: 372 us, the empty blocks), non-temporal
+// loads of the weights (131 us), 16 wavefronts a block (142 us).
 
 #include <type_traits>
 
