@@ -250,22 +250,37 @@ inline bool grouped_gemm_can_fuse(int in_dtype, int K, int64_t a_rows) {
 }
 
 // The 16-bit GEMM on few rows (any K, same `fuse` contract): right for any row counts, it reads an expert's
-// weights once per 32 of its rows.
+// weights once per 64 of its rows.  most > 0: it leaves, nothing done, if an expert has more rows than that.
 hipError_t launch_grouped_gemm_few_rows(int in_dtype, bool gelu, const bf16_t* A, const bf16_t* B, bf16_t* C,
-                                        const int32_t* offsets, int n_exp, int Nout, int K,
+                                        const int32_t* offsets, int n_exp, int Nout, int K, int most,
                                         void* workspace, hipStream_t s, int fuse, const int32_t* aux_rows,
                                         const float* aux_w, int aux_div,
                                         const int32_t* aux_inv, bf16_t* C2);
 // Where in a GEMM workspace block 0 leaves its clocks (four words: shader and wall clock, start and end).
 unsigned long long* gemm_clock_words(void* workspace);
-// Taken where a weight panel is read once (32 rows), or seldom more than once: at most 128 rows (the host's bound; one
-// expert may have them all: four passes) and 16 per expert.  Layer, bf16, before -> now: 8 experts of 2048 x 8192, 16
-// tokens 194 -> 128 us, 128 tokens 197 -> 140 us, 64 skewed tokens 155 -> 135 us; 8 of 64 experts of 4096 x 16384, 128 tokens
-// 509 -> 459 us.  Past the line: one expert of 4096 x 16384, 64 rows 130 -> 198 us; 64 experts of 1024 x 4096, 1024
-// tokens 355 -> 268 us evenly spread, but 144 -> 552 us skewed.
-inline bool grouped_gemm_is_few_rows(int in_dtype, int K, int64_t max_rows, int n_exp) {
-  return grouped_gemm_is_fast(in_dtype, K) &&
-         (max_rows <= 32 || (max_rows <= 128 && max_rows <= 16 * static_cast<int64_t>(n_exp)));
+// The most rows one expert may have for that kernel to be taken; 0: it is not taken whatever the counts.  With at most
+// 32 rows or, up to 128, 16 per expert (the host's bound `max_rows`) it is the faster one as long as the fetches of the
+// rows by every block of 32 columns, rows x K x Nout, stay behind what the other kernel loses to latencies.  Layer, bf16,
+// that kernel -> this one, all rows on one of 8 experts: 128 rows of 2048 x 8192 127 -> 128 us, of 1024 x 4096 104 -> 74;
+// 4096 x 16384: 32 rows 119 -> 111, 48 rows 132 -> 136, 128 rows 172 -> 279; in one pass over the weights (32 rows) also
+// further on: 5120 x 20480 166 -> 161, 8192 x 28672 24 rows 265 -> 254, 32 rows 267 -> 274.  Evenly spread, 128 tokens over 8
+// experts of 2048 x 8192: 195 -> 137.  A bound above the result does not say where the rows are: both kernels
+// are launched and the counts decide on the device (launch_grouped_gemm).
+// Beyond 128 rows or 16 per expert: one expert of 4096 x 16384, 64 rows 130 -> 150 us.
+inline int grouped_gemm_few_rows_most(int in_dtype, int Nout, int K, int64_t max_rows, int n_exp) {
+  if (!grouped_gemm_is_fast(in_dtype, K) || (max_rows > 32 && (max_rows > 128 || max_rows > 16 * static_cast<int64_t>(n_exp))))
+    return 0;
+  const int64_t weights = static_cast<int64_t>(Nout) * K;
+  const int64_t one_pass = (3ll << 31) / weights < 32 ? (3ll << 31) / weights : 32;
+  const int64_t most = (1ll << 31) / weights > one_pass ? (1ll << 31) / weights : one_pass;
+  if (max_rows > most && n_exp == 1) return 0;   // (the bound is what it will be)
+  return static_cast<int>(most < 128 ? most : 128);
+}
+// Has no expert more than `most` rows?  (The same answer in every wavefront of a launch.)
+__device__ __forceinline__ bool no_expert_above(const int32_t* __restrict__ offsets, int n_exp, int most) {
+  bool above = false;
+  for (int i = threadIdx.x & 63; i < n_exp; i += 64) above |= offsets[i + 1] - offsets[i] > most;
+  return __ballot(above) == 0;
 }
 
 // 16-bit fast path of the above: persistent, at most kMaxPersistentBlocks blocks.
@@ -288,8 +303,9 @@ hipError_t grouped_gemm_fast_init(hipStream_t s);
 // spin_limit: polls of a flag before the reader gives up and computes the missing k range itself
 // (0 = never wait).
 void grouped_gemm_fast_set_handover(int force_device_scope, int spin_limit);
+// few_most > 0: leaves, nothing done, if no expert has more rows than that.
 hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, const bf16_t* B, bf16_t* C,
-                                    const int32_t* offsets, int n_exp, int64_t max_rows, int Nout,
+                                    const int32_t* offsets, int n_exp, int few_most, int Nout,
                                     int K, void* workspace, hipStream_t s, int fuse,
                                     const int32_t* aux_rows, const float* aux_w, int aux_div,
                                     const int32_t* aux_inv, bf16_t* C2);

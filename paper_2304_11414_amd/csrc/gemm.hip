@@ -352,13 +352,17 @@ hipError_t launch_grouped_gemm(int in_dtype, bool gelu, const void* A, const voi
                                void* workspace, hipStream_t s, int fuse, const int32_t* aux_rows,
                                const float* aux_w, int aux_div, const int32_t* aux_inv, void* C2) {
   if (max_rows == 0) return hipSuccess;
-  if (grouped_gemm_is_few_rows(in_dtype, K, max_rows, n_exp))
-    return launch_grouped_gemm_few_rows(in_dtype, gelu, static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(B),
-                                        static_cast<bf16_t*>(C), offsets, n_exp, Nout, K, workspace, s, fuse,
-                                        aux_rows, aux_w, aux_div, aux_inv, static_cast<bf16_t*>(C2));
+  const int few_most = grouped_gemm_few_rows_most(in_dtype, Nout, K, max_rows, n_exp);
+  if (few_most > 0) {
+    const bool sure = max_rows <= few_most;   // else both are launched, and one of them leaves (about 4 us)
+    const hipError_t e = launch_grouped_gemm_few_rows(
+        in_dtype, gelu, static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(B), static_cast<bf16_t*>(C), offsets,
+        n_exp, Nout, K, sure ? 0 : few_most, workspace, s, fuse, aux_rows, aux_w, aux_div, aux_inv, static_cast<bf16_t*>(C2));
+    if (e != hipSuccess || sure) return e;
+  }
   if (grouped_gemm_is_fast(in_dtype, K)) {
     return launch_grouped_gemm_fast(in_dtype, gelu, static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(B),
-                                    static_cast<bf16_t*>(C), offsets, n_exp, max_rows, Nout, K, workspace, s,
+                                    static_cast<bf16_t*>(C), offsets, n_exp, few_most, Nout, K, workspace, s,
                                     fuse, aux_rows, aux_w, aux_div, aux_inv, static_cast<bf16_t*>(C2));
   }
   if (fuse != 0) return hipErrorInvalidValue;   // the other kernels work on packed tensors only

@@ -218,13 +218,14 @@ __global__ __launch_bounds__(kThreads) void xcc_probe_kernel() {
 template <bool GELU, int FUSE, int DT, bool RAGGED>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
-    const int32_t* __restrict__ offsets, int n_exp, int Nout, int K, float* __restrict__ slots,
+    const int32_t* __restrict__ offsets, int n_exp, int few_most, int Nout, int K, float* __restrict__ slots,
     uint32_t* __restrict__ flags, uint32_t epoch, int same_l2, int spin_limit,
     const int32_t* __restrict__ aux_rows, const float* __restrict__ aux_w, int aux_div,
     const int32_t* __restrict__ aux_inv, bf16_t* __restrict__ C2) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   __shared__ int contrib[kMaxPersistentBlocks / 8 + 1];   // [0] = how many, then the block ids whose slots to add
   __shared__ int contrib_failed;
+  if (few_most > 0 && no_expert_above(offsets, n_exp, few_most)) return;   // (the kernel for few rows has done it)
   const uint32_t my_xcc = xcc_id();
   // A block's flag is down before it can be looked at: whatever the caller's workspace held, a stale
   // word cannot pass for this launch's epoch (the readers poll tens of microseconds from now).
@@ -968,7 +969,7 @@ void grouped_gemm_fast_set_handover(int force_device_scope, int spin_limit) {
 }
 
 hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, const bf16_t* B, bf16_t* C,
-                                    const int32_t* offsets, int n_exp, int64_t max_rows, int Nout,
+                                    const int32_t* offsets, int n_exp, int few_most, int Nout,
                                     int K, void* workspace, hipStream_t s, int fuse,
                                     const int32_t* aux_rows, const float* aux_w, int aux_div,
                                     const int32_t* aux_inv, bf16_t* C2) {
@@ -1005,7 +1006,6 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
   float* slots = static_cast<float*>(workspace);
   uint32_t* flags = reinterpret_cast<uint32_t*>(
       slots + static_cast<size_t>(kSlotsPerBlock) * kMaxPersistentBlocks * kSlotFloats);
-  (void)max_rows;
   const bool ragged = K % BK != 0;
   // fuse: 0 none; 1 rows of A through aux_rows (first GEMM only); 2 rows of the result placed through
   // aux_rows (second GEMM only; with aux_div > 1 it needs the inverse permutation and a place for
@@ -1016,7 +1016,7 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
     return hipErrorInvalidValue;
 #define PPMOE_LAUNCH_DT(G, F, DT, R)                                                  \
   grouped_gemm_bf16_fast_kernel<G, F, DT, R><<<blocks, kThreads, kLdsBytes, s>>>(     \
-      A, B, C, offsets, n_exp, Nout, K, slots, flags, epoch, same_l2, spin_limit, aux_rows, aux_w, aux_div, \
+      A, B, C, offsets, n_exp, few_most, Nout, K, slots, flags, epoch, same_l2, spin_limit, aux_rows, aux_w, aux_div, \
       aux_inv, C2)
 #define PPMOE_LAUNCH(G, F)                            \
   do {                                                \

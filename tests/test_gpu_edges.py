@@ -5,9 +5,10 @@ import numpy as np
 import pytest
 
 from oracle import ppmoe_oracle as O
+from paper_2304_11414_amd import binding as B
 from paper_2304_11414_amd import synth
-from tests.gpu_util import GRAD_ELEM_FACTOR, TOL, DeviceLayer, assert_close
-from tests.test_gpu_parity import check_dispatch, compare_layer_full, small_cfg
+from tests.gpu_util import GRAD_ELEM_FACTOR, TOL, DeviceLayer, assert_close, to_np, torch_dtype
+from tests.test_gpu_parity import check_dispatch, compare_layer_full, ragged_offsets, small_cfg
 from tests.test_gpu_parity import test_expert_ffn_on_oracle_rows as check_ffn
 from tests.test_gpu_parity import test_gate_router as check_router
 
@@ -84,21 +85,75 @@ def test_layer_with_rows_of_no_whole_tiles(kw):
 @pytest.mark.parametrize("kw", [
     dict(T=1, d=8, F=8, E=4, top_k=2, renorm_topk=True, seed=90),                       # one row, one 16-byte piece
     dict(T=17, d=1160, F=1024, E=1, top_k=1, seed=91),                                  # 16 rows and one, row ends inside a span
-    dict(T=33, d=1024, F=1992, E=2, top_k=2, renorm_topk=True, in_dtype="f16", out_dtype="f16", seed=92),   # two passes
-    dict(T=128, d=136, F=264, E=1, top_k=1, out_dtype="f32", seed=93),                  # as many rows as are taken
-    dict(T=129, d=136, F=264, E=1, top_k=1, seed=94),                                   # one more
-    dict(T=60, d=256, F=512, E=16, top_k=4, renorm_topk=True, local_begin=3, local_count=2, seed=95),
+    dict(T=33, d=1024, F=1992, E=2, top_k=2, renorm_topk=True, in_dtype="f16", out_dtype="f16", seed=92),   # 66 rows of 2 experts: too many
+    dict(T=128, d=136, F=264, E=8, top_k=1, out_dtype="f32", seed=93),                  # as many rows as are taken
+    dict(T=129, d=136, F=264, E=8, top_k=1, seed=94),                                   # one more
+    dict(T=32, d=256, F=512, E=16, top_k=4, renorm_topk=True, local_begin=3, local_count=8, seed=95),
     dict(T=64, d=320, F=640, E=8, top_k=2, capacity_factor=0.5, seed=96),               # dropped picks, rows of zeros
+    # nearly all rows on one or two experts: rows read and placed through the permutation, more than one pass
+    dict(T=64, d=328, F=640, E=8, top_k=2, renorm_topk=True, bias_kind="zipf", bias_s=40.0, seed=97),
+    dict(T=128, d=136, F=264, E=8, top_k=1, bias_kind="zipf", bias_s=40.0, in_dtype="f16", out_dtype="f16", seed=98),
+    dict(T=64, d=136, F=520, E=9, top_k=2, bias_kind="zipf", bias_s=40.0, local_begin=1, local_count=8, seed=99),
 ])
 def test_layer_on_few_rows(kw):
     lc = small_cfg(**kw)
     compare_layer_full(lc, synth.make_inputs(lc))
 
 
-@pytest.mark.parametrize("counts", [[128], [0, 1, 0], [16, 17, 32, 33], [31, 0, 97]])
+def run_ffn_and_see_the_kernel(lc, x, offsets, W1, W2):
+    """moe_expert_ffn on device tensors; returns H, y and whether the kernel of the large tiles has worked: its
+    blocks lower their hand-over flags (256 words before the other 257 words and 256 bytes that end the workspace)."""
+    import torch
+    cfg = B.config_from(lc)
+    ws = torch.full((B.moe_ffn_workspace_bytes(cfg),), 0xFF, dtype=torch.uint8, device="cuda")
+    rows = int(offsets[-1])
+    H = torch.empty((rows, lc.F), dtype=x.dtype, device="cuda")
+    y = torch.empty((rows, lc.d), dtype=x.dtype, device="cuda")
+    B.moe_expert_ffn(cfg, x, torch.from_numpy(offsets).cuda(), W1, W2, H, y, ws)
+    assert B.moe_ffn_check(cfg, ws, False) == 0
+    flags = ws[-(513 * 4 + 256):][: 256 * 4].view(torch.int32)
+    return H, y, bool((flags != -1).any())
+
+
+@pytest.mark.parametrize("counts,few", [
+    ([32], True), ([33], False),
+    ([0, 1, 0], True), ([31, 0, 17], True), ([32, 0, 17], False),               # 16 rows per expert, and one more
+    ([128, 0, 0, 0, 0, 0, 0, 0], True),                                         # two passes of 64 rows
+    ([0, 0, 65, 0, 0, 0, 0, 63], True),
+    ([33, 0, 1, 31, 32, 17, 14, 0], True), ([33, 0, 1, 31, 32, 17, 15, 0], False),   # 128 rows, and one more
+])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-def test_expert_ffn_on_few_rows(dtype, counts):
-    check_ffn(dtype, 1160, 520, counts)
+def test_expert_ffn_on_few_rows(dtype, counts, few):
+    check_ffn(dtype, 1160, 1032, counts)
+    lc = small_cfg(T=sum(counts), d=1160, F=1032, E=len(counts), top_k=1, in_dtype=dtype, out_dtype=dtype, seed=3)
+    dl = DeviceLayer(lc, synth.make_inputs(lc, parts=("x", "W1_t", "W2_t")))
+    assert run_ffn_and_see_the_kernel(lc, dl.x, ragged_offsets(counts), dl.W1, dl.W2)[2] != few
+
+
+@pytest.mark.parametrize("counts,few", [
+    ([16] * 8, True),
+    ([0, 1, 127, 0, 0, 0, 0, 0], True),            # 2^31 / (4096 * 4104) = 127 rows: the most one expert may have
+    ([128, 0, 0, 0, 0, 0, 0, 0], False),           # one more
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_few_rows_decided_by_the_counts(dtype, counts, few):
+    """Weights so large that an expert with many rows is better off on the large tiles: both kernels are launched,
+    one of them leaves.  Reference: the same products in float64 (torch)."""
+    import torch
+    d, F, n = 4096, 4104, len(counts)
+    lc = small_cfg(T=128, d=d, F=F, E=n, top_k=1, in_dtype=dtype, out_dtype=dtype)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch_dtype(dtype), device="cuda").normal_(0.0, std, generator=g)
+    x, W1, W2 = draw(1.0, 128, d), draw(0.02, n, F, d), draw(0.02, n, d, F)
+    offsets = ragged_offsets(counts)
+    H, y, large = run_ffn_and_see_the_kernel(lc, x, offsets, W1, W2)
+    assert large != few
+    for i in range(n):
+        rows = slice(int(offsets[i]), int(offsets[i + 1]))
+        if counts[i]:
+            h_ref = torch.nn.functional.gelu(x[rows].double() @ W1[i].double().t(), approximate="tanh")
+            assert_close(to_np(H[rows]), to_np(h_ref), TOL[dtype], "H")
+            assert_close(to_np(y[rows]), to_np(H[rows].double() @ W2[i].double().t()), TOL[dtype], "y_sliced")
 
 
 # ---------------------------------------------------------------- float32 products
