@@ -332,8 +332,8 @@ int moe_layer_forward_aux(const moe_config* cfg, const void* x, const void* Wg, 
                           int32_t* first_counts, void* workspace, size_t workspace_bytes,
                           void* const* stage_events, void* stream);
 
-/* Which stages moe_layer_forward folds into the expert GEMMs for `cfg` (bf16 / fp16 input): a
- * mask of
+/* Which stages moe_layer_forward folds into the expert GEMMs for `cfg` (bf16 / fp16 input; neither if d is
+ * no multiple of 64 and below 456, nor the combine if F is, except on the few rows of token generation): a mask of
  *   MOE_FUSE_SLICE    the first GEMM reads the token rows through the permutation (Algorithm 1's
  *                     index selection done by its loads): x_sliced is not written;
  *   MOE_FUSE_COMBINE  (output of the input's 16-bit type) the second GEMM applies the gate weight

@@ -661,9 +661,11 @@ int moe_combine(const moe_config* cfg, const void* y_sliced, const int32_t* inv_
 // the packed expert outputs are then not made at all; under top-k the others still go through
 // y_sliced and the combine kernel, which leaves the placed rows alone).
 static int layer_fuses(const moe_config& c) {
-  if (!grouped_gemm_can_fuse(c.in_dtype, c.d, c.T)) return 0;
+  const int64_t rows = max_rows_of(c);
+  if (!grouped_gemm_can_fuse(c.in_dtype, c.F, c.d, rows, c.local_count)) return 0;
+  if (static_cast<int64_t>(c.T) * c.d * 2 >= 0x7fffffffLL) return 0;   // byte offsets of the listed rows: 32 bits
   int f = MOE_FUSE_SLICE;
-  if (c.out_dtype == c.in_dtype && grouped_gemm_is_fast(c.in_dtype, c.F)) f |= MOE_FUSE_COMBINE;
+  if (c.out_dtype == c.in_dtype && grouped_gemm_can_fuse(c.in_dtype, c.d, c.F, rows, c.local_count)) f |= MOE_FUSE_COMBINE;
   return f;
 }
 

@@ -197,8 +197,8 @@ hipError_t launch_mfma_probe(int64_t iters, int random_operands, float* sink, in
 
 // C[r, :] = act(A[r, :] . B[i]^T) for offsets[i] <= r < offsets[i+1];  A [rows, K], B [n_exp, Nout, K].
 // workspace: grouped_gemm_workspace_bytes() of device scratch (partial sums of tiles cut between CUs).
-// fuse (only where grouped_gemm_can_fuse says so): 1: packed row r of A is row aux_rows[r] / aux_div
-// of the matrix given as A (first GEMM); 2 (second GEMM): packed row r of the result belongs to
+// fuse (only where grouped_gemm_can_fuse says so; for 1 the bytes of that matrix must be fewer than 2^31): 1: packed
+// row r of A is row aux_rows[r] / aux_div of the matrix given as A (first GEMM); 2 (second GEMM): packed row r of the result belongs to
 // assignment a = aux_rows[r] of token a / aux_div; if it is the only entry >= 0 of aux_inv[token, :]
 // it is stored, times aux_w[a], as row `token` of C (written by nobody else); else unweighted as
 // packed row r of C2 (aux_div == 1: always the former, aux_inv and C2 are not used).
@@ -241,12 +241,12 @@ size_t dwg_scratch_bytes(const moe_config& c);
 hipError_t launch_dwg(const moe_config& c, const void* x, const float* dlogits, float* dWg, float* dbias,
                       void* scratch, hipStream_t s);
 
+// The persistent kernel of the large tiles takes contractions of whole k-tiles of 64, others from 8 k-tiles on: below that
+// the tile-per-block kernel is faster, which has less to set up (136 tokens of 72 x 136, 4 experts, top-2: layer 41 us there, 57 here; 6000: 56 and 72;
+// one product, 3000 rows of 520 x 520: 29 and 25 us, of 4104 x 1000: 139 and 66).  Slower here all the same: one tile more than
+// the chip has CUs, which is a second tile for one of them (32000 rows of 1000 x 328 over 4 experts 54 and 66 us).
 inline bool grouped_gemm_is_fast(int in_dtype, int K) {
-  return is_16bit(in_dtype) && K < (1 << 22);   // 32-bit panel offsets in the fast kernel
-}
-// Can A be read through a row list?  Its byte offsets must fit the 32-bit offsets of the loads.
-inline bool grouped_gemm_can_fuse(int in_dtype, int K, int64_t a_rows) {
-  return grouped_gemm_is_fast(in_dtype, K) && a_rows * K * 2 < 0x7fffffffLL;
+  return is_16bit(in_dtype) && (K % 64 == 0 || K > 7 * 64) && K < (1 << 22);   // 32-bit panel offsets in that kernel
 }
 
 // The 16-bit GEMM on few rows (any K, same `fuse` contract): right for any row counts, it reads an expert's
@@ -268,13 +268,18 @@ unsigned long long* gemm_clock_words(void* workspace);
 // are launched and the counts decide on the device (launch_grouped_gemm).
 // Beyond 128 rows or 16 per expert: one expert of 4096 x 16384, 64 rows 130 -> 150 us.
 inline int grouped_gemm_few_rows_most(int in_dtype, int Nout, int K, int64_t max_rows, int n_exp) {
-  if (!grouped_gemm_is_fast(in_dtype, K) || (max_rows > 32 && (max_rows > 128 || max_rows > 16 * static_cast<int64_t>(n_exp))))
+  if (!is_16bit(in_dtype) || K >= (1 << 22) || (max_rows > 32 && (max_rows > 128 || max_rows > 16 * static_cast<int64_t>(n_exp))))
     return 0;
   const int64_t weights = static_cast<int64_t>(Nout) * K;
   const int64_t one_pass = (3ll << 31) / weights < 32 ? (3ll << 31) / weights : 32;
   const int64_t most = (1ll << 31) / weights > one_pass ? (1ll << 31) / weights : one_pass;
-  if (max_rows > most && n_exp == 1) return 0;   // (the bound is what it will be)
+  // (one expert: the bound is what it will be)
+  if (max_rows > most && (n_exp == 1 || !grouped_gemm_is_fast(in_dtype, K))) return 0;
   return static_cast<int>(most < 128 ? most : 128);
+}
+// Can the kernel that will be taken read A through a row list, and place its results?
+inline bool grouped_gemm_can_fuse(int in_dtype, int Nout, int K, int64_t max_rows, int n_exp) {
+  return grouped_gemm_is_fast(in_dtype, K) || grouped_gemm_few_rows_most(in_dtype, Nout, K, max_rows, n_exp) > 0;
 }
 // Has no expert more than `most` rows?  (The same answer in every wavefront of a launch.)
 __device__ __forceinline__ bool no_expert_above(const int32_t* __restrict__ offsets, int n_exp, int most) {

@@ -285,10 +285,20 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
                                      (full_rounds == 0 && static_cast<int64_t>(KT) * (cus - rem_x) >= 25 * cus));
   const int rounds = full_rounds + (!cut_big && lx1 > lx0 ? 1 : 0);
   const int stream_big = cut_big ? lx1 - lx0 : 0;                  // big tiles at the head of the stream
-  const int64_t units = static_cast<int64_t>(stream_big + sx1 - sx0) * KT;
+  const int stream_tiles = stream_big + sx1 - sx0;
+  const int64_t units = static_cast<int64_t>(stream_tiles) * KT;
+  // Rows of no whole k-tiles come with short contractions, where a hand-over costs more than the rest of the
+  // tile: the stream is then dealt out in whole tiles.  Up to 20 k-tiles always; up to 32 where a partial round keeps
+  // the other CUs from their shares; up to 40 where big tiles are in it.  3000 rows of 520 x 1000 over 4 experts 83 -> 26 us
+  // (few CUs had all the tiles: shares of kMinShare k-tiles), 700 of 1304 x 4000 67 -> 38, 1500 of 1608 x 328 over 2 experts 61 -> 39, 3000
+  // of 1992 x 4000 over 12 93 -> 63; beyond the lines: 136 of 1992 x 1000 over 12 cut 33, whole 46, 12000 of 1800 x 4000 over
+  // 12 cut 241, whole 255, 1500 of 3528 x 1000 over 2 cut 68, whole 80.
+  const bool whole = RAGGED && KT <= (stream_big > 0 ? 40 : full_rounds == 0 && rounds > 0 ? 32 : 20);
   // Shares shorter than kMinShare k-tiles are not worth their hand-over: fewer CUs then take part.
-  const int takers = static_cast<int>(max(static_cast<int64_t>(1), min(static_cast<int64_t>(cus), units / kMinShare)));
-  auto share_begin = [&](int c) -> int64_t { return units * min(c, takers) / takers; };
+  const int takers = static_cast<int>(max(static_cast<int64_t>(1), min(static_cast<int64_t>(cus), whole ? stream_tiles : units / kMinShare)));
+  const int deal = whole ? KT : 1;   // k-tiles dealt out together
+  const int64_t deals = whole ? stream_tiles : units;
+  auto share_begin = [&](int c) -> int64_t { return deals * min(c, takers) / takers * deal; };
   // When an XCD runs its share of the stream: before big round `stream_slot` (= rounds: after the
   // last one), the XCDs spread over the launch.  The stream's small tiles are bound by the HBM stream
   // of their weight panels and leave CUs without a share idle; the big tiles are bound by the matrix

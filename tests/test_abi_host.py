@@ -109,6 +109,20 @@ def test_invalid_arguments_are_rejected_before_any_launch(lib):
         B._check(-2, "x")
 
 
+def test_which_kernels_take_rows_through_the_permutation(lib):
+    """The lines between the GEMM kernels: the ones of the large tiles and of few rows read and place rows through the
+    permutation, the one for short contractions of no whole k-tiles does not."""
+    both, slice_only = B.MOE_FUSE_SLICE | B.MOE_FUSE_COMBINE, B.MOE_FUSE_SLICE
+    fuses = lambda T, d, F, E=4, k=1, **kw: B.moe_layer_fuses(B.make_config(T, d, F, E, k, **kw))
+    assert fuses(1000, 64, 128) == both
+    assert fuses(1000, 440, 4096) == 0 and fuses(1000, 448, 4096) == both and fuses(1000, 456, 4096) == both
+    assert fuses(1000, 4096, 440) == slice_only and fuses(1000, 4096, 456) == both
+    assert fuses(64, 440, 136) == both and fuses(65, 440, 136) == 0              # 16 rows per expert, and one more
+    assert fuses(32, 8, 8, E=1) == both and fuses(33, 8, 8, E=1) == 0
+    assert fuses(64, 440, 136, out_dtype="f32") == slice_only
+    assert fuses(1000, 448, 4096, in_dtype="f32", out_dtype="f32") == 0
+
+
 def test_missing_library_is_a_loud_error(tmp_path, monkeypatch):
     monkeypatch.setattr(B, "_lib", None)
     with pytest.raises(B.MoeError):

@@ -74,10 +74,23 @@ def test_router_gradients(kw):
     dict(T=515, d=200, F=824, E=3, top_k=2, renorm_topk=True, seed=81),                     # gathered rows and placed rows
     dict(T=700, d=136, F=1000, E=5, top_k=1, out_dtype="f32", seed=82),                     # cut tiles, packed results
     dict(T=1100, d=1000, F=4000, E=4, top_k=2, local_begin=2, local_count=2, in_dtype="f16", out_dtype="f16", seed=83),
+    dict(T=600, d=440, F=1000, E=4, top_k=1, seed=84),                      # the first product on the tile-per-block kernel
+    dict(T=600, d=456, F=440, E=4, top_k=2, renorm_topk=True, seed=85),     # the second
 ])
 def test_layer_with_rows_of_no_whole_tiles(kw):
     lc = small_cfg(**kw)
     compare_layer_full(lc, synth.make_inputs(lc))
+
+
+@pytest.mark.parametrize("dtype,d,F,counts", [
+    ("bf16", 456, 3000, [700, 300, 0, 129]),      # 8 k-tiles: the first taken; 47: cut
+    ("f16", 1288, 1000, [700]),                   # big tiles in the stream, 21 and 16 k-tiles, dealt out whole
+    ("bf16", 1240, 2568, [40, 60, 128, 7]),       # small tiles alone: 20 k-tiles whole, 41 cut
+    ("bf16", 1992, 4000, [257] * 6),              # a partial round beside 96 small tiles of 32 k-tiles
+    ("f16", 520, 136, [1500, 1000, 30]),          # more tiles than 16-k-tile shares of a short contraction
+])
+def test_expert_ffn_with_rows_of_no_whole_tiles(dtype, d, F, counts):
+    check_ffn(dtype, d, F, counts)
 
 
 # ---------------------------------------------------------------- few rows

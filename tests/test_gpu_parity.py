@@ -202,7 +202,7 @@ def ragged_offsets(counts):
 @pytest.mark.parametrize("dtype,d,F,counts", [
     ("bf16", 64, 128, [5, 0, 300]),
     ("bf16", 192, 520, [300, 0, 513, 1, 255, 256]),
-    ("bf16", 200, 264, [257, 31]),
+    ("bf16", 200, 264, [257, 31]),                # rows of no whole k-tiles, too short for the persistent kernel
     ("bf16", 512, 1024, [1024, 1000, 0, 24]),
     ("bf16", 4096, 256, [300, 3, 0, 257]),        # long K: tail tiles go through the cut k-tile stream
     ("bf16", 256, 4096, [129, 128, 600]),         # long K in the second GEMM
@@ -213,7 +213,7 @@ def ragged_offsets(counts):
     ("bf16", 2048, 2048, [2304, 2048, 2048, 2048]),
     ("f32", 64, 136, [70, 0, 64, 1]),
     ("f32", 256, 1024, [64, 64, 64, 64]),
-    ("f16", 192, 520, [300, 0, 513, 1, 255, 256]),          # general 16-bit kernel (K not a multiple of 64)
+    ("f16", 192, 520, [300, 0, 513, 1, 255, 256]),          # rows of no whole k-tiles in the second GEMM
     ("f16", 512, 1024, [1024, 1000, 0, 24]),
     ("f16", 4096, 256, [300, 3, 0, 257]),                   # tail tiles through the cut k-tile stream
 ])
