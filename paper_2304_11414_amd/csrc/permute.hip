@@ -9,7 +9,7 @@
 //      and counts, per local expert, how many of them it holds (ballot + popcount, counts kept in
 //      registers);
 //   2. the per-segment counts are turned into exclusive prefix sums per expert (by every block of step 3
-//      for its own segments; by a launch of its own when there are many);
+//      for its own segments; by a launch of its own when there are many segments or experts);
 //   3. every wavefront walks its segment again, 64 assignments at a time: rank inside the step by
 //      ballot/popcount, plus the running count carried in registers, plus the segment's prefix.
 // counts/offsets (capacity-clamped, exclusive scan over the local experts) are rebuilt by every
@@ -167,7 +167,7 @@ __device__ __forceinline__ void finish_balance_loss(const AuxOut& aux) {
   }
 }
 
-// Step 2 as a launch of its own (many segments, see launch_permute).  One block per local expert:
+// Step 2 as a launch of its own (see launch_permute).  One block per local expert:
 // seg_base = exclusive scan of seg_count over segments (may be done in place), totals[i] = queue length
 // of expert i before any capacity clamp.  A thread adds up a run of consecutive segments, the run sums
 // are scanned (butterfly inside a wavefront, the wavefront totals in order), and every thread then
@@ -240,8 +240,8 @@ __device__ __forceinline__ void scan_for_block(const int32_t* __restrict__ seg_c
   }
 }
 
-// Step 3.  first_pick: expert_idx of this lane's assignment in the segment's first 64.  totals[i]: queue length of local expert i; seg_base[i * stride]: assignments to it before this
-// segment.
+// Step 3.  first_pick: expert_idx of this lane's assignment in the segment's first 64.  totals[i]: queue length of
+// local expert i; seg_base[i * stride]: assignments to it before this segment.
 __device__ __forceinline__ void rank_segment(
     const int32_t* __restrict__ expert_idx, const int32_t* seg_base, int64_t stride, const int32_t* totals,
     int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
@@ -333,6 +333,8 @@ __global__ __launch_bounds__(kPlaceThreads) void place_kernel(
                  offsets, perm, inv_perm, seg, n_assign, seg_assign, local_begin, n_local, cap, first_pick);
 }
 
+constexpr int kFoldExperts = 2 * kPlaceWaves;   // local experts up to which the placing kernel scans
+
 hipError_t launch_permute(const moe_config& c, int64_t cap, const int32_t* expert_idx,
                           int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm,
                           int32_t* seg_scratch, hipStream_t s, int seg_assign, bool counted,
@@ -349,10 +351,12 @@ hipError_t launch_permute(const moe_config& c, int64_t cap, const int32_t* exper
   // loads to make for it (8 local experts: up to 4096 segments).  A launch costs 4-5 us whatever it does, those
   // loads 1 us at 512 segments (8192 tokens) and, growing with the segments, about as much as the launch where
   // the line is; beyond it the scan is a launch of its own.  (8192 tokens, 8 experts: scan + rank 4.9 + 6.5 us,
-  // this kernel 8.6; 16 tokens: 4.6 + 5.2, 6.4.)
+  // this kernel 8.6; 16 tokens: 4.6 + 5.2, 6.4.)  So it is past 32 local experts, whose rows a wavefront takes one
+  // after another, a memory latency each (dispatch of 1000 tokens, top-1: 32 experts 18.2 us folded, 19.0 with the
+  // launch; 64: 20.4 and 19.0; 128: 25.2 and 20.5; 256, top-8: 31.6 and 20.0).
   const int64_t loads = static_cast<int64_t>((N + kPlaceWaves - 1) / kPlaceWaves) * ((n_seg + kWave - 1) / kWave);
   int32_t *seg_base = nullptr, *totals = nullptr;
-  if (loads > 64) {
+  if (loads > 64 || N > kFoldExperts) {
     seg_base = seg_scratch + static_cast<int64_t>(N) * n_seg;
     totals = seg_base + static_cast<int64_t>(N) * n_seg;
     segment_scan_kernel<<<N, kScanThreads, 0, s>>>(seg_count, seg_base, totals, n_seg);

@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     dict(T=64 * 4096, E=8, top_k=1),                                # 4096 segments: the last the placing kernel scans
     dict(T=64 * 4096 + 1, E=8, top_k=1, capacity_factor=1.0),       # one more: the scan is a launch of its own
     dict(T=64 * 15 + 1, E=17, top_k=1),                             # 16 segments = one block; two rounds of experts
+    dict(T=64 * 16 + 1, E=33, top_k=1, local_begin=1, local_count=32),   # one more block; the most experts it scans
+    dict(T=64 * 16 + 1, E=33, top_k=2),                             # one expert more: the scan is a launch of its own
     dict(T=32769, E=130, top_k=2, local_begin=1, local_count=129),
 ])
 def test_dispatch_at_the_lines_of_the_scan(kw):
