@@ -274,7 +274,7 @@ def moe_ffn_check(cfg, workspace, layer_workspace, stream=None) -> int:
 
 
 def moe_ffn_clock(cfg, workspace, layer_workspace, stream=None):
-    """(shader clock in GHz, lifetime in microseconds) of the first block of the last fast-path GEMM
+    """(shader clock in GHz, lifetime in microseconds) of the first block with work of the last fast-path GEMM
     launch on `workspace` (synchronises); (0, 0) if there was none."""
     ghz, us = c_double(0.0), c_double(0.0)
     _check(load_library().moe_ffn_clock(byref(cfg), _ptr(workspace), int(bool(layer_workspace)),

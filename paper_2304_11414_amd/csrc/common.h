@@ -256,7 +256,7 @@ hipError_t launch_grouped_gemm_few_rows(int in_dtype, bool gelu, const bf16_t* A
                                         void* workspace, hipStream_t s, int fuse, const int32_t* aux_rows,
                                         const float* aux_w, int aux_div,
                                         const int32_t* aux_inv, bf16_t* C2);
-// Where in a GEMM workspace block 0 leaves its clocks (four words: shader and wall clock, start and end).
+// Where in a GEMM workspace a block leaves its clocks (four words: shader and wall clock, start and end).
 unsigned long long* gemm_clock_words(void* workspace);
 // The most rows one expert may have for that kernel to be taken; 0: it is not taken whatever the counts.  With at most
 // 32 rows or, up to 128, 16 per expert (the host's bound `max_rows`) it is the faster one as long as the fetches of the

@@ -872,7 +872,7 @@ unsigned long long* gemm_clock_words(void* workspace) {
   return reinterpret_cast<unsigned long long*>(flags + fast::kClockWord);
 }
 
-// Shader-clock and wall-clock ticks block 0 of the last fast-path launch on this workspace counted
+// Shader-clock and wall-clock ticks a block of the last fast-path launch on this workspace counted
 // between its start and its end.  Synchronises the stream.
 hipError_t read_gemm_clock_words(const void* workspace, uint64_t* shader_ticks, uint64_t* wall_ticks,
                                  hipStream_t s) {

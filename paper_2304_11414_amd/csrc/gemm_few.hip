@@ -46,7 +46,9 @@ __global__ __launch_bounds__(kThreads, 4) void grouped_gemm_few_rows_kernel(
   const int n_tiles = (Nout + BN - 1) / BN;
   const int expert = blockIdx.x / n_tiles, col0 = (blockIdx.x - expert * n_tiles) * BN;
   const int lo = offsets[expert], cnt = offsets[expert + 1] - lo;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {   // (read back by moe_ffn_clock)
+  // (read back by moe_ffn_clock: the first block of the first expert with rows)
+  const bool clocked = threadIdx.x == 0 && col0 == 0 && lo == offsets[0] && (cnt > 0 || expert == n_exp - 1);
+  if (clocked) {
     clock_words[0] = clock64();
     clock_words[1] = wall_clock64();
   }
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(kThreads, 4) void grouped_gemm_few_rows_kernel(
     else if (rows > 16) pass(t0, rows, std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
     else pass(t0, rows, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (clocked) {
     clock_words[2] = clock64();
     clock_words[3] = wall_clock64();
   }

@@ -171,6 +171,21 @@ def test_few_rows_decided_by_the_counts(dtype, counts, few):
             assert_close(to_np(y[rows]), to_np(H[rows].double() @ W2[i].double().t()), TOL[dtype], "y_sliced")
 
 
+@pytest.mark.parametrize("counts", [[0, 5, 0], [0, 0, 1], [20, 0, 3]])
+def test_clock_of_a_product_on_few_rows(counts):
+    """The block whose counters are read back is one with work, also where the first expert has none: it fetches 512 KiB
+    of weights, which takes more than a microsecond at any clock."""
+    import torch
+    lc = small_cfg(T=sum(counts), d=64, F=8192, E=3, top_k=1)
+    dl = DeviceLayer(lc, synth.make_inputs(lc, parts=("x", "W1_t", "W2_t")))
+    ws = torch.zeros((B.moe_ffn_workspace_bytes(dl.cfg),), dtype=torch.uint8, device="cuda")
+    H = torch.empty((sum(counts), lc.F), dtype=dl.x.dtype, device="cuda")
+    y = torch.empty_like(dl.x)
+    B.moe_expert_ffn(dl.cfg, dl.x, torch.from_numpy(ragged_offsets(counts)).cuda(), dl.W1, dl.W2, H, y, ws)
+    ghz, us = B.moe_ffn_clock(dl.cfg, ws, False)
+    assert us > 1.0 and 0.1 < ghz < 3.0, (us, ghz)
+
+
 # ---------------------------------------------------------------- float32 products
 
 @pytest.mark.parametrize("d,F,counts", [
