@@ -303,6 +303,9 @@ hipError_t read_gemm_clock_words(const void* workspace, uint64_t* shader_ticks, 
 inline size_t grouped_gemm_workspace_bytes() { return grouped_gemm_fast_workspace_bytes(); }
 // Per-device set-up of the fast GEMM (kernel attributes, placement check); synchronises `s` once.
 hipError_t grouped_gemm_fast_init(hipStream_t s);
+// The same as the first 16-bit product on a device does it, whichever kernel that product takes: nothing is done or
+// waited for under capture, or a second time.
+hipError_t grouped_gemm_set_up(hipStream_t s);
 // Diagnostic switches of the hand-over; a negative value leaves a setting as it is.
 // force_device_scope: 1 = every hand-over uses device-scope fences whatever the placement check said.
 // spin_limit: polls of a flag before the reader gives up and computes the missing k range itself

@@ -368,7 +368,8 @@ hipError_t launch_grouped_gemm(int in_dtype, bool gelu, const void* A, const voi
   }
   if (fuse != 0) return hipErrorInvalidValue;   // the other kernels work on packed tensors only
   if (is_16bit(in_dtype)) {
-    hipError_t e = ensure_lds_attr();
+    hipError_t e = grouped_gemm_set_up(s);
+    if (e == hipSuccess) e = ensure_lds_attr();
     if (e != hipSuccess) return e;
     const int64_t m_tiles = (max_rows + kBM - 1) / kBM + n_exp;   // upper bound on sum of ceilings
     const int64_t n_tiles = (Nout + kBN - 1) / kBN;

@@ -962,6 +962,35 @@ hipError_t setup_probe(FastSetup& st, hipStream_t s) {
 
 }  // namespace
 
+// The set-up as a launch on `s` finds it or, outside a capture, makes it.
+static hipError_t set_up_for_launch(hipStream_t s, int* blocks, int* same_l2) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lock(g_setup_mutex);
+  FastSetup& st = g_setup[dev];
+  e = setup_attrs(st, dev);
+  if (e != hipSuccess) return e;
+  if (!st.probed) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    e = hipStreamIsCapturing(s, &cap);
+    if (e != hipSuccess) return e;
+    if (cap == hipStreamCaptureStatusNone) {
+      e = setup_probe(st, s);
+      if (e != hipSuccess) return e;
+    }
+  }
+  *blocks = st.blocks;
+  *same_l2 = st.probed ? st.same_l2 : 0;   // unknown placement: device-scope fences are always right
+  return hipSuccess;
+}
+
+hipError_t grouped_gemm_set_up(hipStream_t s) {
+  int blocks = 0, same_l2 = 0;
+  return set_up_for_launch(s, &blocks, &same_l2);
+}
+
 hipError_t grouped_gemm_fast_init(hipStream_t s) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -984,28 +1013,9 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
                                     const int32_t* aux_rows, const float* aux_w, int aux_div,
                                     const int32_t* aux_inv, bf16_t* C2) {
   using namespace fast;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
   int blocks = 0, same_l2 = 0;
-  {
-    std::lock_guard<std::mutex> lock(g_setup_mutex);
-    FastSetup& st = g_setup[dev];
-    e = setup_attrs(st, dev);
-    if (e != hipSuccess) return e;
-    if (!st.probed) {
-      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-      e = hipStreamIsCapturing(s, &cap);
-      if (e != hipSuccess) return e;
-      if (cap == hipStreamCaptureStatusNone) {
-        e = setup_probe(st, s);
-        if (e != hipSuccess) return e;
-      }
-    }
-    blocks = st.blocks;
-    same_l2 = st.probed ? st.same_l2 : 0;   // unknown placement: device-scope fences are always right
-  }
+  hipError_t e = set_up_for_launch(s, &blocks, &same_l2);
+  if (e != hipSuccess) return e;
   if (g_force_device_scope.load()) same_l2 = 0;
   const int spin_limit = g_spin_limit.load();
   static std::atomic<uint32_t> launches{0};

@@ -167,6 +167,8 @@ hipError_t launch_grouped_gemm_few_rows(int in_dtype, bool gelu, const bf16_t* A
       (fuse == 2 && aux_w == nullptr) || aux_div < 1 ||
       (fuse == 2 && aux_div != 1 && (aux_inv == nullptr || C2 == nullptr)))
     return hipErrorInvalidValue;
+  const hipError_t e = grouped_gemm_set_up(s);
+  if (e != hipSuccess) return e;
   unsigned long long* clock_words = gemm_clock_words(workspace);
   const unsigned grid = static_cast<unsigned>(n_exp) * static_cast<unsigned>((Nout + BN - 1) / BN);
 #define PPMOE_LAUNCH(G, F)                                                                                 \

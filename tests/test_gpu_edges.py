@@ -171,6 +171,49 @@ def test_few_rows_decided_by_the_counts(dtype, counts, few):
             assert_close(to_np(y[rows]), to_np(H[rows].double() @ W2[i].double().t()), TOL[dtype], "y_sliced")
 
 
+FIRST_CALL_SETS_UP = """
+import sys, torch
+from paper_2304_11414_amd import binding as B
+T, d, F, E = int(sys.argv[1]), int(sys.argv[2]), int(sys.argv[3]), 4
+cfg = B.make_config(T, d, F, E, 1)
+x = torch.randn(T, d, device="cuda").bfloat16()
+Wg = torch.randn(E, d, device="cuda").bfloat16()
+W1 = torch.randn(E, F, d, device="cuda").bfloat16()
+W2 = torch.randn(E, d, F, device="cuda").bfloat16()
+out = torch.empty_like(x)
+ws = torch.empty(B.moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+start.record()
+torch.cuda._sleep(1000000)
+end.record()
+torch.cuda.synchronize()
+second = int(1000000 * 1000.0 / start.elapsed_time(end))      # cycles of a kernel that runs for a second
+waited = []
+for call in range(2):
+    done = torch.cuda.Event()
+    torch.cuda._sleep(second)
+    done.record()
+    B.moe_layer_forward(cfg, x, Wg, None, W1, W2, out, ws)
+    waited.append(done.query())
+    torch.cuda.synchronize()
+print("WAITED", waited, flush=True)
+"""
+
+
+@pytest.mark.parametrize("T,d,F", [(4, 64, 128), (500, 72, 136)])
+def test_first_call_of_a_process_sets_up(T, d, F):
+    """Without moe_init the first 16-bit layer call does the set-up and waits for it, also where its products take the
+    kernel for few rows or the one for short contractions (a later capture of a large batch relies on it)."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-u", "-c", FIRST_CALL_SETS_UP, str(T), str(d), str(F)], cwd=root,
+                       capture_output=True, text=True, timeout=100)
+    print(r.stdout, r.stderr, flush=True)
+    assert r.returncode == 0 and "WAITED [True, False]" in r.stdout
+
+
 @pytest.mark.parametrize("counts", [[0, 5, 0], [0, 0, 1], [20, 0, 3]])
 def test_clock_of_a_product_on_few_rows(counts):
     """The block whose counters are read back is one with work, also where the first expert has none: it fetches 512 KiB
