@@ -114,13 +114,14 @@ __global__ __launch_bounds__(kGemmThreads) void grouped_gemm_bf16_kernel(
   const bf16_t* Ab = A + static_cast<size_t>(tc.row0) * K;
   const bf16_t* Bb = B + (static_cast<size_t>(tc.expert) * Nout + tc.col0) * K;
   const int cols = min(kBN, Nout - tc.col0);
-  int a_off[4], b_off[4], l_off[4];
+  int64_t a_off[4], b_off[4];   // (255 K passes 31 bits from K = 8.4 M on)
+  int l_off[4];
   const int ch = tid & 7;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = (tid >> 3) + i * 64;
-    a_off[i] = min(row, tc.rows - 1) * K + ch * 8;   // rows past the group re-read its last row
-    b_off[i] = min(row, cols - 1) * K + ch * 8;
+    a_off[i] = static_cast<int64_t>(min(row, tc.rows - 1)) * K + ch * 8;   // rows past the group re-read its last row
+    b_off[i] = static_cast<int64_t>(min(row, cols - 1)) * K + ch * 8;
     l_off[i] = lds_piece(row, ch);
   }
   const u32x4 zero = u32x4{0u, 0u, 0u, 0u};

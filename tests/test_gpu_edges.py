@@ -95,6 +95,27 @@ def test_expert_ffn_with_rows_of_no_whole_tiles(dtype, d, F, counts):
     check_ffn(dtype, d, F, counts)
 
 
+@pytest.mark.parametrize("K", [(1 << 22) + 8, 8421600])   # the first too long for the persistent kernel; 255 K > 2^31
+@pytest.mark.parametrize("product,rows,cols", [("up", 33, 256), ("down", 256, 8)])
+def test_products_of_very_long_contractions(product, rows, cols, K):
+    """256 rows or 256 columns: the last row of a tile starts more than 2^31 elements behind the first.  Reference: float64
+    sums over pieces of the contraction (torch)."""
+    import torch
+    F, d = (cols, K) if product == "up" else (K, cols)
+    cfg = B.make_config(rows, d, F, 1, 1)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    a, w = draw(1.0, rows, K), draw(K ** -0.5, 1, cols, K)
+    got = torch.empty((rows, cols), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty((B.moe_ffn_workspace_bytes(cfg),), dtype=torch.uint8, device="cuda")
+    run = B.moe_expert_ffn_up if product == "up" else B.moe_expert_ffn_down
+    run(cfg, a, torch.tensor([0, rows], dtype=torch.int32, device="cuda"), w, got, ws)
+    ref = sum(x.double() @ y.double().t() for x, y in zip(a.split(1 << 18, dim=1), w[0].split(1 << 18, dim=1)))
+    if product == "up":
+        ref = torch.nn.functional.gelu(ref, approximate="tanh")
+    assert_close(to_np(got), to_np(ref), TOL["bf16"], product)
+
+
 # ---------------------------------------------------------------- few rows
 
 @pytest.mark.parametrize("kw", [
