@@ -71,7 +71,7 @@ __device__ __forceinline__ void load_tile(const Operand& op, int k0, int half, i
     for (int i = 0; i < R / 16; ++i) {
       const int row = (lane >> 3) + 8 * half + 16 * i;
       const bool ok = row < op.rows && k0 + ch * 8 < op.ks;
-      v[i] = ok ? *reinterpret_cast<const u32x4*>(op.base + row * op.ld + k0 + ch * 8) : zero;
+      v[i] = ok ? *reinterpret_cast<const u32x4*>(op.base + static_cast<int64_t>(row) * op.ld + k0 + ch * 8) : zero;
     }
   } else {
     const int rg = lane & 15, kg = half * 4 + (lane >> 4);
@@ -81,7 +81,7 @@ __device__ __forceinline__ void load_tile(const Operand& op, int k0, int half, i
       for (int kk = 0; kk < 8; ++kk) {
         const int k = k0 + kg * 8 + kk;
         const bool ok = k < op.ks && g * 128 + rg * 8 < op.rows;
-        v[g * 8 + kk] = ok ? *reinterpret_cast<const u32x4*>(op.base + k * op.ld + g * 128 + rg * 8) : zero;
+        v[g * 8 + kk] = ok ? *reinterpret_cast<const u32x4*>(op.base + static_cast<int64_t>(k) * op.ld + g * 128 + rg * 8) : zero;
       }
     }
   }

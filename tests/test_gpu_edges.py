@@ -276,6 +276,34 @@ def test_router_on_few_tokens(T, d, E, k, dtype):
     check_router(dict(T=T, d=d, F=64, E=E, top_k=k, renorm_topk=k > 1, in_dtype=dtype, out_dtype=dtype, seed=101))
 
 
+# ---------------------------------------------------------------- many rows on a small layer
+
+def test_weight_gradients_over_more_than_two_to_the_31_elements():
+    """One expert with so many rows that its last rows of H and dU start more than 2^31 elements behind the first, on a
+    layer so small that the 128 x 128 tiles are taken.  Reference: float64 sums over pieces of the rows (torch)."""
+    import torch
+    rows, d, F = 524288 + 520, 8, 4096
+    cfg = B.make_config(rows, d, F, 1, 1)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, dY, W1, W2 = draw(1.0, rows, d), draw(1.0, rows, d), draw(0.35, 1, F, d), draw(0.35, 1, d, F)
+    dX = torch.empty_like(x)
+    dW1, dW2 = (torch.empty(s, dtype=torch.float32, device="cuda") for s in ((1, F, d), (1, d, F)))
+    ws = torch.empty((B.moe_ffn_backward_workspace_bytes(cfg),), dtype=torch.uint8, device="cuda")
+    B.moe_expert_ffn_backward(cfg, x, torch.tensor([0, rows], dtype=torch.int32, device="cuda"), W1, W2, dY, dX, dW1, dW2, ws)
+    w1, w2 = W1[0].double(), W2[0].double()
+    ref1, ref2 = torch.zeros_like(w1), torch.zeros_like(w2)
+    for xs, dy, dx in zip(x.split(1 << 15), dY.split(1 << 15), dX.split(1 << 15)):
+        u = (xs.double() @ w1.t()).requires_grad_()
+        h = torch.nn.functional.gelu(u, approximate="tanh")
+        (du,) = torch.autograd.grad(h, u, dy.double() @ w2)
+        ref1 += du.t() @ xs.double()
+        ref2 += dy.double().t() @ h.detach()
+    assert_close(to_np(dx), to_np(du @ w1), TOL["bf16"], "dX_sliced", GRAD_ELEM_FACTOR * TOL["bf16"])   # (the last piece)
+    assert_close(to_np(dW1[0]), to_np(ref1), TOL["bf16"], "dW1", GRAD_ELEM_FACTOR * TOL["bf16"])
+    assert_close(to_np(dW2[0]), to_np(ref2), TOL["bf16"], "dW2", GRAD_ELEM_FACTOR * TOL["bf16"])
+
+
 # ---------------------------------------------------------------- data gradient of a rank with some of the experts
 
 @pytest.mark.parametrize("counts", [
