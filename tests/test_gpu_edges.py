@@ -327,3 +327,44 @@ def test_data_gradient_tiles_follow_the_rows(counts):
     ref = O.expert_ffn_backward(x, offsets, mv["W1"], mv["W2"], dY)
     dX = DeviceLayer(lc, inp).run_ffn_backward(x, offsets, dY)[0]
     assert_close(dX, ref["dX"], TOL["bf16"], "dX_sliced", GRAD_ELEM_FACTOR * TOL["bf16"])
+
+
+@pytest.mark.parametrize("counts", [
+    [2000, 0, 31, 33],       # both data gradients on the 128 x 128 launch; the tail launches leave
+    [3840, 0, 0, 0],         # dX: 15 row tiles x 8 column tiles, the last size there; dH (16 column tiles) on 256 x 256
+    [4000, 60, 0, 36],       # 256 x 256, no round saved by the tail launches
+    [8192, 20, 0, 0],        # 33 x 8 tiles, one round more than 256 CUs: the 20 rows are a tail
+    [8192, 0, 200, 0],       # the same with a remainder past 128
+    [44, 8000, 0, 300],      # remainders of 44 each side of a whole tile
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_data_gradient_tiles_with_tail_launches(dtype, counts):
+    """A long contraction on a rank with some of the experts: four launches (256 x 256, 128 x 128, tails, their sums) take
+    one decision from the row counts, each by itself.  Reference: the chain rule in float64 (torch)."""
+    import torch
+    d, F, T = 2048, 4096, 8448
+    lc = small_cfg(T=T, d=d, F=F, E=64, top_k=1, local_begin=4, local_count=4, in_dtype=dtype, out_dtype=dtype)
+    cfg = B.config_from(lc)
+    g = torch.Generator(device="cuda").manual_seed(17)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch_dtype(dtype), device="cuda").normal_(0.0, std, generator=g)
+    x, dY, W1, W2 = draw(1.0, T, d), draw(1.0, T, d), draw(0.02, 4, F, d), draw(0.02, 4, d, F)
+    offsets = ragged_offsets(counts)
+    A = int(offsets[-1])
+    x[A:], dY[A:] = float("nan"), float("nan")               # rows past the last packed row must not be read
+    dX = torch.full_like(x, 5.0)
+    dW1, dW2 = (torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in ((4, F, d), (4, d, F)))
+    ws = torch.full((B.moe_ffn_backward_workspace_bytes(cfg),), 0xFF, dtype=torch.uint8, device="cuda")
+    B.moe_expert_ffn_backward(cfg, x, torch.from_numpy(offsets).cuda(), W1, W2, dY, dX, dW1, dW2, ws)
+    assert bool((dX[A:] == 5.0).all()), "rows past the last packed row were written"
+    et = GRAD_ELEM_FACTOR * TOL[dtype]
+    for i in range(4):
+        rows = slice(int(offsets[i]), int(offsets[i + 1]))
+        xs, dy, w1, w2 = x[rows].double(), dY[rows].double(), W1[i].double(), W2[i].double()
+        u = (xs @ w1.t()).requires_grad_()
+        h = torch.nn.functional.gelu(u, approximate="tanh")
+        (du,) = torch.autograd.grad(h, u, dy @ w2)
+        # (elementwise only over many rows: see test_router_gradients)
+        many = et if counts[i] >= 256 else 1.0
+        assert_close(to_np(dX[rows]), to_np(du @ w1), TOL[dtype], "dX_sliced", et)
+        assert_close(to_np(dW1[i]), to_np(du.t() @ xs), TOL[dtype], "dW1", many)
+        assert_close(to_np(dW2[i]), to_np(dy.t() @ h.detach()), TOL[dtype], "dW2", many)
