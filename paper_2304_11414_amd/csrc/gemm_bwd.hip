@@ -122,6 +122,22 @@ struct TileInfo {
   Operand opA, opB;   // opA: the operand whose tile rows are the output rows; opB: the output columns
 };
 
+// The data gradient's tile shape where the host's bound on the rows is loose (a rank with some of the
+// experts may get any share of the assignments): pick_cus = number of CUs says that both shapes are
+// launched and the row counts decide; the 256 x 256 launch leaves when it would leave more than half of the
+// CUs without a tile, else the 128 x 128 launch does.  With a long contraction it stays also when its tiles
+// are mostly empty (experts of up to about 128 rows): it does not fetch the rows that are not there, and the weights,
+// used once, come in with more loads in flight.  FFN backward, 8 experts of 1024 x 4096 with 128 rows each, 256 x 256
+// tiles 197 us, 128 x 128 222, of 2048 x 8192 with 62 rows 548 and 612; with 256 rows 269 and 250, of 1024 x 1024 with
+// 128 rows 121 and 110.  0: no such choice.
+__device__ __forceinline__ bool few_big_tiles(const int32_t* __restrict__ offsets, int n_exp, int N, int K, int pick_cus) {
+  if (pick_cus <= 0) return false;
+  int all = 0;
+  for (int i = 0; i < n_exp; ++i) all += (offsets[i + 1] - offsets[i] + 255) / 256;
+  const int64_t rows = offsets[n_exp] - offsets[0];
+  return 2 * all * ((N + 255) / 256) < pick_cus && (K <= 2048 || 5 * rows > 3 * 256 * static_cast<int64_t>(all));
+}
+
 // Data gradient with a long contraction: an expert's rows past the last multiple of 256 cost the
 // 256 x 256 kernel a whole tile each, and with few tiles per CU a whole extra round of the chip.
 // They can go to a second launch instead (128-row tiles, 32-row blocks without a valid row skipped,
@@ -137,9 +153,10 @@ __device__ __forceinline__ int tail_rows_of(int n, int threshold) {
   const int t = n & 255;
   return t <= threshold ? t : 0;
 }
-__device__ __forceinline__ int tail_threshold(const int32_t* __restrict__ offsets, int n_exp, int N, int tail_cus,
+__device__ __forceinline__ int tail_threshold(const int32_t* __restrict__ offsets, int n_exp, int N, int K, int tail_cus,
                                               int pick_cus) {
   if (tail_cus <= 0) return 0;   // (the launcher has not provided for the two extra launches)
+  if (few_big_tiles(offsets, n_exp, N, K, pick_cus)) return 0;   // (the 128 x 128 launch has all the rows)
   const int n_tiles = (N + 255) / 256;
   int all = 0, big[2] = {0, 0}, blocks[2] = {0, 0};   // candidates 128 and 255
   for (int i = 0; i < n_exp; ++i) {
@@ -152,7 +169,6 @@ __device__ __forceinline__ int tail_threshold(const int32_t* __restrict__ offset
       blocks[c] += (t + 31) / 32;
     }
   }
-  if (2 * all < pick_cus) return 0;   // (the 128 x 128 launch has all the rows)
   const int rounds_all = (all + tail_cus - 1) / tail_cus;
   int saved[2];
 #pragma unroll
@@ -166,16 +182,6 @@ __device__ __forceinline__ int tail_threshold(const int32_t* __restrict__ offset
   }
   if (saved[0] > 0 && saved[0] >= saved[1]) return 128;
   return saved[1] > 0 ? 255 : 0;
-}
-
-// The data gradient's tile shape where the host's bound on the rows is loose (a rank with some of the
-// experts may get any share of the assignments): pick_cus = number of CUs says that both shapes are
-// launched and the row counts decide; the 256 x 256 launch leaves when it would leave more than half of the
-// CUs without a tile, else the 128 x 128 launch does.  0: no such choice.
-__device__ __forceinline__ bool few_big_tiles(const int32_t* __restrict__ offsets, int n_exp, int N, int pick_cus) {
-  int all = 0;
-  for (int i = 0; i < n_exp; ++i) all += (offsets[i + 1] - offsets[i] + 255) / 256;
-  return 2 * all * ((N + 255) / 256) < pick_cus;
 }
 
 // tail_cus (MODE 0 only): 0, or the number of CUs when the launcher runs the tail launches as well.
@@ -194,7 +200,7 @@ __device__ __forceinline__ bool locate_tile(const bf16_t* __restrict__ A, const 
   };
   if (MODE == 0) {
     // tiles ordered expert-major, then n-tile, then m-tile; blocks past the last tile leave
-    const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus, pick_cus);
+    const int tail_thr = tail_threshold(offsets, n_exp, N, K, tail_cus, pick_cus);
     int total = 0;
     for (int i = 0; i < n_exp; ++i) {
       const int n = offsets[i + 1] - offsets[i];
@@ -369,7 +375,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_kernel(
     const int32_t* __restrict__ offsets, int n_exp, int M, int N, int K, int pick_cus) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   TileInfo ti;
-  if (MODE == 0 && pick_cus > 0 && !few_big_tiles(offsets, n_exp, N, pick_cus)) return;
+  if (MODE == 0 && pick_cus > 0 && !few_big_tiles(offsets, n_exp, N, K, pick_cus)) return;
   if (!locate_tile<MODE, BM, BN>(A, B, offsets, n_exp, M, N, K, ti)) return;
   f32x16 acc[BM / 64][BN / 64];
   accumulate_tile<MODE, DT, BM, BN, false>(ti, 0, ti.kt_count, acc, lds);
@@ -387,7 +393,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_tail_kernel(
     int pick_cus) {
   constexpr int BM = kTailTile, BN = 128;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus, pick_cus);
+  const int tail_thr = tail_threshold(offsets, n_exp, N, K, tail_cus, pick_cus);
   if (tail_thr == 0) return;
   const int n_tiles = (N + BN - 1) / BN;
   int b = blockIdx.x;
@@ -438,9 +444,9 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_tail_kernel(
 // One block per (expert, tail row), a thread per 8 columns.
 template <int DT>
 __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restrict__ partial, bf16_t* __restrict__ C,
-                                                          const int32_t* __restrict__ offsets, int n_exp, int N,
+                                                          const int32_t* __restrict__ offsets, int n_exp, int N, int K,
                                                           int splits, int tail_cus, int pick_cus) {
-  const int tail_thr = tail_threshold(offsets, n_exp, N, tail_cus, pick_cus);
+  const int tail_thr = tail_threshold(offsets, n_exp, N, K, tail_cus, pick_cus);
   if (tail_thr == 0) return;
   const int expert = blockIdx.x >> 8, r = blockIdx.x & 255;
   const int lo = offsets[expert], hi = offsets[expert + 1];
@@ -501,7 +507,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_pipelined_kernel(
   typedef typename Elem16<DT>::vec8 vec8;
 
   TileInfo ti;
-  if (MODE == 0 && few_big_tiles(offsets, n_exp, N, pick_cus)) return;
+  if (MODE == 0 && few_big_tiles(offsets, n_exp, N, K, pick_cus)) return;
   if (!locate_tile<MODE, BM, BN>(A, B, offsets, n_exp, M, N, K, ti, MODE == 0 ? tail_cus : 0, pick_cus)) return;
   const int kt_count = ti.kt_count;
 
@@ -993,12 +999,12 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
       grouped_gemm_bwd_tail_kernel<MOE_F16><<<tail_grid, kThreads, lds_bytes(kTailTile, 128), s>>>(
           dU, w1, tail_partial, offsets, N, c.d, c.F, splits, tail_cus, dx_pick);
       tail_reduce_kernel<MOE_F16><<<N * 256, 256, 0, s>>>(tail_partial, static_cast<bf16_t*>(dX), offsets, N,
-                                                                c.d, splits, tail_cus, dx_pick);
+                                                                c.d, c.F, splits, tail_cus, dx_pick);
     } else {
       grouped_gemm_bwd_tail_kernel<MOE_BF16><<<tail_grid, kThreads, lds_bytes(kTailTile, 128), s>>>(
           dU, w1, tail_partial, offsets, N, c.d, c.F, splits, tail_cus, dx_pick);
       tail_reduce_kernel<MOE_BF16><<<N * 256, 256, 0, s>>>(tail_partial, static_cast<bf16_t*>(dX), offsets, N,
-                                                                 c.d, splits, tail_cus, dx_pick);
+                                                                 c.d, c.F, splits, tail_cus, dx_pick);
     }
   }
   // dB^T[i] = dY_i^T H_i  ([d, F]);  dA^T[i] = dU_i^T X_i  ([F, d])

@@ -331,6 +331,7 @@ def test_data_gradient_tiles_follow_the_rows(counts):
 
 @pytest.mark.parametrize("counts", [
     [2000, 0, 31, 33],       # both data gradients on the 128 x 128 launch; the tail launches leave
+    [60, 100, 128, 9],       # dX: mostly empty tiles, 256 x 256 all the same; dH (K = 2048): 128 x 128
     [3840, 0, 0, 0],         # dX: 15 row tiles x 8 column tiles, the last size there; dH (16 column tiles) on 256 x 256
     [4000, 60, 0, 36],       # 256 x 256, no round saved by the tail launches
     [8192, 20, 0, 0],        # 33 x 8 tiles, one round more than 256 CUs: the 20 rows are a tail
@@ -363,8 +364,7 @@ def test_data_gradient_tiles_with_tail_launches(dtype, counts):
         u = (xs @ w1.t()).requires_grad_()
         h = torch.nn.functional.gelu(u, approximate="tanh")
         (du,) = torch.autograd.grad(h, u, dy @ w2)
-        # (elementwise only over many rows: see test_router_gradients)
-        many = et if counts[i] >= 256 else 1.0
+        many = et if counts[i] >= 256 else 1.0   # (elementwise only over many rows: see test_router_gradients)
         assert_close(to_np(dX[rows]), to_np(du @ w1), TOL[dtype], "dX_sliced", et)
         assert_close(to_np(dW1[i]), to_np(du.t() @ xs), TOL[dtype], "dW1", many)
         assert_close(to_np(dW2[i]), to_np(dy.t() @ h.detach()), TOL[dtype], "dW2", many)
