@@ -129,13 +129,14 @@ struct TileInfo {
 // are mostly empty (experts of up to about 128 rows): it does not fetch the rows that are not there, and the weights,
 // used once, come in with more loads in flight.  FFN backward, 8 experts of 1024 x 4096 with 128 rows each, 256 x 256
 // tiles 197 us, 128 x 128 222, of 2048 x 8192 with 62 rows 548 and 612; with 256 rows 269 and 250, of 1024 x 1024 with
-// 128 rows 121 and 110.  0: no such choice.
+// 128 rows 121 and 110.  (The line is at 0.55 of the tiles' rows: experts of 128 rows fill 0.5, of 256 rows 0.6 to 0.8.)
+// 0: no such choice.
 __device__ __forceinline__ bool few_big_tiles(const int32_t* __restrict__ offsets, int n_exp, int N, int K, int pick_cus) {
   if (pick_cus <= 0) return false;
   int all = 0;
   for (int i = 0; i < n_exp; ++i) all += (offsets[i + 1] - offsets[i] + 255) / 256;
   const int64_t rows = offsets[n_exp] - offsets[0];
-  return 2 * all * ((N + 255) / 256) < pick_cus && (K <= 2048 || 5 * rows > 3 * 256 * static_cast<int64_t>(all));
+  return 2 * all * ((N + 255) / 256) < pick_cus && (K <= 2048 || 20 * rows > 11 * 256 * static_cast<int64_t>(all));
 }
 
 // Data gradient with a long contraction: an expert's rows past the last multiple of 256 cost the
