@@ -324,11 +324,11 @@ __global__ __launch_bounds__(64 * W) void gate_bf16_kernel(
   } else {
     for (int w = 0; w < 4; ++w) {
       if (wave == w) {
-  #pragma unroll
+#pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-  #pragma unroll
+#pragma unroll
           for (int nt = 0; nt < NT; ++nt)
-  #pragma unroll
+#pragma unroll
             for (int i = 0; i < 4; ++i) {
               float* p = &red[(mt * 16 + g * 4 + i) * kLd + nt * 16 + r];
               *p = (w == 0) ? acc[mt][nt][i] : (*p + acc[mt][nt][i]);

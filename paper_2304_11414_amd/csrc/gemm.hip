@@ -331,7 +331,9 @@ __global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(
 
 // 64 x 64 tiles from two blocks per CU on: 34 Gflop each way, 2048 rows of 1024 x 4096 take 637 us (the kernel
 // before, plain FMA on 64 x 64 x 16 tiles in LDS: 692 us).  Below that 32 x 32 tiles: 256 rows of 256 x 1024 take 11 and
-// 14 us (before: 21 and 61 us, 128 and 32 blocks).
+// 14 us (before: 21 and 61 us, 128 and 32 blocks).  The line is that of several experts (layer, 4 experts, 2048 rows of
+// 512 x 2048, second product below it: 186 us, with 64 x 64 tiles 215); one expert alone is faster on the wide tiles from
+// half of it on (151 and 128 us; of 1024 x 512 94 and 86).
 constexpr int64_t kF32WideTiles = 512;
 
 static hipError_t ensure_lds_attr() {

@@ -84,21 +84,21 @@ __global__ __launch_bounds__(kThreads) void gate_backward_kernel(
     const bool live = t < T;   // (lanes past the end stay: the shuffles are the whole wavefront's)
     const float* lg = logits + (live ? t : T - 1) * E;
     float v[NE], m = -__builtin_inff();
-  #pragma unroll
+#pragma unroll
     for (int i = 0; i < NE; ++i) {
       const int e = sub + i * LPT;
       v[i] = e < E ? lg[e] : -__builtin_inff();
       m = fmaxf(m, v[i]);
     }
     auto group_sum = [](float x) {
-  #pragma unroll
+#pragma unroll
       for (int off = LPT / 2; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
       return x;
     };
-  #pragma unroll
+#pragma unroll
     for (int off = LPT / 2; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
     float sum = 0.f;
-  #pragma unroll
+#pragma unroll
     for (int i = 0; i < NE; ++i) {
       v[i] = sub + i * LPT < E ? expf(v[i] - m) : 0.f;
       sum += v[i];
@@ -122,16 +122,16 @@ __global__ __launch_bounds__(kThreads) void gate_backward_kernel(
     const float here = pj * dw;
     const float dot = group_sum(here);   // sum_e dp[e] p[e]
     float o[NE];
-  #pragma unroll
+#pragma unroll
     for (int i = 0; i < NE; ++i) o[i] = -(v[i] / sum) * dot;
     for (int j = 0; j < k; ++j) {   // (a token picks an expert at most once)
       const int ej = __shfl(idx, j, LPT);
       const float add = __shfl(here, j, LPT);
-  #pragma unroll
+#pragma unroll
       for (int i = 0; i < NE; ++i)
         if (ej == sub + i * LPT) o[i] += add;
     }
-  #pragma unroll
+#pragma unroll
     for (int i = 0; i < NE; ++i) {
       const int e = sub + i * LPT;
       if (live && e < E) dlogits[t * E + e] = o[i];
@@ -160,21 +160,21 @@ __global__ __launch_bounds__(kThreads) void dx_kernel(const bf16_t* __restrict__
   for (int64_t tg = static_cast<int64_t>(blockIdx.x) * (16 * MT); tg < T; tg += static_cast<int64_t>(gridDim.x) * (16 * MT)) {
     const int t0 = static_cast<int>(tg);
     f32x4 acc[MT][8];        // [q][v]: column col0 + 8 (4 v + g) + q
-  #pragma unroll
+#pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-  #pragma unroll
+#pragma unroll
       for (int q = 0; q < 8; ++q) acc[mt][q] = f32x4{0.f, 0.f, 0.f, 0.f};
       const int t = t0 + mt * 16 + j;
       for (int p = 0; t < T && p < k; ++p) {
         const int r = inv_perm[static_cast<int64_t>(t) * k + p];
         if (r < 0) continue;
-  #pragma unroll
+#pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int c = col0 + 8 * (4 * v + g);
           if (c >= d) continue;
           float f[8];
           widen8<DT>(dXs + static_cast<int64_t>(r) * d + c, f);
-  #pragma unroll
+#pragma unroll
           for (int q = 0; q < 8; ++q) acc[mt][q][v] += f[q];
         }
       }
@@ -217,12 +217,12 @@ __global__ __launch_bounds__(kThreads) void dx_kernel(const bf16_t* __restrict__
     for (int mt = 0; mt < MT; ++mt) {
       const int t = t0 + mt * 16 + j;
       if (t >= T) continue;
-  #pragma unroll
+#pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int c = col0 + 8 * (4 * v + g);
         if (c >= d) continue;
         float f[8];
-  #pragma unroll
+#pragma unroll
         for (int q = 0; q < 8; ++q) f[q] = acc[mt][q][v];
         *reinterpret_cast<u32x4*>(dx + static_cast<int64_t>(t) * d + c) = pack8<DT>(f);
       }
@@ -236,7 +236,9 @@ __global__ __launch_bounds__(kThreads) void dx_kernel(const bf16_t* __restrict__
 // through LDS in order and a second launch adds the blocks' partial sums in order.  Bound: HBM (x is read
 // once per 64 experts), beyond about 32 experts the matrix unit.  At 16384 x 1024 with 64
 // experts 32 + 7 us; with vector FMAs, eight experts at a time, x was read E / 8 times and it took 173 + 19.
-// The number of token shares: about two wavefronts per SIMD, at least 16 tokens each.
+// The number of token shares: about two wavefronts per SIMD, at least 16 tokens each, and no more than 64 (the partial sums
+// are read back once per share): up to 64 experts, columns below 1024 leave SIMDs with one wavefront or none (16384 tokens
+// of 256 columns: 128 blocks; layer backward of 8 experts of 256 x 1024 306 us with the vector FMAs, 268 now).
 constexpr int kMaxChunks = 64;
 inline int dwg_chunks(const moe_config& c) {
   const int col_blocks = (c.d + 127) / 128;

@@ -265,7 +265,9 @@ def test_expert_ffn_in_float32(d, F, counts):
 # ---------------------------------------------------------------- router on few tokens
 
 @pytest.mark.parametrize("T,d,E,k,dtype", [
-    (1, 8, 16, 1, "bf16"),                # most wavefronts without a span
+    (1, 8, 16, 1, "bf16"),                # as many experts as stay on the kernel of whole rows
+    (1, 8, 17, 1, "bf16"),                # one more: all wavefronts but one without a span
+    (1, 8, 64, 2, "f16"),
     (17, 1032, 17, 2, "f16"),             # two blocks, a span past the end of the row
     (16, 4104, 33, 8, "bf16"),            # a second round of spans
     (4096, 136, 64, 1, "bf16"),           # the last size the kernel of few tokens takes
