@@ -372,10 +372,10 @@ int moe_mfma_probe(int64_t iters, int random_operands, float* sink, double* flop
 
 /* What clock the matrix-core kernels ran at.  The fast path of the grouped GEMMs (Section 3.3.2; the kernels
  * of the large tiles and of few rows) leaves in its scratch the shader-clock and wall-clock counters its first
- * block with work read at its start and its end; this reads them back for the LAST such launch on `workspace` (the one given to moe_expert_ffn_*,
- * or, layer_workspace != 0, to moe_layer_forward) and returns the shader clock in GHz and the
- * block's lifetime in microseconds (both 0 if no fast-path launch has used the workspace).  A
- * measurement helper: under load the clock settles well below the 2.4 GHz the published peak is
+ * block with work read at its start and its end; this reads them back for the LAST such launch on `workspace`
+ * (the one given to moe_expert_ffn_*, or, layer_workspace != 0, to moe_layer_forward) and returns the shader
+ * clock in GHz and the block's lifetime in microseconds (both 0 if no fast-path launch has used the workspace).
+ * A measurement helper: under load the clock settles well below the 2.4 GHz the published peak is
  * quoted at, and a fraction of that peak has to be read with this beside it.  Synchronises `stream`. */
 int moe_ffn_clock(const moe_config* cfg, const void* workspace, int layer_workspace, double* shader_ghz,
                   double* kernel_us, void* stream);

@@ -241,10 +241,11 @@ size_t dwg_scratch_bytes(const moe_config& c);
 hipError_t launch_dwg(const moe_config& c, const void* x, const float* dlogits, float* dWg, float* dbias,
                       void* scratch, hipStream_t s);
 
-// The persistent kernel of the large tiles takes contractions of whole k-tiles of 64, others from 8 k-tiles on: below that
-// the tile-per-block kernel is faster, which has less to set up (136 tokens of 72 x 136, 4 experts, top-2: layer 41 us there, 57 here; 6000: 56 and 72;
-// one product, 3000 rows of 520 x 520: 29 and 25 us, of 4104 x 1000: 139 and 66).  Slower here all the same: one tile more than
-// the chip has CUs, which is a second tile for one of them (32000 rows of 1000 x 328 over 4 experts 54 and 66 us).
+// The persistent kernel of the large tiles takes contractions of whole k-tiles of 64, others from 8 k-tiles on: below
+// that the tile-per-block kernel is faster, which has less to set up (136 tokens of 72 x 136, 4 experts, top-2: layer
+// 41 us there, 57 here; 6000 tokens: 56 and 72; one product, 3000 rows of 520 x 520: 29 and 25 us, of 4104 x 1000: 139
+// and 66).  Slower here all the same: one tile more than the chip has CUs, which is a second tile for one of them
+// (32000 rows of 1000 x 328 over 4 experts 54 and 66 us).
 inline bool grouped_gemm_is_fast(int in_dtype, int K) {
   return is_16bit(in_dtype) && (K % 64 == 0 || K > 7 * 64) && K < (1 << 22);   // 32-bit panel offsets in that kernel
 }

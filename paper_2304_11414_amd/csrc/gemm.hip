@@ -6,8 +6,8 @@
 //
 // Both operands are K-contiguous, so every global access is a 16-byte piece of a row.
 //
-// 16-bit kernel of this file (where it is taken: below): 256x256x64 block tile, 8 wavefronts (2 along rows x 4 along columns), each owning a
-// 128x64 sub-tile as 4x2 MFMA 32x32x16 accumulators (128 VGPRs).  Tiles are staged through LDS,
+// 16-bit kernel of this file (where it is taken: below): 256x256x64 block tile, 8 wavefronts (2 along rows x 4 along
+// columns), each owning a 128x64 sub-tile as 4x2 MFMA 32x32x16 accumulators (128 VGPRs).  Tiles are staged through LDS,
 // double buffered, with an XOR swizzle of the 16-byte pieces so that both the row-wise stores and
 // the column-of-rows MFMA operand reads are conflict free.  The MFMA computes C^T (weights as the
 // A operand, tokens as the B operand) so that each lane ends up with 4 consecutive output columns
@@ -358,7 +358,7 @@ hipError_t launch_grouped_gemm(int in_dtype, bool gelu, const void* A, const voi
   if (max_rows == 0) return hipSuccess;
   const int few_most = grouped_gemm_few_rows_most(in_dtype, Nout, K, max_rows, n_exp);
   if (few_most > 0) {
-    const bool sure = max_rows <= few_most;   // else both are launched, and one of them leaves (about 5 us, and the gap before the next)
+    const bool sure = max_rows <= few_most;   // else both are launched, and one of them leaves (5 us and a gap)
     const hipError_t e = launch_grouped_gemm_few_rows(
         in_dtype, gelu, static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(B), static_cast<bf16_t*>(C), offsets,
         n_exp, Nout, K, sure ? 0 : few_most, workspace, s, fuse, aux_rows, aux_w, aux_div, aux_inv, static_cast<bf16_t*>(C2));

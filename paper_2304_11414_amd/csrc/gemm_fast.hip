@@ -295,7 +295,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
   // 12 cut 241, whole 255, 1500 of 3528 x 1000 over 2 cut 68, whole 80.
   const bool whole = RAGGED && KT <= (stream_big > 0 ? 40 : full_rounds == 0 && rounds > 0 ? 32 : 20);
   // Shares shorter than kMinShare k-tiles are not worth their hand-over: fewer CUs then take part.
-  const int takers = static_cast<int>(max(static_cast<int64_t>(1), min(static_cast<int64_t>(cus), whole ? stream_tiles : units / kMinShare)));
+  const int64_t worth = whole ? static_cast<int64_t>(stream_tiles) : units / kMinShare;
+  const int takers = static_cast<int>(max(static_cast<int64_t>(1), min(static_cast<int64_t>(cus), worth)));
   const int deal = whole ? KT : 1;   // k-tiles dealt out together
   const int64_t deals = whole ? stream_tiles : units;
   auto share_begin = [&](int c) -> int64_t { return deals * min(c, takers) / takers * deal; };
