@@ -3,25 +3,7 @@
 //
 //   C[r, n] = act( sum_k A[r, k] * B[i][n, k] ),  offsets[i] <= r < offsets[i+1]
 //
-// Block tile 256 x 256 x 64, four wavefronts (one per SIMD), each owning a 128 x 128 sub-tile as
-// 4 x 4 MFMA 32x32x16 bf16 accumulators (256 accumulator registers).
-//
-// A 256x256 tile needs 32 bytes per CU per clock from the L2 at full MFMA rate, about what the
-// fetch path of a CU sustains, so the loop is built around keeping that path evenly busy:
-//   * staging loads are buffer loads of 16 bytes per lane, 8 lanes per row: every request is a whole
-//     128-byte line;
-//   * exactly one memory instruction (LDS read, LDS write or load) is issued after each MFMA, all
-//     through the K loop, never in a burst;
-//   * a load stays in flight in registers for two tile times (two sets of staging registers) before
-//     it is written to LDS, and LDS holds two tiles (written one tile ahead of use);
-//   * one barrier per tile, placed after the third of the four k-steps, when every wavefront has
-//     already fetched the last fragments of the current tile: the fragments of the next tile are
-//     prefetched behind it, so no LDS latency is exposed at the tile boundary.
-//
-// LDS layout of a tile buffer: 256 token rows then 256 weight rows of 128 bytes (eight 16-byte
-// pieces); piece p of row r sits at slot p ^ ((r >> 1) & 7).  A ds_read_b128 serves 16 lanes per
-// cycle (16 consecutive rows, same logical piece) from 64 banks, and with this swizzle they touch 16
-// different 16-byte slots; so do the 16 lanes (2 rows x 8 pieces) of a ds_write_b128.
+// Block tile 256 x 256 x 64 with the K loop of gemm_core.h, which says what bounds it.
 //
 // Scheduling: the kernel is persistent (one block per CU; consecutive block ids go round-robin over
 // the 8 XCDs, checked once per process with the XCC_ID register).  Row tiles are "big" (up to 256
@@ -43,62 +25,38 @@
 // the reading CU computes the missing k range itself, so the output tile is always complete and the
 // error word only reports lost time.
 //
-// All LDS traffic is inline assembly with hand-counted lgkmcnt waits, so that the MFMA stream never
-// waits for more than it needs; global loads are buffer loads (the compiler counts vmcnt for them).
+// A CU goes from one tile to the next without draining: the next tile is looked up while the current one
+// starts, its first two k-tiles are requested (the ring of the K loop is free by then) before the current tile's
+// epilogue, which has LDS of its own, and the epilogue's stores drain under the next tile's first k-tiles.
 
 #include <atomic>
 #include <mutex>
-#include <type_traits>
 
-#include "common.h"
+#include "gemm_core.h"
 
 namespace ppmoe {
 
 
 namespace fast {
 
-constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int kThreads = 256;
-constexpr int kOperandBytes = BM * BK * 2;     // 32 KiB
-constexpr int kBufBytes = 2 * kOperandBytes;   // 64 KiB: one tile (tokens + weights)
-constexpr int kLdsBytes = 2 * kBufBytes;       // 128 KiB
+using namespace core;
 
-// Reads one accumulator element where it lives (an accumulator register), at this point of the
-// program: without it the compiler copies all 256 accumulators to vector registers right after the
-// K loop and spills half of them.
-__device__ __forceinline__ float read_acc(float a) {
-  float v;
-  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
-  return v;
-}
-
-template <int OFF, typename V>
-__device__ __forceinline__ void lds_read16(V& dst, uint32_t addr) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
-}
-template <int OFF>
-__device__ __forceinline__ void lds_write16(uint32_t addr, const u32x4& v) {
-  asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(addr), "v"(v), "n"(OFF) : "memory");
-}
-
-#define PPMOE_TIE8(f) \
-  "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7])
-
-struct Tile {
-  int expert, row0, rows, col0;
-};
+// LDS: the K loop's ring, then 4 KiB per wavefront for the output transpose.
+constexpr int kOutBytes = 4096;                              // 16 rows of 128 columns
+constexpr int kLdsBytes = kRing + 4 * kOutBytes;             // 144 KiB
+// A small tile's k-tiles in the ring: three stages of weight rows (32 KiB), two of token rows (up to 16 KiB).
+constexpr int kSmallWeights = 256 * BK * 2, kSmallTokens = 128 * BK * 2;
+static_assert(3 * kSmallWeights + 2 * kSmallTokens <= kRing, "a small tile's stages fit in the ring");
 
 // How a tile is computed.  0: "big", the wavefronts form a 2 x 2 grid of 128 x 128 sub-tiles.
 // 1, 2, 4: "small", at most 32, 64, 128 rows: the wavefronts stand side by side, each owning all
-// the rows and 64 of the 256 columns (KIND x 2 accumulator blocks instead of 4 x 4), so a tail of a
+// the rows and 64 of the 256 columns (2 KIND x 4 accumulator blocks instead of 8 x 8), so a tail of a
 // few rows costs its share of MFMAs and the fetch of its weight panel, not a whole tile.
-__device__ __forceinline__ int tile_kind(int rows, bool small) {
-  return !small ? 0 : rows <= 32 ? 1 : rows <= 64 ? 2 : 4;
-}
+__device__ __forceinline__ int tile_kind(int rows) { return rows <= 32 ? 1 : rows <= 64 ? 2 : 4; }
 
 // An expert's rows are cut into m-tiles of BM; its last m-tile is "small" when it has at most
 // kSmallRows rows.  The tile list has two parts: all the other ("big") tiles, ordered expert-major,
-// in blocks of row tiles x column tiles (see big_tile_at); then the small tiles, ordered
+// in blocks of row tiles x column tiles; then the small tiles, ordered
 // expert-major, then n-tile.
 constexpr int kSmallRows = 128;
 constexpr int kMinShare = 16;   // k-tiles: the smallest share of a cut stream a CU is given (8, 12, 24 and 32 measured slower)
@@ -109,76 +67,14 @@ __device__ __forceinline__ void expert_tiles(int cnt, int small_rows, int& big_m
   big_m = m_tiles - small;
 }
 
-__device__ __forceinline__ void count_tiles(const int32_t* __restrict__ offsets, int n_exp,
-                                            int n_tiles, int small_rows, int& total_big,
-                                            int& total_small) {
-  total_big = total_small = 0;
-  for (int i = 0; i < n_exp; ++i) {
-    int big_m, small;
-    expert_tiles(offsets[i + 1] - offsets[i], small_rows, big_m, small);
-    total_big += big_m * n_tiles;
-    total_small += small * n_tiles;
-  }
-}
-
-// Big tiles of one expert are listed in blocks of hm row tiles x hn column tiles (hm = up to 8,
-// hm * hn = the CUs of an XCD), row tile fastest inside a block, blocks along the columns first:
-// `cus` consecutive tiles -- what an XCD runs at the same time -- share hm token panels and hn
-// weight panels, and the blocks the eight XCDs run at the same time share their token panels.
-// (Listing an expert column by column instead gives every CU of an XCD its own token panel: with
-// 100 row tiles per expert each token panel was fetched again for every column tile.)
-__device__ __forceinline__ Tile big_tile_at(const int32_t* __restrict__ offsets, int n_exp,
-                                            int n_tiles, int small_rows, int cus, int tile) {
-  Tile t = {0, 0, 1, 0};
-  int lo = offsets[0];
-  for (int i = 0; i < n_exp; ++i) {
-    const int hi = offsets[i + 1];
-    int big_m, small;
-    expert_tiles(hi - lo, small_rows, big_m, small);
-    const int here = big_m * n_tiles;
-    if (tile < here) {
-      const int hm = min(big_m, 8), hn = max(1, cus / hm);
-      const int mb = tile / (hm * n_tiles);              // block row
-      const int t2 = tile - mb * hm * n_tiles;
-      const int hmb = min(hm, big_m - mb * hm);          // its height (the last one may be lower)
-      const int nb = t2 / (hmb * hn);                    // block inside the block row
-      const int t3 = t2 - nb * hmb * hn;
-      const int n_in = t3 / hmb, m_in = t3 - n_in * hmb;
-      const int mt = mb * hm + m_in, nt = nb * hn + n_in;
-      t.expert = i;
-      t.row0 = lo + mt * BM;
-      t.rows = min(BM, hi - t.row0);
-      t.col0 = nt * BN;
-      return t;
-    }
-    tile -= here;
-    lo = hi;
-  }
-  return t;
-}
-
-__device__ __forceinline__ Tile small_tile_at(const int32_t* __restrict__ offsets, int n_exp,
-                                              int n_tiles, int small_rows, int tile) {
-  Tile t = {0, 0, 1, 0};
-  int lo = offsets[0];
-  for (int i = 0; i < n_exp; ++i) {
-    const int hi = offsets[i + 1];
-    int big_m, small;
-    expert_tiles(hi - lo, small_rows, big_m, small);
-    if (small) {
-      if (tile < n_tiles) {
-        t.expert = i;
-        t.row0 = lo + big_m * BM;
-        t.rows = hi - t.row0;
-        t.col0 = tile * BN;
-        return t;
-      }
-      tile -= n_tiles;
-    }
-    lo = hi;
-  }
-  return t;
-}
+// A segment: k-tiles [kb, ke) of one output tile.  stream: index of the tile in the XCD's stream (cut tiles).
+struct Segment {
+  int expert, row0, rows, col0, kind;
+  int kb, ke, stream;
+  int list;        // which of the two row lists in LDS is its
+  bool resumed;    // the rest of a tile whose hand-over did not arrive
+  bool valid;
+};
 
 // Scratch for tiles cut between CUs: per block one slot of 256 x 256 float accumulators for the
 // partial sums it hands over and one flag, plus a second slot where it parks its own partial sums
@@ -216,7 +112,7 @@ __global__ __launch_bounds__(kThreads) void xcc_probe_kernel() {
 // end of a row belong to the next row: their loads get an offset no descriptor covers and read zeros,
 // which costs one vector OR per load (a variant of its own, so that the other one does not pay it).
 template <bool GELU, int FUSE, int DT, bool RAGGED>
-__global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
+__global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, int n_exp, int few_most, int Nout, int K, float* __restrict__ slots,
     uint32_t* __restrict__ flags, uint32_t epoch, int same_l2, int spin_limit,
@@ -225,6 +121,12 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   __shared__ int contrib[kMaxPersistentBlocks / 8 + 1];   // [0] = how many, then the block ids whose slots to add
   __shared__ int contrib_failed;
+  // Per expert: its first packed row, the next expert's, big row tiles and small row tiles before it.
+  __shared__ u32x4 table[kMaxExperts];
+  __shared__ int wave_sums[2][4];
+  // Per tile row (of this tile and the next): FUSE 1: aux_rows; FUSE 2: where it goes (>= 0: row of C; else ~packed row
+  // of C2) and its weight.
+  __shared__ uint32_t row_list[FUSE == 0 ? 1 : 2 * BM], row_weight[FUSE == 2 ? 2 * BM : 1];
   if (few_most > 0 && no_expert_above(offsets, n_exp, few_most)) return;   // (the kernel for few rows has done it)
   const uint32_t my_xcc = xcc_id();
   // A block's flag is down before it can be looked at: whatever the caller's workspace held, a stale
@@ -240,14 +142,74 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
-      (const __attribute__((address_space(3))) unsigned char*)lds));
+  const int fr = lane & 15, fq = lane >> 4;
+  const uint32_t lds0 = lds_address(lds);
+
+  // ---- the tile list ---------------------------------------------------------------------------
+  const int n_tiles = (Nout + BN - 1) / BN;
+  const int KT = (K + BK - 1) / BK;
+  int total_big, total_small;
+  {
+    int big_m = 0, small = 0, lo = 0, hi = 0;
+    if (tid < n_exp) {
+      lo = offsets[tid];
+      hi = offsets[tid + 1];
+      expert_tiles(hi - lo, kSmallRows, big_m, small);
+    }
+    int big_sum = big_m, small_sum = small;   // over the lanes up to this one
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int bs = __shfl_up(big_sum, d, 64), ss = __shfl_up(small_sum, d, 64);
+      if (lane >= d) {
+        big_sum += bs;
+        small_sum += ss;
+      }
+    }
+    if (lane == 63) {
+      wave_sums[0][wave] = big_sum;
+      wave_sums[1][wave] = small_sum;
+    }
+    __syncthreads();
+    total_big = total_small = 0;
+    for (int w = 0; w < 4; ++w) {
+      if (w == wave) {
+        big_sum += total_big;
+        small_sum += total_small;
+      }
+      total_big += wave_sums[0][w];
+      total_small += wave_sums[1][w];
+    }
+    if (tid < n_exp)
+      table[tid] = u32x4{static_cast<uint32_t>(lo), static_cast<uint32_t>(hi), static_cast<uint32_t>(big_sum - big_m),
+                         static_cast<uint32_t>(small_sum - small)};
+    __syncthreads();
+    total_big = __builtin_amdgcn_readfirstlane(total_big) * n_tiles;
+    total_small = __builtin_amdgcn_readfirstlane(total_small) * n_tiles;
+  }
+  // The expert that holds the nth big (COL 2) or small (COL 3) row tile: the last one whose entry is at most nth.
+  struct Expert {
+    int index, lo, hi, before;
+  };
+  auto find_expert = [&](auto col_c, int nth) -> Expert {
+    constexpr int COL = decltype(col_c)::value;
+    Expert e = {0, 0, 0, 0};
+    for (int i0 = 0; i0 < n_exp; i0 += 64) {
+      const u32x4 v = lds_read_quad(lds_address(table) + 16 * min(i0 + lane, n_exp - 1));
+      const int n = __popcll(__ballot(i0 + lane < n_exp && static_cast<int>(v[COL]) <= nth));
+      if (n == 0) break;
+      e.index = i0 + n - 1;
+      e.lo = __builtin_amdgcn_readlane(v[0], n - 1);
+      e.hi = __builtin_amdgcn_readlane(v[1], n - 1);
+      e.before = __builtin_amdgcn_readlane(v[COL], n - 1);
+    }
+    return e;
+  };
 
   // ---- this block's work -----------------------------------------------------------------------
   // Consecutive block ids go round-robin over the 8 XCDs, so `cus` = gridDim/8 blocks share an L2.
   //  * Big tiles are taken whole, in rounds of the whole chip: in round j, XCD x runs the cus tiles
   //    starting at (8 j + x) cus of the tile list, one per CU.  The list is ordered so that those
-  //    cus tiles are a block of a few row tiles x a few column tiles (see big_tile_at): they run at
+  //    cus tiles are a block of a few row tiles x a few column tiles (see big_tile): they run at
   //    the same time and in step along K, which is what lets the L2 serve a panel once for several
   //    CUs.  What is left after the whole rounds (fewer than 8 cus tiles) is split evenly over the
   //    XCDs: one more, partial round per XCD -- unless an XCD's part is at most a quarter of its
@@ -256,11 +218,6 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
   //    stream of k-tiles that is cut into shares, so that a 3-row tail of an expert, or one tile more
   //    than the chip has CUs, does not cost a whole tile slot and every CU has work.  A tile cut
   //    this way is finished by the CU that holds its first k-tile.
-  const int n_tiles = (Nout + BN - 1) / BN;
-  const int KT = (K + BK - 1) / BK;
-  int total_big, total_small;
-  const int small_rows = kSmallRows;
-  count_tiles(offsets, n_exp, n_tiles, small_rows, total_big, total_small);
   const int xcd = blockIdx.x & 7, cu = blockIdx.x >> 3, cus = gridDim.x >> 3;
   // Big tiles: whole rounds of the chip first -- in round j XCD x takes the cus tiles starting at
   // (8 j + x) cus of the list, so at any time the eight XCDs work on neighbouring blocks -- then the
@@ -313,304 +270,286 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
   int64_t u = share_begin(share);
   const int64_t u_end = share_begin(share + 1);
 
-  // Staging: a tile is 512 rows (256 token, 256 weight) of 128 bytes; one load instruction covers 8
-  // rows, so a tile is 64 instructions, 16 per wavefront.  Wavefronts 0,1 fetch token rows, 2,3
-  // weight rows; instruction n of a wavefront covers rows (wave & 1) * 128 + n * 8 .. + 8.
-  const bool is_b = wave >= 2;
-  const unsigned char* gbase;
-  uint32_t goff[16];   // byte offset of this lane's piece in row n*8 + lrow (rows past the end re-read the last)
-  f32x16 acc[4][4];
-
-// The sched_barrier pins the hand-written interleaving of MFMAs and memory operations: without it
-// the compiler sinks the fragment reads below the MFMAs (to reuse their registers) and the next
-// k-step then waits for LDS.
-// KIND (a constant of the enclosing segment body) selects the accumulator blocks and fragments in
-// use: all 4 x 4 for a big tile, KIND x 2 for a small one.
-#define PPMOE_MFMA(f, mi, ni)                                                                        \
-  do {                                                                                               \
-    __builtin_amdgcn_sched_barrier(0);                                                               \
-    if (KIND == 0 || (mi < KIND && ni < 2))                                                          \
-      acc[mi][ni] = Elem16<DT>::mfma32(f[4 + ni], f[mi], acc[mi][ni]);                               \
-    __builtin_amdgcn_sched_barrier(0);                                                               \
-  } while (0)
-#define PPMOE_READ_TOK(f, i, ks, buf)                                                  \
-  do {                                                                                 \
-    if (KIND == 0 || i < KIND) lds_read16<i * 4096>(f[i], tok_a[ks] + (buf));           \
-  } while (0)
-#define PPMOE_READ_WGT(f, i, ks, buf)                                                  \
-  do {                                                                                 \
-    if (KIND == 0 || i < 2) lds_read16<i * 4096>(f[4 + i], wgt_a[ks] + (buf));          \
-  } while (0)
-// S: which of the two sets of staging registers (each holds one tile's share of this wavefront).
-#define PPMOE_WRITE(S, n, buf) lds_write16<(n) * 1024>(wr_addr[(n) & 1] + (buf), stage[(S) * 16 + (n)])
-#define PPMOE_WRITE4(S, q, buf)     \
-  do {                              \
-    PPMOE_WRITE(S, 4 * q + 0, buf); \
-    PPMOE_WRITE(S, 4 * q + 1, buf); \
-    PPMOE_WRITE(S, 4 * q + 2, buf); \
-    PPMOE_WRITE(S, 4 * q + 3, buf); \
-  } while (0)
-
-  // One k-step: 16 MFMAs on `cur`, the 8 fragment reads of the next k-step into `nxt`, and one
-  // quarter (4 instructions) of the staging traffic: write quarter Q of register set S to LDS, then
-  // reload it.
-  // RB/WB: byte offsets of the buffer read from / written to.  NKS: k-step the reads are for.
-  // One memory instruction per MFMA, and never two LDS writes in consecutive slots: four wavefronts
-  // writing 1 KiB each in the same 32 cycles exceed what the LDS takes in, and the wavefront then
-  // stalls at the next write (measured: 4 writes in 4 consecutive slots cost 56 cycles per k-step,
-  // the same 4 writes one every 4 slots cost nothing).  The last LDS instruction of a k-step is a
-  // write and every read precedes it: "at most 1 outstanding" means the reads have landed.
-#define PPMOE_STEP(cur, nxt, NKS, RB, S, Q, WB, LT, DO_READ, DO_STAGE)                                  \
-  do {                                                                                               \
-    PPMOE_MFMA(cur, 0, 0);                                                                           \
-    if (DO_READ) PPMOE_READ_TOK(nxt, 0, NKS, RB);                                                    \
-    PPMOE_MFMA(cur, 0, 1);                                                                           \
-    if (DO_READ) PPMOE_READ_WGT(nxt, 0, NKS, RB);                                                    \
-    PPMOE_MFMA(cur, 1, 0);                                                                           \
-    if (DO_STAGE) PPMOE_WRITE(S, 4 * Q + 0, WB);                                                     \
-    PPMOE_MFMA(cur, 1, 1);                                                                           \
-    if (DO_READ) PPMOE_READ_TOK(nxt, 1, NKS, RB);                                                    \
-    PPMOE_MFMA(cur, 0, 2);                                                                           \
-    if (DO_STAGE && stage_live(Q)) gload(S, 4 * Q + 0, LT);                                          \
-    PPMOE_MFMA(cur, 0, 3);                                                                           \
-    if (DO_READ) PPMOE_READ_WGT(nxt, 1, NKS, RB);                                                    \
-    PPMOE_MFMA(cur, 1, 2);                                                                           \
-    if (DO_STAGE) PPMOE_WRITE(S, 4 * Q + 1, WB);                                                     \
-    PPMOE_MFMA(cur, 1, 3);                                                                           \
-    if (DO_READ) PPMOE_READ_TOK(nxt, 2, NKS, RB);                                                    \
-    PPMOE_MFMA(cur, 2, 0);                                                                           \
-    if (DO_STAGE && stage_live(Q)) gload(S, 4 * Q + 1, LT);                                          \
-    PPMOE_MFMA(cur, 2, 1);                                                                           \
-    if (DO_READ) PPMOE_READ_WGT(nxt, 2, NKS, RB);                                                    \
-    PPMOE_MFMA(cur, 3, 0);                                                                           \
-    if (DO_STAGE) PPMOE_WRITE(S, 4 * Q + 2, WB);                                                     \
-    PPMOE_MFMA(cur, 3, 1);                                                                           \
-    if (DO_READ) PPMOE_READ_TOK(nxt, 3, NKS, RB);                                                    \
-    PPMOE_MFMA(cur, 2, 2);                                                                           \
-    if (DO_STAGE && stage_live(Q)) gload(S, 4 * Q + 2, LT);                                          \
-    PPMOE_MFMA(cur, 2, 3);                                                                           \
-    if (DO_READ) PPMOE_READ_WGT(nxt, 3, NKS, RB);                                                    \
-    PPMOE_MFMA(cur, 3, 2);                                                                           \
-    if (DO_STAGE) PPMOE_WRITE(S, 4 * Q + 3, WB);                                                     \
-    PPMOE_MFMA(cur, 3, 3);                                                                           \
-    if (DO_STAGE && stage_live(Q)) gload(S, 4 * Q + 3, LT);                                          \
-  } while (0)
-
-
-  // A hand-over that fails (see below) makes the reader put its own partial sums into its own slot
-  // and run the rest of the tile's k range as one more segment: resume_tl / resume_kb say which.
-  int resume_tl = -1, resume_kb = 0;
-  while (resume_tl >= 0 || round < rounds || u < u_end) {
-    // ---- one segment: k-tiles [kb, ke) of one output tile ---------------------------------------
-    int tl = 0, kb = 0, ke = KT, kind = 0;
-    Tile tc;
-    asm volatile("" : "+s"(resume_tl), "+s"(resume_kb));   // (uniform values: keep them in scalar registers)
-    const bool resumed = resume_tl >= 0;
-    if (resumed) {
-      tl = resume_tl;
-      kb = resume_kb;
-      resume_tl = -1;
-      tc = tl < stream_big ? big_tile_at(offsets, n_exp, n_tiles, small_rows, cus, lx0 + tl)
-                           : small_tile_at(offsets, n_exp, n_tiles, small_rows, sx0 + tl - stream_big);
-      kind = tile_kind(tc.rows, tl >= stream_big);
-    } else if (round < rounds && !(u < u_end && round >= stream_slot)) {
-      const int b = round < full_rounds ? (round * 8 + xcd) * cus + cu : lx0 + cu;
-      const bool none = round >= full_rounds && b >= lx1;   // the last round may be partial
-      ++round;
-      if (none) continue;   // (the stream, if any, still follows)
-      tc = big_tile_at(offsets, n_exp, n_tiles, small_rows, cus, b);
-    } else {
-      tl = static_cast<int>(u / KT);
-      kb = static_cast<int>(u - static_cast<int64_t>(tl) * KT);
-      ke = static_cast<int>(min(static_cast<int64_t>(KT), kb + (u_end - u)));
-      u += ke - kb;
-      tc = tl < stream_big ? big_tile_at(offsets, n_exp, n_tiles, small_rows, cus, lx0 + tl)
-                           : small_tile_at(offsets, n_exp, n_tiles, small_rows, sx0 + tl - stream_big);
-      kind = tile_kind(tc.rows, tl >= stream_big);
+  // Big tiles of one expert are listed in blocks of hm row tiles x hn column tiles (hm = up to 8,
+  // hm * hn = the CUs of an XCD), row tile fastest inside a block, blocks along the columns first:
+  // `cus` consecutive tiles -- what an XCD runs at the same time -- share hm token panels and hn
+  // weight panels, and the blocks the eight XCDs run at the same time share their token panels.
+  // (Listing an expert column by column instead gives every CU of an XCD its own token panel: with
+  // 100 row tiles per expert each token panel was fetched again for every column tile.)
+  auto big_tile = [&](int tile, Segment& s) {
+    const Expert e = find_expert(IC<2>{}, tile / n_tiles);
+    const int lo = e.lo, hi = e.hi;
+    s.expert = e.index;
+    tile -= e.before * n_tiles;
+    int big_m, small;
+    expert_tiles(hi - lo, kSmallRows, big_m, small);
+    const int hm = min(big_m, 8), hn = max(1, cus / hm);
+    const int mb = tile / (hm * n_tiles);              // block row
+    const int t2 = tile - mb * hm * n_tiles;
+    const int hmb = min(hm, big_m - mb * hm);          // its height (the last one may be lower)
+    const int nb = t2 / (hmb * hn);                    // block inside the block row
+    const int t3 = t2 - nb * hmb * hn;
+    const int n_in = t3 / hmb, m_in = t3 - n_in * hmb;
+    s.row0 = lo + (mb * hm + m_in) * BM;
+    s.rows = min(BM, hi - s.row0);
+    s.col0 = (nb * hn + n_in) * BN;
+    s.kind = 0;
+  };
+  // The small tiles: expert-major, then column tile.
+  auto small_tile = [&](int tile, Segment& s) {
+    const int nth = tile / n_tiles;
+    const Expert e = find_expert(IC<3>{}, nth);
+    const int lo = e.lo, hi = e.hi;
+    s.expert = e.index;
+    int big_m, small;
+    expert_tiles(hi - lo, kSmallRows, big_m, small);
+    s.row0 = lo + big_m * BM;
+    s.rows = hi - s.row0;
+    s.col0 = (tile - nth * n_tiles) * BN;
+    s.kind = tile_kind(s.rows);
+  };
+  auto next_segment = [&]() -> Segment {
+    Segment s = {};
+    while (round < rounds || u < u_end) {
+      if (round < rounds && !(u < u_end && round >= stream_slot)) {
+        const int b = round < full_rounds ? (round * 8 + xcd) * cus + cu : lx0 + cu;
+        const bool none = round >= full_rounds && b >= lx1;   // the last round may be partial
+        ++round;
+        if (none) continue;   // (the stream, if any, still follows)
+        big_tile(b, s);
+        s.kb = 0;
+        s.ke = KT;
+      } else {
+        s.stream = static_cast<int>(u / KT);
+        s.kb = static_cast<int>(u - static_cast<int64_t>(s.stream) * KT);
+        s.ke = static_cast<int>(min(static_cast<int64_t>(KT), s.kb + (u_end - u)));
+        u += s.ke - s.kb;
+        if (s.stream < stream_big) big_tile(lx0 + s.stream, s);
+        else small_tile(sx0 + s.stream - stream_big, s);
+      }
+      s.valid = true;
+      break;
     }
-    // Per-lane addresses.  They do not depend on the tile, but they are derived here, per segment,
-    // from an opaque copy of the lane id: computed once before the segment loop they would all stay
-    // live across it (some forty registers, which then spill).
-    int lane_s = lane;
+    return s;
+  };
+
+  // ---- loads -----------------------------------------------------------------------------------
+  // Buffer loads: a scalar descriptor of the tile's panel (base = its first row), this lane's
+  // 32-bit byte offset in a register and the k-tile offset as a scalar -- one address register
+  // per lane and no 64-bit vector add per load.  (Offsets are 32-bit: a panel of 256 rows must
+  // stay below 2 GiB, i.e. K < 4M.)  The descriptor ends with the last valid row of the panel: an offset beyond it
+  // (there is none, rows are clamped) would read zeros instead of touching memory.  k-tiles past the end of the
+  // segment are loaded through an empty descriptor: every lane is out of range and gets zeros.
+  // (a gathered panel is the whole matrix: the rows the list names are rows of A, nothing to clamp)
+  const unsigned char *ga = nullptr, *gb = nullptr;
+  int rec_a = 0, rec_b = 0, load_kb = 0, load_ke = 0;
+  uint32_t off_a[8], off_b[8];       // by chunk (big tile: half * 4 + n)
+  uint32_t past_a[2], past_b[2];     // RAGGED, by parity of the chunk: this lane's piece of the last k-tile is past the row's end
+  auto load_a = [&](int n, int kt, unsigned char* dst) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(ga), 0, kt < load_ke ? rec_a : 0, 0x00020000);
+    load_to_lds(rsrc, dst, RAGGED ? off_a[n] | (kt == KT - 1 ? past_a[n & 1] : 0u) : off_a[n], kt * (BK * 2));
+  };
+  auto load_b = [&](int n, int kt, unsigned char* dst) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(gb), 0, kt < load_ke ? rec_b : 0, 0x00020000);
+    load_to_lds(rsrc, dst, RAGGED ? off_b[n] | (kt == KT - 1 ? past_b[n & 1] : 0u) : off_b[n], kt * (BK * 2));
+  };
+  auto load_big = [&](auto j_c, auto n_c, int i) __attribute__((always_inline)) {
+    constexpr int j = decltype(j_c)::value, n = decltype(n_c)::value;
+    unsigned char* dst = lds + (i & 1) * kKTile + j * kHalfTile + (wave * 4 + n) * 1024;
+    if constexpr (j == 0 || j == 3) load_a((j == 3) * 4 + n, load_kb + i, dst);
+    else load_b((j == 2) * 4 + n, load_kb + i, dst);
+  };
+  // Small tile: a wavefront fetches the 64 weight rows it multiplies, and a quarter of the token rows.
+  auto load_small_weights = [&](int i, int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int n = 0; n < 8; ++n) load_b(n, load_kb + i, lds + stage * kSmallWeights + (wave * 8 + n) * 1024);
+  };
+  auto load_small_tokens = [&](auto kind_c, int i) __attribute__((always_inline)) {
+    constexpr int KIND = decltype(kind_c)::value;
+#pragma unroll
+    for (int n = 0; n < KIND; ++n)
+      load_a(n, load_kb + i, lds + 3 * kSmallWeights + (i & 1) * kSmallTokens + (wave * KIND + n) * 1024);
+  };
+
+  // Addresses of a segment, and the loads of its first two k-tiles.
+  auto begin = [&](const Segment& s) __attribute__((always_inline)) {
+    const int cols = min(BN, Nout - s.col0);
+    ga = reinterpret_cast<const unsigned char*>(FUSE == 1 ? A : A + static_cast<size_t>(s.row0) * K);
+    gb = reinterpret_cast<const unsigned char*>(B + (static_cast<size_t>(s.expert) * Nout + s.col0) * K);
+    const int64_t bytes_a = FUSE == 1 ? 0x7fffffff : static_cast<int64_t>(s.rows) * K * 2;
+    const int64_t bytes_b = static_cast<int64_t>(cols) * K * 2;
+    rec_a = static_cast<int>(bytes_a < 0x7fffffff ? bytes_a : 0x7fffffff);
+    rec_b = static_cast<int>(bytes_b < 0x7fffffff ? bytes_b : 0x7fffffff);
+    load_kb = s.kb;
+    load_ke = s.ke;
+    int lane_s = lane;   // (opaque: what is derived from the lane alone would otherwise stay live across the K loop)
     asm volatile("" : "+v"(lane_s));
-    const int lrow = lane_s >> 3, piece = lane_s & 7;
-    // LDS write address: row*128 + swizzled piece; rows n*8 + lrow: (row >> 1) & 7 = (n & 1) * 4 + (lrow >> 1)
-    uint32_t wr_addr[2];
+    const int lrow = lane_s >> 3, slot = lane_s & 7;
+    uint32_t row_a[8];
 #pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int sw = (par * 4 + (lrow >> 1)) & 7;
-      wr_addr[par] = lds0 + (is_b ? kOperandBytes : 0) + ((wave & 1) * 128 + lrow) * 128 + ((piece ^ sw) << 4);
-    }
-    // MFMA operands: lane holds row (lane_s & 31) of a 32-row fragment and the 8 k-values of piece
-    // 2*ks + (lane_s >> 5).
-    const int frow = lane_s & 31, half = lane_s >> 5;
-    uint32_t tok_addr[4], wgt_addr[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int slot = ((2 * ks + half) ^ ((frow >> 1) & 7)) << 4;
-      tok_addr[ks] = lds0 + (wm * 128 + frow) * 128 + slot;
-      wgt_addr[ks] = lds0 + kOperandBytes + (wn * 128 + frow) * 128 + slot;
-    }
-    const uint32_t epi = lds0 + wave * (128 * 256);   // this wavefront's 32 KiB for the output transpose
-
-    const int last = ke - 1;
-    const int cols = min(BN, Nout - tc.col0);
-    const bool gathered = FUSE == 1 && !is_b;
-    gbase = reinterpret_cast<const unsigned char*>(
-        is_b ? B + (static_cast<size_t>(tc.expert) * Nout + tc.col0) * K
-             : A + (gathered ? 0 : static_cast<size_t>(tc.row0) * K));
-    const int row_lim = (is_b ? cols : tc.rows) - 1;
-    const uint32_t past_row = RAGGED && (KT - 1) * BK + piece * 8 >= K ? 0x80000000u : 0u;   // in the last k-tile
-    if (gathered) {
-#pragma unroll
-      for (int n = 0; n < 16; ++n) {
-        const int row = (wave & 1) * 128 + n * 8 + lrow;
-        const int a = aux_rows[tc.row0 + min(row, row_lim)];
-        goff[n] = (static_cast<uint32_t>(aux_div == 1 ? a : a / aux_div) * K + piece * 8) * 2;
+    for (int n = 0; n < 8; ++n) {
+      const int big_row = (wave >> 1) * 128 + (wave & 1) * 32 + (n >> 2) * 64 + (n & 3) * 8;
+      const int ra = (s.kind == 0 ? big_row : (wave * s.kind + (n & (s.kind - 1))) * 8) + lrow;
+      const int rb = (s.kind == 0 ? big_row : (wave * 8 + n) * 8) + lrow;
+      const int piece_a = slot ^ ((ra >> 1) & 7), piece_b = slot ^ ((rb >> 1) & 7);
+      row_a[n] = min(ra, s.rows - 1);
+      off_a[n] = piece_a * 16;
+      off_b[n] = static_cast<uint32_t>(min(rb, cols - 1)) * K * 2 + piece_b * 16;
+      if (RAGGED && n < 2) {
+        past_a[n] = (KT - 1) * BK + piece_a * 8 >= K ? 0x80000000u : 0u;
+        past_b[n] = (KT - 1) * BK + piece_b * 8 >= K ? 0x80000000u : 0u;
       }
+    }
+    if (FUSE == 1) {
+      const uint32_t list = lds_address(row_list) + s.list * (BM * 4);
+      lds_read_words(row_a, list);
+#pragma unroll
+      for (int n = 0; n < 8; ++n) row_a[n] = aux_div == 1 ? row_a[n] : row_a[n] / static_cast<uint32_t>(aux_div);
+    }
+#pragma unroll
+    for (int n = 0; n < 8; ++n) off_a[n] += row_a[n] * K * 2;
+    if (s.kind == 0) {
+      each<16>([&](auto i) __attribute__((always_inline)) { load_big(IC<i.value / 4>{}, IC<i.value % 4>{}, 0); });
+      each<16>([&](auto i) __attribute__((always_inline)) { load_big(IC<i.value / 4>{}, IC<i.value % 4>{}, 1); });
     } else {
+      load_small_weights(0, 0);
+      if (s.kind == 1) load_small_tokens(IC<1>{}, 0);
+      else if (s.kind == 2) load_small_tokens(IC<2>{}, 0);
+      else load_small_tokens(IC<4>{}, 0);
+      load_small_weights(1, 1);
+    }
+  };
+  // FUSE 1: the list of a segment's rows goes to LDS while the segment before it runs.
+  auto fetch_list = [&](const Segment& s) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(aux_rows + s.row0), 0, s.rows * 4, 0x00020000);
+    unsigned char* dst = reinterpret_cast<unsigned char*>(row_list) + s.list * (BM * 4) + wave * 256;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 4,
+                                             min(tid, s.rows - 1) * 4, 0, 0, 0);
+  };
+  // FUSE 2: where the rows of a segment go, and their weights.
+  auto place_rows = [&](const Segment& s) __attribute__((always_inline)) {
+    const int r = s.row0 + min(tid, s.rows - 1);
+    const int a = aux_rows[r];
+    int dst = a;
+    float w = aux_w[a];
+    if (aux_div != 1) {
+      const int t = a / aux_div;
+      int kept = 0;
+      for (int j = 0; j < aux_div; ++j) kept += aux_inv[t * aux_div + j] >= 0;
+      dst = kept == 1 ? t : ~r;
+      if (kept != 1) w = 1.f;
+    }
+    lds_write_word(lds_address(row_list) + (s.list * BM + tid) * 4, static_cast<uint32_t>(dst));
+    lds_write_word(lds_address(row_weight) + (s.list * BM + tid) * 4, __float_as_uint(w));
+  };
+
+  uint32_t a_base[2], b_base[2];
+  fragment_base(lds0, lane, wm, a_base);
+  fragment_base(lds0, lane, wn, b_base);
+
+  // The K loop of a small tile: a wavefront multiplies all the token rows (KIND x 2 blocks of 16) by its own 64
+  // weight rows.  It is bound by the HBM stream of the weights, so two k-tiles of them are in flight and the rest is
+  // left simple: the fragments of a k-tile are read and multiplied after one barrier (for the token rows; the weight
+  // rows are the wavefront's own).
+  auto small_loop = [&](auto kind_c, f32x4 (&acc)[8][8], int tiles, bool stores_behind) __attribute__((always_inline)) {
+    constexpr int KIND = decltype(kind_c)::value;
+    typename Elem16<DT>::vec8 ft[2][2 * KIND], fw[2][4];
+    uint32_t wb[2], tb[2];
 #pragma unroll
-      for (int n = 0; n < 16; ++n) {
-        const int row = (wave & 1) * 128 + n * 8 + lrow;
-        goff[n] = (static_cast<uint32_t>(min(row, row_lim)) * K + piece * 8) * 2;
+    for (int ks = 0; ks < 2; ++ks) {
+      const uint32_t at = lds0 + fr * 128 + (((4 * ks + fq) ^ ((fr >> 1) & 7)) << 4);
+      wb[ks] = at + wave * 64 * 128;
+      tb[ks] = at + 3 * kSmallWeights;
+    }
+    int stage = 0;
+#pragma clang loop unroll(disable)
+    for (int t = 0; t < tiles; ++t) {
+      // the weights and tokens of k-tile t have landed (younger: the 8 weight loads of the next one)
+      if (stores_behind && t == 0) asm volatile("s_waitcnt vmcnt(40)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      const uint32_t ws = stage * kSmallWeights, ts = (t & 1) * kSmallTokens;
+      const uint32_t w0 = wb[0] + ws, w1 = wb[1] + ws, t0 = tb[0] + ts, t1 = tb[1] + ts;
+      each<4>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(fw[0][i.value], w0); });
+      each<2 * KIND>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(ft[0][i.value], t0); });
+      each<4>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(fw[1][i.value], w1); });
+      each<2 * KIND>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(ft[1][i.value], t1); });
+      load_small_tokens(kind_c, t + 1);
+      load_small_weights(t + 2, stage == 0 ? 2 : stage - 1);
+      stage = stage == 2 ? 0 : stage + 1;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        if (ks == 0) asm volatile("s_waitcnt lgkmcnt(%[n])" : PPMOE_TIE4(fw[0]) : [n] "n"(4 + 2 * KIND) : "memory");
+        else asm volatile("s_waitcnt lgkmcnt(0)" : PPMOE_TIE4(fw[1]) : : "memory");
+#pragma unroll
+        for (int i = 0; i < 2 * KIND; ++i) asm volatile("" : "+v"(ft[ks][i]) : : "memory");
+        each<8 * KIND>([&](auto x) __attribute__((always_inline)) {
+          constexpr int mi = x.value / 4, ni = (mi & 1) ? 3 - x.value % 4 : x.value % 4;
+          acc[mi][ni] = Elem16<DT>::mfma16(fw[ks][ni], ft[ks][mi], acc[mi][ni]);
+        });
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < 4; ++ni)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  };
 
-    // The K loop of one segment, compiled once per tile kind.
-    auto run_segment = [&](auto kind_c) __attribute__((always_inline)) {
-      constexpr int KIND = decltype(kind_c)::value;
-      // Staging registers and fragments belong to the segment: declared outside they would carry
-      // their last values across the epilogue wherever a kind leaves some of them unwritten.
-      u32x4 stage[32];
-      // Buffer loads: a scalar descriptor of the tile's panel (base = its first row), this lane's
-      // 32-bit byte offset in a register and the k-tile offset as a scalar -- one address register
-      // per lane and no 64-bit vector add per load.  (Offsets are 32-bit: a panel of 256 rows must
-      // stay below 2 GiB, i.e. K < 4M.)
-      // The descriptor ends with the last valid row of the panel: an offset beyond it (there is none,
-      // rows are clamped) would read zeros instead of touching memory.  k-tiles past the end of the
-      // segment are loaded through an empty descriptor: every lane is out of range and gets zeros, so
-      // the MFMAs of a phantom tile add nothing (the loop runs tiles in pairs).
-      // (a gathered panel is the whole matrix: the rows the list names are rows of A, nothing to clamp)
-      const int64_t panel_bytes = gathered ? 0x7fffffff : static_cast<int64_t>(row_lim + 1) * K * 2;
-      const int n_records = static_cast<int>(panel_bytes < 0x7fffffff ? panel_bytes : 0x7fffffff);
-      auto gload = [&](int set, int n, int t) {   // t: tile index along K
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<unsigned char*>(gbase), 0, t <= last ? n_records : 0, 0x00020000);
-        const uint32_t off = RAGGED ? goff[n] | (t == KT - 1 ? past_row : 0u) : goff[n];
-        stage[set * 16 + n] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, t * (BK * 2), 0);
-      };
-      typename Elem16<DT>::vec8 f0[8], f1[8];
-      // Small tile: every wavefront reads the token rows from row 0 and its own 64 weight rows.
-      // (the shifts are made opaque so that the shifted addresses are computed here, per segment, and
-      // not once per kind before the segment loop, where they would be live across everything)
-      uint32_t tok_a[4], wgt_a[4];
-      uint32_t tok_shift = KIND ? wm * (128 * 128) : 0, wgt_shift = KIND ? (wave * 64 - wn * 128) * 128 : 0;
-      asm volatile("" : "+s"(tok_shift), "+s"(wgt_shift));
+  Segment nxt = next_segment(), pending = {};
+  if (FUSE == 1 && nxt.valid) {
+    fetch_list(nxt);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+  }
+  // A segment that does not hold the first k-tile of its output tile hands its partial sums to the
+  // CU that does (through this block's scratch slot) and raises its flag: mode 1.  The one that
+  // holds it writes the output tile (mode 0), after adding the partial sums of the CUs after it, if
+  // the rest of the k range went there (their first segment, which they finished long ago).  If
+  // those do not arrive it takes nobody's: it parks its own partial sums in its own slot (mode 2,
+  // no flag) and runs the rest of the k range as one more segment, which ends by adding them back.
+  bool stores_behind = false;   // exactly 32 stores per wavefront were issued after the loads of a segment's first two k-tiles
+  bool begun = false;           // the loads of the next segment's first two k-tiles are under way
+  while (nxt.valid) {
+    // ---- a segment's products --------------------------------------------------------------------
+    const Segment cur = nxt;
+    if (!begun) begin(cur);
+    if (pending.valid) {
+      nxt = pending;
+      pending.valid = false;
+    } else {
+      nxt = next_segment();
+      nxt.list = cur.list ^ 1;
+      if (FUSE == 1 && nxt.valid) fetch_list(nxt);
+    }
+    if (FUSE == 2) place_rows(cur);
+    const int tiles = cur.ke - cur.kb;
+    f32x4 acc[8][8];
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        tok_a[ks] = tok_addr[ks] - tok_shift;
-        wgt_a[ks] = wgt_addr[ks] + wgt_shift;
-      }
-      // Token rows are staged 32 at a time by wavefront 0 (quarter q of its loads = rows 32q..32q+31):
-      // a small tile only fetches the row blocks it has (wavefront 1 stages rows 128..255: none).
-      auto stage_live = [&](int q) -> bool { return KIND == 0 || is_b || (wave == 0 && q < KIND); };
+    for (int mi = 0; mi < 8; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < 8; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (cur.kind == 0) k_loop<DT>(acc, a_base, b_base, tiles, stores_behind, load_big);
+    else if (cur.kind == 1) small_loop(IC<1>{}, acc, tiles, stores_behind);
+    else if (cur.kind == 2) small_loop(IC<2>{}, acc, tiles, stores_behind);
+    else small_loop(IC<4>{}, acc, tiles, stores_behind);
+    __builtin_amdgcn_s_barrier();   // every wavefront is done with the ring
 
-      // ---- prologue ------------------------------------------------------------------------------
-      // Two sets of staging registers: a load stays in flight for two tile times before it is written
-      // to LDS.  Set i & 1 holds tile kb + i (i = t - kb).  Here: tile kb goes through set 0 into
-      // buffer 0; sets 1 and 0 are loaded with tiles kb+1 and kb+2; quarter 0 of tile kb+1 is written
-      // to buffer 1 and replaced by quarter 0 of tile kb+3: the state every loop iteration starts in.
-      // Tiles past the end of the segment read as zeros, which keeps the loop free of branches.
-      auto gload_tile = [&](int set, int t) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (stage_live(q)) {
-#pragma unroll
-            for (int n = 4 * q; n < 4 * q + 4; ++n) gload(set, n, t);
-          }
-      };
-      gload_tile(0, kb);
-      __builtin_amdgcn_s_barrier();   // the previous segment's output transpose is out of LDS
-      PPMOE_WRITE4(0, 0, 0); PPMOE_WRITE4(0, 1, 0); PPMOE_WRITE4(0, 2, 0); PPMOE_WRITE4(0, 3, 0);
-      gload_tile(1, kb + 1);
-      gload_tile(0, kb + 2);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      PPMOE_READ_TOK(f0, 0, 0, 0); PPMOE_READ_WGT(f0, 0, 0, 0);
-      PPMOE_READ_TOK(f0, 1, 0, 0); PPMOE_READ_WGT(f0, 1, 0, 0);
-      PPMOE_READ_TOK(f0, 2, 0, 0); PPMOE_READ_WGT(f0, 2, 0, 0);
-      PPMOE_READ_TOK(f0, 3, 0, 0); PPMOE_READ_WGT(f0, 3, 0, 0);
-      // (after the reads: the loop's first wait, "at most 1 outstanding", then covers them)
-      PPMOE_WRITE4(1, 0, kBufBytes);
-      if (stage_live(0)) {
-#pragma unroll
-        for (int n = 0; n < 4; ++n) gload(1, n, kb + 3);
-      }
-
-      // ---- main loop -----------------------------------------------------------------------------
-      // At the top of tile t (i = t - kb): buffer i&1 holds tile t (visible to all), f0 <- its k-step
-      // 0 (in flight); quarter 0 of tile t+1 is already in buffer (i+1)&1; set (i+1)&1 holds quarters
-      // 1..3 of tile t+1 and quarter 0 of tile t+3; set i&1 holds tile t+2 (all in flight or landed).
-      // TILE(t, RB, WB, SA, SB): RB/WB the buffers of tiles t / t+1, SA = (i+1)&1, SB = i&1.
-#define PPMOE_TILE(t, RB, WB, SA, SB)                                                                \
-  do {                                                                                               \
-    const int lt = (t) + 3;                                                                          \
-    /* LDS operations complete in order: the reads being waited for were always followed by      */ \
-    /* exactly one write, so "at most 1 outstanding" means the reads have landed.                 */ \
-    asm volatile("s_waitcnt lgkmcnt(1)" : PPMOE_TIE8(f0)::"memory");                                 \
-    PPMOE_STEP(f0, f1, 1, RB, SA, 1, WB, lt, true, true);                                            \
-    asm volatile("s_waitcnt lgkmcnt(1)" : PPMOE_TIE8(f1)::"memory");                                 \
-    PPMOE_STEP(f1, f0, 2, RB, SA, 2, WB, lt, true, true);                                            \
-    asm volatile("s_waitcnt lgkmcnt(1)" : PPMOE_TIE8(f0)::"memory");                                 \
-    PPMOE_STEP(f0, f1, 3, RB, SA, 3, WB, lt, true, true);                                            \
-    /* Every read of tile t and every write of tile t+1 by this wavefront has completed once     */ \
-    /* lgkmcnt is 0; after the barrier that holds for the whole block.                            */ \
-    asm volatile("s_waitcnt lgkmcnt(0)" : PPMOE_TIE8(f1)::"memory");                                 \
-    __builtin_amdgcn_s_barrier();                                                                    \
-    /* k-step 3: prefetch k-step 0 of tile t+1; quarter 0 of tile t+2 goes into the buffer tile t */ \
-    /* is leaving, and is replaced in the registers by quarter 0 of tile t+4.                     */ \
-    const int lt4 = (t) + 4;                                                                         \
-    PPMOE_STEP(f1, f0, 0, WB, SB, 0, RB, lt4, true, true);                                           \
-  } while (0)
-      for (int t = kb; t < ke; t += 2) {   // (a segment of odd length ends with a phantom tile of zeros)
-        PPMOE_TILE(t, 0, kBufBytes, 1, 0);
-        PPMOE_TILE(t + 1, kBufBytes, 0, 0, 1);
-      }
-#undef PPMOE_TILE
-      asm volatile("s_waitcnt lgkmcnt(0)" : PPMOE_TIE8(f0)::"memory");
-    };
-    if (kind == 0) run_segment(std::integral_constant<int, 0>{});
-    else if (kind == 1) run_segment(std::integral_constant<int, 1>{});
-    else if (kind == 2) run_segment(std::integral_constant<int, 2>{});
-    else run_segment(std::integral_constant<int, 4>{});
-
-    // A segment that does not hold the first k-tile of its output tile hands its partial sums to the
-    // CU that does (through this block's scratch slot) and raises its flag: mode 1.  The one that
-    // holds it writes the output tile (mode 0), after adding the partial sums of the CUs after it, if
-    // the rest of the k range went there (their first segment, which they finished long ago).  If
-    // those do not arrive it takes nobody's: it parks its own partial sums in its own slot (mode 2,
-    // no flag) and runs the rest of the k range as one more segment, which ends by adding them back.
-    int mode = (kb > 0 && !resumed) ? 1 : 0;
+    int mode = (cur.kb > 0 && !cur.resumed) ? 1 : 0;
     int n_contrib = 0;
-    if (resumed) {
+    if (cur.resumed) {
       if (tid == 0) {
         contrib[0] = 1;
         contrib[1] = kMaxPersistentBlocks + blockIdx.x;   // its parking slot
       }
       __syncthreads();
       n_contrib = 1;   // (this CU's own stores, complete since the barrier that followed them)
-    } else if (mode == 0 && ke < KT) {
+    } else if (mode == 0 && cur.ke < KT) {
       if (tid == 0) {
         // One thread lists the CUs of the shares after this one that begin inside this tile (skipping empty
         // shares) and polls their flags (relaxed loads that go to L2, no cache maintenance in the loop).
         int n = 0, failed = 0;
-        for (int c2 = share + 1; c2 < cus && share_begin(c2) < static_cast<int64_t>(tl + 1) * KT; ++c2) {
+        for (int c2 = share + 1; c2 < cus && share_begin(c2) < static_cast<int64_t>(cur.stream + 1) * KT; ++c2) {
           if (share_begin(c2 + 1) == share_begin(c2)) continue;
           const int b2 = ((cus - 1 - c2) << 3) | xcd;
           contrib[++n] = b2;
@@ -645,6 +584,11 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
       __syncthreads();
       if (contrib_failed) {
         mode = 2;
+        pending = nxt;
+        nxt = cur;
+        nxt.kb = cur.ke;
+        nxt.ke = KT;
+        nxt.resumed = true;
       } else {
         // Once per thread, after the flags are up.  Within an XCD the partial sums are in the shared L2
         // (stores write through the L1, and this CU has never read these lines since its L1 was
@@ -658,176 +602,200 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
       }
     }
 
-    // Per-segment opaque copies: they stop the compiler from hoisting the address arithmetic of the
-    // code below out of the segment loop, where it would cost a few hundred live registers.
-    uint32_t epi_l = epi;
-    int tid_l = tid;
-    asm volatile("" : "+v"(epi_l), "+v"(tid_l));
-    // Where this wavefront's accumulator blocks sit in the tile (see tile_kind).
-    const int row_base = kind ? 0 : wm * 128, col_base = kind ? wave * 64 : wn * 128;
-    const int ni_lim = kind ? 2 : 4, wave_cols = kind ? 64 : 128;
+    // The ring is free: the next segment's first two k-tiles are under way during the epilogue -- unless somebody waits
+    // for its stores, or it starts with loads of its own (partial sums).
+    begun = nxt.valid && mode == 0 && n_contrib == 0;
+    if (begun) begin(nxt);
 
-    int my_slot_id = (mode == 2 ? kMaxPersistentBlocks : 0) + static_cast<int>(blockIdx.x);
-    asm volatile("" : "+s"(my_slot_id));
-    f32x4* my_slot = reinterpret_cast<f32x4*>(slots + static_cast<size_t>(my_slot_id) * kSlotFloats) + tid_l;
-
-    // ---- epilogue --------------------------------------------------------------------------------
-    // D = W_frag (32 n) x Tok_frag^T (32 m): lane holds token m = lane & 31 and, in register v,
-    // output column n = (v / 4) * 8 + (lane >> 5) * 4 + v % 4: four consecutive columns per group.
-    // The 128 x 128 sub-tile of a wavefront goes through its own 32 KiB of LDS (rows of 256 bytes,
-    // 16-byte chunk c of row r at chunk c ^ (r & 15)) so that global stores are 16 bytes per lane
-    // and 256 contiguous bytes per row instead of 8-byte pieces scattered over 32 rows.
-    // The accumulators are read in exactly one place (one 32x32 block at a time), whichever way
-    // they go: that keeps them in the accumulator registers until then.
-    __builtin_amdgcn_s_barrier();   // every wavefront is done with the tile buffers
-    // FUSE == 2: where packed row r goes.  >= 0: row of C (the token; r is its only kept pick here);
-    // < 0: ~r, packed row r of C2.
-    auto placed_row = [&](int r, int& a_out) -> int {
-      const int a = aux_rows[r];
-      a_out = a;
-      if (aux_div == 1) return a;
-      const int t = a / aux_div;
-      int kept = 0;
-      for (int j = 0; j < aux_div; ++j) kept += aux_inv[t * aux_div + j] >= 0;
-      return kept == 1 ? t : ~r;
-    };
-    float row_w[4] = {1.f, 1.f, 1.f, 1.f};   // FUSE == 2: gate weight of this lane's row of each row block
-    if (FUSE == 2 && mode == 0) {
+    // ---- epilogue of the current segment ---------------------------------------------------------
+    stores_behind = false;
+    {
+      // Per-segment opaque copies: they stop the compiler from hoisting the address arithmetic of the
+      // code below out of the segment loop, where it would cost live registers.
+      int tid_l = tid;
+      asm volatile("" : "+v"(tid_l));
+      const int lane_l = tid_l & 63, fr_l = tid_l & 15, fq_l = lane_l >> 4;
+      // Where this wavefront's accumulator blocks sit in the tile (see tile_kind).
+      const int row_base = cur.kind ? 0 : wm * 128, col_base = cur.kind ? wave * 64 : wn * 128;
+      const int ni_lim = cur.kind ? 4 : 8, wave_cols = cur.kind ? 64 : 128;
+      const int cols = min(BN, Nout - cur.col0);
+      const int ncol = min(cols - col_base, wave_cols);   // valid columns of this wavefront's part (may be <= 0)
+      const int nrow = cur.rows - row_base;               // valid rows of it (may be <= 0)
+      const bool full = cur.kind == 0 && cur.rows == BM && cols == BN;
+      int my_slot_id = (mode == 2 ? kMaxPersistentBlocks : 0) + static_cast<int>(blockIdx.x);
+      asm volatile("" : "+s"(my_slot_id));
+      f32x4* my_slot = reinterpret_cast<f32x4*>(slots + static_cast<size_t>(my_slot_id) * kSlotFloats) + tid_l;
+      // The accumulators leave 16 rows at a time (all 128, or 64, columns of the wavefront) through 4 KiB of LDS of
+      // the wavefront's own: rows of 256 bytes, 16-byte chunk c of row r at chunk c ^ r, written 8 bytes per lane,
+      // read back 16 (a store instruction covers 4 rows x 256 contiguous bytes).  LDS operations of a wavefront complete in
+      // order: nothing is waited for between the writes and the reads; the stores of a block go out after the arithmetic
+      // of the next one.
+      const uint32_t epi = lds0 + kRing + wave * kOutBytes;
+      const uint32_t wr = epi + fr_l * 256 + (fq_l & 1) * 8;
+      const int ec = lane_l & 15, er = fq_l;              // (read back: row i * 4 + er, chunk ec)
+      const uint32_t list = lds_address(row_list) + cur.list * (BM * 4), weight = lds_address(row_weight) + cur.list * (BM * 4);
+      u32x4 back[4];
+      // stores block mi (rows mi * 16 ..) of this wavefront's part from `back`
+      auto store_rows = [&](auto mi_c, auto full_c) __attribute__((always_inline)) {
+        constexpr int mi = decltype(mi_c)::value;
+        int dst[4];
+        if (FUSE == 2) {
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi) {
-        const int row = min(row_base + mi * 32 + frow, tc.rows - 1);
-        int a;
-        const int dst = placed_row(tc.row0 + row, a);
-        row_w[mi] = dst >= 0 ? aux_w[a] : 1.f;
-      }
-    }
+          for (int i = 0; i < 4; ++i)
+            asm volatile("ds_read_b32 %0, %1" : "=v"(dst[i]) : "v"(list + (row_base + mi * 16 + i * 4 + er) * 4) : "memory");
+          asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(dst[0]), "+v"(dst[1]), "+v"(dst[2]), "+v"(dst[3]) : : "memory");
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" : PPMOE_TIE4(back) : : "memory");
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi) {
+        for (int i = 0; i < 4; ++i) {
+          const int r = mi * 16 + i * 4 + er;
+          bf16_t* base = FUSE == 2 && dst[i] < 0 ? C2 : C;
+          const int row = FUSE == 2 ? (dst[i] >= 0 ? dst[i] : ~dst[i]) : cur.row0 + row_base + r;
+          bf16_t* at = base + static_cast<size_t>(row) * Nout + cur.col0 + col_base + ec * 8;
+          if (decltype(full_c)::value || (r < nrow && ec * 8 < ncol)) *reinterpret_cast<u32x4*>(at) = back[i];
+        }
+      };
+      // the final values of 16 x 16 block (mi, ni) as 16-bit elements
+      auto finish = [&](f32x4 y, float w) __attribute__((always_inline)) -> uint64_t {
+        if (GELU) y = gelu_tanh4(y);
+        if (FUSE == 2) y *= w;
+        return static_cast<uint64_t>(Elem16<DT>::pack2(y[0], y[1])) |
+               (static_cast<uint64_t>(Elem16<DT>::pack2(y[2], y[3])) << 32);
+      };
+      auto weight_of = [&](int mi) __attribute__((always_inline)) -> float {
+        return FUSE == 2 ? __int_as_float(lds_read_word(weight + (row_base + mi * 16 + fr_l) * 4)) : 1.f;
+      };
+      auto write_block = [&](int ni, uint64_t v) __attribute__((always_inline)) {
+        const uint32_t a = wr + (((ni * 2 + (fq_l >> 1)) ^ fr_l) << 4);
+        asm volatile("ds_write_b64 %0, %1" : : "v"(a), "v"(v) : "memory");
+      };
+      auto read_back = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int ni = 0; ni < 4; ++ni) {
-        f32x4 v[4];
+        for (int i = 0; i < 4; ++i) {
+          const int r = i * 4 + er;
+          asm volatile("ds_read_b128 %0, %1" : "=v"(back[i]) : "v"(epi + r * 256 + ((ec ^ r) << 4)) : "memory");
+        }
+      };
+      // v[ni] += the partial sums of block row mi, NI blocks wide, C contributors at a time
+      auto add_partials = [&](auto c_c, auto ni_c, int mi, f32x4 (&v)[8]) __attribute__((always_inline)) {
+        constexpr int CN = decltype(c_c)::value, NI = decltype(ni_c)::value;
+        for (int c0 = 0; c0 < n_contrib; c0 += CN) {
+          f32x4 p[CN][NI];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+          for (int j = 0; j < CN; ++j) {
+            const int b2 = __builtin_amdgcn_readfirstlane(contrib[1 + min(c0 + j, n_contrib - 1)]);
+            const f32x4* slot = reinterpret_cast<const f32x4*>(slots + static_cast<size_t>(b2) * kSlotFloats) + tid_l;
+            if (c0 + j < n_contrib) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[q][e] = read_acc(acc[mi][ni][q * 4 + e]);
-        // Blocks of 32 rows with no valid row are neither sent nor fetched (a 3-row tail tile moves an
-        // eighth of a slot).
-        const bool live = row_base + mi * 32 < tc.rows && ni < ni_lim;
-        if (mode != 0) {
+              for (int ni = 0; ni < NI; ++ni) p[j][ni] = slot[(mi * 8 + ni) * kThreads];
+            } else {
+#pragma unroll
+              for (int ni = 0; ni < NI; ++ni) p[j][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < CN; ++j)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) v[ni] += p[j][ni];
+        }
+      };
+      const bool plain = full && mode == 0 && n_contrib == 0;
+      if (plain) {
+        // (no branches: they cost a wavefront that is alone on its SIMD more than the work they would skip)
+        each<8>([&](auto mi_c) __attribute__((always_inline)) {
+          constexpr int mi = decltype(mi_c)::value;
+          uint64_t packed[8];
+          const float w = weight_of(mi);
+          each<8>([&](auto ni_c) __attribute__((always_inline)) {
+            constexpr int ni = decltype(ni_c)::value;
+            f32x4 v;
+            v[0] = read_acc(acc[mi][ni][0]);
+            v[1] = read_acc(acc[mi][ni][1]);
+            v[2] = read_acc(acc[mi][ni][2]);
+            v[3] = read_acc(acc[mi][ni][3]);
+            packed[ni] = finish(v, w);
+          });
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (mi > 0) store_rows(IC<(mi > 0 ? mi - 1 : 0)>{}, std::true_type{});
+          each<8>([&](auto ni_c) __attribute__((always_inline)) { write_block(ni_c.value, packed[ni_c.value]); });
+          read_back();
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        store_rows(IC<7>{}, std::true_type{});
+      } else {
+      each<8>([&](auto mi_c) __attribute__((always_inline)) {
+        constexpr int mi = decltype(mi_c)::value;
+        const bool live = mi * 16 < nrow;   // (blocks of 16 rows with no valid row are neither sent nor fetched)
+        f32x4 v[8];
+        uint64_t packed[8];
+        if (live) {
+#pragma unroll
+          for (int ni = 0; ni < 8; ++ni)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[ni][e] = read_acc(acc[mi][ni][e]);
+          if (mode == 0) {
+            // Partial sums are added in CU order (fixed summation order); the loads of several CUs' slots go out
+            // together, so that the wait is one memory latency for them all.
+            if (n_contrib > 0) {
+              if (cur.kind == 0) add_partials(IC<3>{}, IC<8>{}, mi, v);
+              else add_partials(IC<7>{}, IC<4>{}, mi, v);
+            }
+            const float w = weight_of(mi);
+#pragma unroll
+            for (int ni = 0; ni < 8; ++ni)
+              if (ni < ni_lim) packed[ni] = finish(v[ni], w);
+          } else {
+#pragma unroll
+            for (int ni = 0; ni < 8; ++ni)
+              if (ni < ni_lim) my_slot[(mi * 8 + ni) * kThreads] = v[ni];
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);   // one block at a time keeps the register footprint small
+        if (mode == 0) {
+          if constexpr (mi > 0)
+            if ((mi - 1) * 16 < nrow) store_rows(IC<(mi > 0 ? mi - 1 : 0)>{}, std::false_type{});
           if (live) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) my_slot[((mi * 4 + ni) * 4 + q) * kThreads] = v[q];
-          }
-        } else {
-          // Partial sums are added in CU order (fixed summation order); the loads of 8 CUs' slots
-          // go out together, so the wait is one memory latency per 8 CUs, not per CU.
-          for (int c0 = 0; live && c0 < n_contrib; c0 += 8) {
-            f32x4 p[8][4];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const bool has = c0 + j < n_contrib;
-              const int b2 = contrib[1 + min(c0 + j, n_contrib - 1)];
-              const f32x4* slot = reinterpret_cast<const f32x4*>(slots + static_cast<size_t>(b2) * kSlotFloats) + tid_l;
-#pragma unroll
-              for (int q = 0; q < 4; ++q)
-                p[j][q] = has ? slot[((mi * 4 + ni) * 4 + q) * kThreads] : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-#pragma unroll
-              for (int q = 0; q < 4; ++q) v[q] += p[j][q];
-          }
-          const int r = mi * 32 + frow;
-#pragma unroll
-          for (int q = 0; live && q < 4; ++q) {
-            f32x4 w = v[q];
-            if (GELU) w = gelu_tanh4(w);
-            if (FUSE == 2) w *= row_w[mi];
-            const int chunk = ni * 4 + q;   // 16-byte chunk of the 256-byte row; `half` picks its 8-byte half
-            const uint32_t a = epi_l + r * 256 + ((chunk ^ (r & 15)) << 4) + half * 8;
-            const uint32_t lo = Elem16<DT>::pack2(w[0], w[1]), hi = Elem16<DT>::pack2(w[2], w[3]);
-            asm volatile("ds_write_b64 %0, %1" : : "v"(a), "v"(static_cast<uint64_t>(lo) | (static_cast<uint64_t>(hi) << 32)) : "memory");
+            for (int ni = 0; ni < 8; ++ni)
+              if (ni < ni_lim) write_block(ni, packed[ni]);
+            read_back();
           }
         }
-        __builtin_amdgcn_sched_barrier(0);   // one 32x32 block at a time keeps the register footprint small
+        __builtin_amdgcn_sched_barrier(0);
+      });
+        if (mode == 0 && 7 * 16 < nrow) store_rows(IC<7>{}, std::false_type{});
       }
-    }
-    if (mode == 2) {
-      // Parked: the stores are in the L2 once vmcnt is 0 (this CU's L1 holds no line of its own
-      // slot: it has not read it in this launch); the block meets, then goes on with the same tile.
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      resume_tl = tl;
-      resume_kb = ke;
-      continue;
-    }
-    if (mode == 1) {
-      // Release: every thread makes its own stores visible device-wide, then the block meets, then
-      // one thread raises the flag (a relaxed store is enough after the fences).
-      // (Within an XCD: the stores have reached the shared L2 once vmcnt is 0.  The device-scope
-      // release would write back every dirty line of the L2 -- the output tiles -- once per hand-over.)
-      if (same_l2) {
+      if (mode == 0) {
+        stores_behind = plain;
+        if (n_contrib > 0 && !cur.resumed) {
+          // every thread has read the partial sums: lower the flags (the scratch may be reused by a
+          // replay of the same launch, whose flags carry the same value)
+          __syncthreads();
+          if (tid == 0)
+            for (int i = 1; i <= n_contrib; ++i)
+              __hip_atomic_store(flags + contrib[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      } else if (mode == 2) {
+        // Parked: the stores are in the L2 once vmcnt is 0 (this CU's L1 holds no line of its own
+        // slot: it has not read it in this launch); the block meets, then goes on with the same tile.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __syncthreads();
       } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      }
-      __syncthreads();
-      if (tid == 0) {
-        uint32_t up = (epoch << 4) | my_xcc;
-        asm volatile("" : "+s"(up));   // (formed here: hoisted out of the segment loop it would cost a vector register)
-        __hip_atomic_store(flags + blockIdx.x, up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      continue;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (n_contrib > 0 && !resumed) {
-      // every thread has read the partial sums: lower the flags (the scratch may be reused by a
-      // replay of the same launch, whose flags carry the same value)
-      __syncthreads();
-      if (tid == 0)
-        for (int i = 1; i <= n_contrib; ++i)
-          __hip_atomic_store(flags + contrib[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // Read back 16 bytes per lane: an instruction covers 4 rows x 256 bytes.
-    const int er = (tid_l & 63) >> 4, ec = tid_l & 15;
-    const int ncol = min(cols - col_base, wave_cols);   // valid columns of this wavefront's part (may be <= 0)
-    const int nrow = tc.rows - row_base;                // valid rows of it (may be <= 0)
-    bf16_t* cbase = C + static_cast<size_t>(tc.row0 + row_base) * Nout + tc.col0 + col_base + ec * 8;
-    for (int i0 = 0; i0 < 32 && i0 * 4 < nrow; i0 += 8) {   // 8 reads in flight, then their 8 stores
-      u32x4 v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int r = (i0 + j) * 4 + er;
-        const uint32_t a = epi_l + r * 256 + ((ec ^ (r & 15)) << 4);
-        asm volatile("ds_read_b128 %0, %1" : "=v"(v[j]) : "v"(a) : "memory");
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
-                   :
-                   : "memory");
-      if (FUSE == 2) {
-        int dst[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          int a;
-          dst[j] = placed_row(tc.row0 + row_base + min((i0 + j) * 4 + er, max(nrow, 1) - 1), a);
+        // Release: every thread makes its own stores visible device-wide, then the block meets, then
+        // one thread raises the flag (a relaxed store is enough after the fences).
+        // (Within an XCD: the stores have reached the shared L2 once vmcnt is 0.  The device-scope
+        // release would write back every dirty line of the L2 -- the output tiles -- once per hand-over.)
+        if (same_l2) {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        } else {
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int r = (i0 + j) * 4 + er;
-          if (r < nrow && ec * 8 < ncol) {
-            bf16_t* base = dst[j] >= 0 ? C : C2;
-            const int row = dst[j] >= 0 ? dst[j] : ~dst[j];
-            *reinterpret_cast<u32x4*>(base + static_cast<size_t>(row) * Nout + tc.col0 + col_base + ec * 8) = v[j];
-          }
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int r = (i0 + j) * 4 + er;
-          if (r < nrow && ec * 8 < ncol)
-            *reinterpret_cast<u32x4*>(cbase + static_cast<size_t>(r) * Nout) = v[j];
+        __syncthreads();
+        if (tid == 0) {
+          uint32_t up = (epoch << 4) | my_xcc;
+          asm volatile("" : "+s"(up));   // (formed here: hoisted out of the segment loop it would cost a vector register)
+          __hip_atomic_store(flags + blockIdx.x, up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
     }
@@ -837,12 +805,6 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_bf16_fast_kernel(
     cw[2] = clock64();
     cw[3] = wall_clock64();
   }
-#undef PPMOE_STEP
-#undef PPMOE_WRITE4
-#undef PPMOE_WRITE
-#undef PPMOE_READ_TOK
-#undef PPMOE_READ_WGT
-#undef PPMOE_MFMA
 }
 
 }  // namespace fast
@@ -921,10 +883,10 @@ hipError_t setup_attrs(FastSetup& st, int dev) {
   using namespace fast;
   if (st.attrs) return hipSuccess;
 #define PPMOE_KERNELS(DT, R)                                                               \
-  reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<true, 0, DT, R>),            \
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<false, 0, DT, R>),       \
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<true, 1, DT, R>),        \
-      reinterpret_cast<const void*>(grouped_gemm_bf16_fast_kernel<false, 2, DT, R>)
+  reinterpret_cast<const void*>(grouped_gemm_fast_kernel<true, 0, DT, R>),            \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 0, DT, R>),       \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<true, 1, DT, R>),        \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 2, DT, R>)
   const void* kernels[] = {PPMOE_KERNELS(MOE_BF16, false), PPMOE_KERNELS(MOE_BF16, true),
                            PPMOE_KERNELS(MOE_F16, false), PPMOE_KERNELS(MOE_F16, true)};
 #undef PPMOE_KERNELS
@@ -1036,7 +998,7 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
       (fuse == 2 && aux_div != 1 && (aux_inv == nullptr || C2 == nullptr)))
     return hipErrorInvalidValue;
 #define PPMOE_LAUNCH_DT(G, F, DT, R)                                                  \
-  grouped_gemm_bf16_fast_kernel<G, F, DT, R><<<blocks, kThreads, kLdsBytes, s>>>(     \
+  grouped_gemm_fast_kernel<G, F, DT, R><<<blocks, kThreads, kLdsBytes, s>>>(     \
       A, B, C, offsets, n_exp, few_most, Nout, K, slots, flags, epoch, same_l2, spin_limit, aux_rows, aux_w, aux_div, \
       aux_inv, C2)
 #define PPMOE_LAUNCH(G, F)                            \
