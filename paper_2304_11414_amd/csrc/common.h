@@ -18,6 +18,7 @@ constexpr int kGateTokens = 16;    // tokens one wavefront of the bf16 gating ke
 
 typedef uint16_t bf16_t;           // raw bf16 bits in memory
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // one 16-byte piece
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) {
@@ -312,12 +313,13 @@ hipError_t grouped_gemm_set_up(hipStream_t s);
 // spin_limit: polls of a flag before the reader gives up and computes the missing k range itself
 // (0 = never wait).
 void grouped_gemm_fast_set_handover(int force_device_scope, int spin_limit);
-// few_most > 0: leaves, nothing done, if no expert has more rows than that.
+// few_most > 0: leaves, nothing done, if no expert has more rows than that.  b_by_rows: B is [n_exp, K, Nout] (K a multiple of
+// 64, no activation, no fuse).
 hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, const bf16_t* B, bf16_t* C,
                                     const int32_t* offsets, int n_exp, int few_most, int Nout,
                                     int K, void* workspace, hipStream_t s, int fuse,
                                     const int32_t* aux_rows, const float* aux_w, int aux_div,
-                                    const int32_t* aux_inv, bf16_t* C2);
+                                    const int32_t* aux_inv, bf16_t* C2, bool b_by_rows = false);
 
 // Most segments the permutation can be asked for: kSegment assignments each when it counts them
 // itself, the tokens of one wavefront of the gating kernel each when that kernel counts them.

@@ -111,7 +111,8 @@ __global__ __launch_bounds__(kThreads) void xcc_probe_kernel() {
 // RAGGED: K is not a multiple of 64 (it is one of 8).  The pieces of the last k-tile that lie past the
 // end of a row belong to the next row: their loads get an offset no descriptor covers and read zeros,
 // which costs one vector OR per load (a variant of its own, so that the other one does not pay it).
-template <bool GELU, int FUSE, int DT, bool RAGGED>
+// B_BY_ROWS: B is [n_exp, K, Nout] (its contraction index is its row): the data gradients of the backward pass.
+template <bool GELU, int FUSE, int DT, bool RAGGED, bool B_BY_ROWS>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, int n_exp, int few_most, int Nout, int K, float* __restrict__ slots,
@@ -343,6 +344,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // (a gathered panel is the whole matrix: the rows the list names are rows of A, nothing to clamp)
   const unsigned char *ga = nullptr, *gb = nullptr;
   int rec_a = 0, rec_b = 0, load_kb = 0, load_ke = 0;
+  int64_t bytes_b = 0;
   uint32_t off_a[8], off_b[8];       // by chunk (big tile: half * 4 + n)
   uint32_t past_a[2], past_b[2];     // RAGGED, by parity of the chunk: this lane's piece of the last k-tile is past the row's end
   auto load_a = [&](int n, int kt, unsigned char* dst) __attribute__((always_inline)) {
@@ -351,6 +353,13 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
     load_to_lds(rsrc, dst, RAGGED ? off_a[n] | (kt == KT - 1 ? past_a[n & 1] : 0u) : off_a[n], kt * (BK * 2));
   };
   auto load_b = [&](int n, int kt, unsigned char* dst) __attribute__((always_inline)) {
+    if (B_BY_ROWS) {   // (the descriptor starts at the k-tile and ends with the expert's last k-row)
+      const int64_t step = static_cast<int64_t>(BK) * Nout * 2, left = bytes_b - kt * step;
+      const int rec = kt < load_ke ? static_cast<int>(left < 0x7fffffff ? left : 0x7fffffff) : 0;
+      load_to_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(gb + kt * step), 0, rec, 0x00020000), dst,
+                  off_b[n], 0);
+      return;
+    }
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(gb), 0, kt < load_ke ? rec_b : 0, 0x00020000);
     load_to_lds(rsrc, dst, RAGGED ? off_b[n] | (kt == KT - 1 ? past_b[n & 1] : 0u) : off_b[n], kt * (BK * 2));
@@ -373,13 +382,21 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       load_a(n, load_kb + i, lds + 3 * kSmallWeights + (i & 1) * kSmallTokens + (wave * KIND + n) * 1024);
   };
 
+  // A small tile's weights by rows: a wavefront's 64 columns are 64 k-rows of 128 bytes, 32-byte block b of k-row k at block
+  // b ^ (((k >> 1) & 1) + 2 ((k >> 3) & 1)): the eight k-rows that 32 lanes of a transposing read touch fall on different banks.
+  auto small_by_rows = [](int wave, int lane, int n, uint32_t row_bytes) -> uint32_t {
+    const int k = n * 8 + (lane >> 3);
+    const int piece = (lane & 7) ^ ((((k >> 1) & 1) + 2 * ((k >> 3) & 1)) << 1);
+    return k * row_bytes + (wave * 64 + piece * 8) * 2;
+  };
   // Addresses of a segment, and the loads of its first two k-tiles.
   auto begin = [&](const Segment& s) __attribute__((always_inline)) {
     const int cols = min(BN, Nout - s.col0);
     ga = reinterpret_cast<const unsigned char*>(FUSE == 1 ? A : A + static_cast<size_t>(s.row0) * K);
-    gb = reinterpret_cast<const unsigned char*>(B + (static_cast<size_t>(s.expert) * Nout + s.col0) * K);
+    gb = reinterpret_cast<const unsigned char*>(
+        B + (B_BY_ROWS ? static_cast<size_t>(s.expert) * Nout * K + s.col0 : (static_cast<size_t>(s.expert) * Nout + s.col0) * K));
     const int64_t bytes_a = FUSE == 1 ? 0x7fffffff : static_cast<int64_t>(s.rows) * K * 2;
-    const int64_t bytes_b = static_cast<int64_t>(cols) * K * 2;
+    bytes_b = B_BY_ROWS ? (static_cast<int64_t>(K) * Nout - s.col0) * 2 : static_cast<int64_t>(cols) * K * 2;
     rec_a = static_cast<int>(bytes_a < 0x7fffffff ? bytes_a : 0x7fffffff);
     rec_b = static_cast<int>(bytes_b < 0x7fffffff ? bytes_b : 0x7fffffff);
     load_kb = s.kb;
@@ -396,7 +413,9 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       const int piece_a = slot ^ ((ra >> 1) & 7), piece_b = slot ^ ((rb >> 1) & 7);
       row_a[n] = min(ra, s.rows - 1);
       off_a[n] = piece_a * 16;
-      off_b[n] = static_cast<uint32_t>(min(rb, cols - 1)) * K * 2 + piece_b * 16;
+      if (!B_BY_ROWS) off_b[n] = static_cast<uint32_t>(min(rb, cols - 1)) * K * 2 + piece_b * 16;
+      else if (s.kind == 0) off_b[n] = staged_by_rows(wave, lane_s, n >> 2, n & 3, Nout * 2u);
+      else off_b[n] = small_by_rows(wave, lane_s, n, Nout * 2u);
       if (RAGGED && n < 2) {
         past_a[n] = (KT - 1) * BK + piece_a * 8 >= K ? 0x80000000u : 0u;
         past_b[n] = (KT - 1) * BK + piece_b * 8 >= K ? 0x80000000u : 0u;
@@ -446,7 +465,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
     lds_write_word(lds_address(row_weight) + (s.list * BM + tid) * 4, __float_as_uint(w));
   };
 
-  uint32_t a_base[2], b_base[2];
+  uint32_t a_base[2], b_base[Fragments<B_BY_ROWS>::kBases];
   fragment_base(lds0, lane, wm, a_base);
   fragment_base(lds0, lane, wn, b_base);
 
@@ -454,15 +473,23 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // weight rows.  It is bound by the HBM stream of the weights, so two k-tiles of them are in flight and the rest is
   // left simple: the fragments of a k-tile are read and multiplied after one barrier (for the token rows; the weight
   // rows are the wavefront's own).
-  auto small_loop = [&](auto kind_c, f32x4 (&acc)[8][8], int tiles, bool stores_behind) __attribute__((always_inline)) {
+  auto small_loop = [&](auto kind_c, f32x4 (&acc)[8][4], int tiles, bool stores_behind) __attribute__((always_inline)) {
     constexpr int KIND = decltype(kind_c)::value;
-    typename Elem16<DT>::vec8 ft[2][2 * KIND], fw[2][4];
-    uint32_t wb[2], tb[2];
+    typedef typename Elem16<DT>::vec8 vec8;
+    u32x4 ft[2][2 * KIND], fw[2][4];
+    u32x2 fwt[2][8];                      // (B_BY_ROWS: a fragment in two halves)
+    uint32_t wb[B_BY_ROWS ? 4 : 2], tb[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       const uint32_t at = lds0 + fr * 128 + (((4 * ks + fq) ^ ((fr >> 1) & 7)) << 4);
-      wb[ks] = at + wave * 64 * 128;
+      if (!B_BY_ROWS) wb[ks] = at + wave * 64 * 128;
       tb[ks] = at + 3 * kSmallWeights;
+    }
+    if (B_BY_ROWS) {
+      const int j = (lane >> 2) & 3;
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        wb[B_BY_ROWS ? b : 0] = lds0 + wave * 8192 + (fq * 8 + j) * 128 + ((b ^ ((j >> 1) + 2 * (fq & 1))) << 5) + (lane & 3) * 8;
     }
     int stage = 0;
 #pragma clang loop unroll(disable)
@@ -472,23 +499,41 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       const uint32_t ws = stage * kSmallWeights, ts = (t & 1) * kSmallTokens;
-      const uint32_t w0 = wb[0] + ws, w1 = wb[1] + ws, t0 = tb[0] + ts, t1 = tb[1] + ts;
-      each<4>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(fw[0][i.value], w0); });
+      const uint32_t t0 = tb[0] + ts, t1 = tb[1] + ts;
+      auto read_weights = [&](auto ks_c) __attribute__((always_inline)) {
+        constexpr int KS = decltype(ks_c)::value;
+        if constexpr (B_BY_ROWS)
+          each<8>([&](auto i) __attribute__((always_inline)) {
+            lds_read_transposed<KS * 4096 + (i.value & 1) * 512>(fwt[KS][i.value], wb[(i.value >> 1) & 3] + ws);
+          });
+        else
+          each<4>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(fw[KS][i.value], wb[KS] + ws); });
+      };
+      read_weights(IC<0>{});
       each<2 * KIND>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(ft[0][i.value], t0); });
-      each<4>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(fw[1][i.value], w1); });
+      read_weights(IC<1>{});
       each<2 * KIND>([&](auto i) __attribute__((always_inline)) { lds_read16<i.value * 2048>(ft[1][i.value], t1); });
       load_small_tokens(kind_c, t + 1);
       load_small_weights(t + 2, stage == 0 ? 2 : stage - 1);
       stage = stage == 2 ? 0 : stage + 1;
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        if (ks == 0) asm volatile("s_waitcnt lgkmcnt(%[n])" : PPMOE_TIE4(fw[0]) : [n] "n"(4 + 2 * KIND) : "memory");
-        else asm volatile("s_waitcnt lgkmcnt(0)" : PPMOE_TIE4(fw[1]) : : "memory");
+        // (the reads of the second k-step may still be under way: lgkmcnt counts to 15)
+        constexpr int kYounger = (B_BY_ROWS ? 8 : 4) + 2 * KIND;
+        if (ks == 0) asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(kYounger < 15 ? kYounger : 15) : "memory");
+        else asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+        if (B_BY_ROWS) {
+          asm volatile("" : PPMOE_TIE8(fwt[ks]) : : "memory");
+#pragma unroll
+          for (int i = 0; i < 4; ++i) fw[ks][i] = __builtin_shufflevector(fwt[ks][2 * i], fwt[ks][2 * i + 1], 0, 1, 2, 3);
+        } else {
+          asm volatile("" : PPMOE_TIE4(fw[ks]) : : "memory");
+        }
 #pragma unroll
         for (int i = 0; i < 2 * KIND; ++i) asm volatile("" : "+v"(ft[ks][i]) : : "memory");
         each<8 * KIND>([&](auto x) __attribute__((always_inline)) {
           constexpr int mi = x.value / 4, ni = (mi & 1) ? 3 - x.value % 4 : x.value % 4;
-          acc[mi][ni] = Elem16<DT>::mfma16(fw[ks][ni], ft[ks][mi], acc[mi][ni]);
+          acc[mi][ni] = Elem16<DT>::mfma16(__builtin_bit_cast(vec8, fw[ks][ni]), __builtin_bit_cast(vec8, ft[ks][mi]), acc[mi][ni]);
         });
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -524,15 +569,10 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
     }
     if (FUSE == 2) place_rows(cur);
     const int tiles = cur.ke - cur.kb;
-    f32x4 acc[8][8];
-#pragma unroll
-    for (int mi = 0; mi < 8; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < 8; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (cur.kind == 0) k_loop<DT>(acc, a_base, b_base, tiles, stores_behind, load_big);
-    else if (cur.kind == 1) small_loop(IC<1>{}, acc, tiles, stores_behind);
-    else if (cur.kind == 2) small_loop(IC<2>{}, acc, tiles, stores_behind);
-    else small_loop(IC<4>{}, acc, tiles, stores_behind);
+    // What follows a segment's K loop: who writes the tile, the next segment's loads, the epilogue.  (One copy for big
+    // tiles and one for small ones: accumulators that both kinds of K loop feed cost the compiler copies inside the loops.)
+    auto finish_segment = [&](auto& acc, auto ni_c) __attribute__((always_inline)) {
+    constexpr int NI = decltype(ni_c)::value;   // 16-column blocks of a wavefront
     __builtin_amdgcn_s_barrier();   // every wavefront is done with the ring
 
     int mode = (cur.kb > 0 && !cur.resumed) ? 1 : 0;
@@ -616,12 +656,11 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       asm volatile("" : "+v"(tid_l));
       const int lane_l = tid_l & 63, fr_l = tid_l & 15, fq_l = lane_l >> 4;
       // Where this wavefront's accumulator blocks sit in the tile (see tile_kind).
-      const int row_base = cur.kind ? 0 : wm * 128, col_base = cur.kind ? wave * 64 : wn * 128;
-      const int ni_lim = cur.kind ? 4 : 8, wave_cols = cur.kind ? 64 : 128;
+      const int row_base = NI == 4 ? 0 : wm * 128, col_base = NI == 4 ? wave * 64 : wn * 128;
       const int cols = min(BN, Nout - cur.col0);
-      const int ncol = min(cols - col_base, wave_cols);   // valid columns of this wavefront's part (may be <= 0)
+      const int ncol = min(cols - col_base, NI * 16);   // valid columns of this wavefront's part (may be <= 0)
       const int nrow = cur.rows - row_base;               // valid rows of it (may be <= 0)
-      const bool full = cur.kind == 0 && cur.rows == BM && cols == BN;
+      const bool full = NI == 8 && cur.rows == BM && cols == BN;
       int my_slot_id = (mode == 2 ? kMaxPersistentBlocks : 0) + static_cast<int>(blockIdx.x);
       asm volatile("" : "+s"(my_slot_id));
       f32x4* my_slot = reinterpret_cast<f32x4*>(slots + static_cast<size_t>(my_slot_id) * kSlotFloats) + tid_l;
@@ -676,9 +715,9 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
           asm volatile("ds_read_b128 %0, %1" : "=v"(back[i]) : "v"(epi + r * 256 + ((ec ^ r) << 4)) : "memory");
         }
       };
-      // v[ni] += the partial sums of block row mi, NI blocks wide, C contributors at a time
-      auto add_partials = [&](auto c_c, auto ni_c, int mi, f32x4 (&v)[8]) __attribute__((always_inline)) {
-        constexpr int CN = decltype(c_c)::value, NI = decltype(ni_c)::value;
+      // v[ni] += the partial sums of block row mi, CN contributors at a time
+      auto add_partials = [&](int mi, f32x4 (&v)[NI]) __attribute__((always_inline)) {
+        constexpr int CN = NI == 8 ? 3 : 7;
         for (int c0 = 0; c0 < n_contrib; c0 += CN) {
           f32x4 p[CN][NI];
 #pragma unroll
@@ -701,6 +740,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       };
       const bool plain = full && mode == 0 && n_contrib == 0;
       if (plain) {
+        if constexpr (NI == 8) {
         // (no branches: they cost a wavefront that is alone on its SIMD more than the work they would skip)
         each<8>([&](auto mi_c) __attribute__((always_inline)) {
           constexpr int mi = decltype(mi_c)::value;
@@ -722,32 +762,28 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
           __builtin_amdgcn_sched_barrier(0);
         });
         store_rows(IC<7>{}, std::true_type{});
+        }
       } else {
       each<8>([&](auto mi_c) __attribute__((always_inline)) {
         constexpr int mi = decltype(mi_c)::value;
         const bool live = mi * 16 < nrow;   // (blocks of 16 rows with no valid row are neither sent nor fetched)
-        f32x4 v[8];
-        uint64_t packed[8];
+        f32x4 v[NI];
+        uint64_t packed[NI];
         if (live) {
 #pragma unroll
-          for (int ni = 0; ni < 8; ++ni)
+          for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[ni][e] = read_acc(acc[mi][ni][e]);
           if (mode == 0) {
             // Partial sums are added in CU order (fixed summation order); the loads of several CUs' slots go out
             // together, so that the wait is one memory latency for them all.
-            if (n_contrib > 0) {
-              if (cur.kind == 0) add_partials(IC<3>{}, IC<8>{}, mi, v);
-              else add_partials(IC<7>{}, IC<4>{}, mi, v);
-            }
+            if (n_contrib > 0) add_partials(mi, v);
             const float w = weight_of(mi);
 #pragma unroll
-            for (int ni = 0; ni < 8; ++ni)
-              if (ni < ni_lim) packed[ni] = finish(v[ni], w);
+            for (int ni = 0; ni < NI; ++ni) packed[ni] = finish(v[ni], w);
           } else {
 #pragma unroll
-            for (int ni = 0; ni < 8; ++ni)
-              if (ni < ni_lim) my_slot[(mi * 8 + ni) * kThreads] = v[ni];
+            for (int ni = 0; ni < NI; ++ni) my_slot[(mi * 8 + ni) * kThreads] = v[ni];
           }
         }
         __builtin_amdgcn_sched_barrier(0);   // one block at a time keeps the register footprint small
@@ -756,8 +792,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
             if ((mi - 1) * 16 < nrow) store_rows(IC<(mi > 0 ? mi - 1 : 0)>{}, std::false_type{});
           if (live) {
 #pragma unroll
-            for (int ni = 0; ni < 8; ++ni)
-              if (ni < ni_lim) write_block(ni, packed[ni]);
+            for (int ni = 0; ni < NI; ++ni) write_block(ni, packed[ni]);
             read_back();
           }
         }
@@ -798,6 +833,26 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
           __hip_atomic_store(flags + blockIdx.x, up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
+    }
+    };
+    if (cur.kind == 0) {
+      f32x4 acc[8][8];
+#pragma unroll
+      for (int mi = 0; mi < 8; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 8; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+      k_loop<DT, false, B_BY_ROWS, 32>(acc, a_base, b_base, tiles, stores_behind, load_big);
+      finish_segment(acc, IC<8>{});
+    } else {
+      f32x4 acc[8][4];
+#pragma unroll
+      for (int mi = 0; mi < 8; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (cur.kind == 1) small_loop(IC<1>{}, acc, tiles, stores_behind);
+      else if (cur.kind == 2) small_loop(IC<2>{}, acc, tiles, stores_behind);
+      else small_loop(IC<4>{}, acc, tiles, stores_behind);
+      finish_segment(acc, IC<4>{});
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -883,12 +938,14 @@ hipError_t setup_attrs(FastSetup& st, int dev) {
   using namespace fast;
   if (st.attrs) return hipSuccess;
 #define PPMOE_KERNELS(DT, R)                                                               \
-  reinterpret_cast<const void*>(grouped_gemm_fast_kernel<true, 0, DT, R>),            \
-      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 0, DT, R>),       \
-      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<true, 1, DT, R>),        \
-      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 2, DT, R>)
+  reinterpret_cast<const void*>(grouped_gemm_fast_kernel<true, 0, DT, R, false>),          \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 0, DT, R, false>),     \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<true, 1, DT, R, false>),      \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 2, DT, R, false>)
   const void* kernels[] = {PPMOE_KERNELS(MOE_BF16, false), PPMOE_KERNELS(MOE_BF16, true),
-                           PPMOE_KERNELS(MOE_F16, false), PPMOE_KERNELS(MOE_F16, true)};
+                           PPMOE_KERNELS(MOE_F16, false), PPMOE_KERNELS(MOE_F16, true),
+                           reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 0, MOE_BF16, false, true>),
+                           reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 0, MOE_F16, false, true>)};
 #undef PPMOE_KERNELS
   for (const void* k : kernels) {
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
@@ -974,7 +1031,7 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
                                     const int32_t* offsets, int n_exp, int few_most, int Nout,
                                     int K, void* workspace, hipStream_t s, int fuse,
                                     const int32_t* aux_rows, const float* aux_w, int aux_div,
-                                    const int32_t* aux_inv, bf16_t* C2) {
+                                    const int32_t* aux_inv, bf16_t* C2, bool b_by_rows) {
   using namespace fast;
   int blocks = 0, same_l2 = 0;
   hipError_t e = set_up_for_launch(s, &blocks, &same_l2);
@@ -997,10 +1054,11 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
       (fuse != 0 && aux_rows == nullptr) || (fuse == 2 && aux_w == nullptr) || aux_div < 1 ||
       (fuse == 2 && aux_div != 1 && (aux_inv == nullptr || C2 == nullptr)))
     return hipErrorInvalidValue;
-#define PPMOE_LAUNCH_DT(G, F, DT, R)                                                  \
-  grouped_gemm_fast_kernel<G, F, DT, R><<<blocks, kThreads, kLdsBytes, s>>>(     \
+#define PPMOE_LAUNCH_KERNEL(...)                                                      \
+  __VA_ARGS__<<<blocks, kThreads, kLdsBytes, s>>>(     \
       A, B, C, offsets, n_exp, few_most, Nout, K, slots, flags, epoch, same_l2, spin_limit, aux_rows, aux_w, aux_div, \
       aux_inv, C2)
+#define PPMOE_LAUNCH_DT(G, F, DT, R) PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<G, F, DT, R, false>)
 #define PPMOE_LAUNCH(G, F)                            \
   do {                                                \
     if (in_dtype == MOE_F16 && ragged) PPMOE_LAUNCH_DT(G, F, MOE_F16, true); \
@@ -1008,11 +1066,16 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
     else if (ragged) PPMOE_LAUNCH_DT(G, F, MOE_BF16, true);                  \
     else PPMOE_LAUNCH_DT(G, F, MOE_BF16, false);                             \
   } while (0)
-  if (fuse == 1) PPMOE_LAUNCH(true, 1);
+  if (b_by_rows) {
+    if (gelu || fuse != 0 || ragged) return hipErrorInvalidValue;
+    if (in_dtype == MOE_F16) PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<false, 0, MOE_F16, false, true>);
+    else PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<false, 0, MOE_BF16, false, true>);
+  } else if (fuse == 1) PPMOE_LAUNCH(true, 1);
   else if (fuse == 2) PPMOE_LAUNCH(false, 2);
   else if (gelu) PPMOE_LAUNCH(true, 0);
   else PPMOE_LAUNCH(false, 0);
 #undef PPMOE_LAUNCH_DT
+#undef PPMOE_LAUNCH_KERNEL
 #undef PPMOE_LAUNCH
   return hipGetLastError();
 }
