@@ -290,6 +290,20 @@ __device__ __forceinline__ bool no_expert_above(const int32_t* __restrict__ offs
   return __ballot(above) == 0;
 }
 
+// The data gradient's tile shape where the host's bound on the rows is loose (a rank with some of the
+// experts may get any share of the assignments): pick_cus = number of CUs says that both kernels are
+// launched and the row counts decide; the 256 x 256 one leaves when it would leave more than half of the
+// CUs without a tile, else the 128 x 128 one does.  With a long contraction it stays also when its tiles
+// are mostly empty (experts of up to about 128 rows): it does not fetch the rows that are not there, and the weights,
+// used once, come in with more loads in flight.  0: no such choice.
+__device__ __forceinline__ bool few_big_tiles(const int32_t* __restrict__ offsets, int n_exp, int N, int K, int pick_cus) {
+  if (pick_cus <= 0) return false;
+  int all = 0;
+  for (int i = 0; i < n_exp; ++i) all += (offsets[i + 1] - offsets[i] + 255) / 256;
+  const int64_t rows = offsets[n_exp] - offsets[0];
+  return 2 * all * ((N + 255) / 256) < pick_cus && (K <= 2048 || 20 * rows > 11 * 256 * static_cast<int64_t>(all));
+}
+
 // 16-bit fast path of the above: persistent, at most kMaxPersistentBlocks blocks.
 constexpr int kMaxPersistentBlocks = 256;
 size_t grouped_gemm_fast_workspace_bytes();
@@ -314,12 +328,12 @@ hipError_t grouped_gemm_set_up(hipStream_t s);
 // (0 = never wait).
 void grouped_gemm_fast_set_handover(int force_device_scope, int spin_limit);
 // few_most > 0: leaves, nothing done, if no expert has more rows than that.  b_by_rows: B is [n_exp, K, Nout] (K a multiple of
-// 64, no activation, no fuse).
+// 64, no activation, no fuse); pick_cus (with it only): see few_big_tiles.
 hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, const bf16_t* B, bf16_t* C,
                                     const int32_t* offsets, int n_exp, int few_most, int Nout,
                                     int K, void* workspace, hipStream_t s, int fuse,
                                     const int32_t* aux_rows, const float* aux_w, int aux_div,
-                                    const int32_t* aux_inv, bf16_t* C2, bool b_by_rows = false);
+                                    const int32_t* aux_inv, bf16_t* C2, bool b_by_rows = false, int pick_cus = 0);
 
 // Most segments the permutation can be asked for: kSegment assignments each when it counts them
 // itself, the tokens of one wavefront of the gating kernel each when that kernel counts them.

@@ -12,7 +12,7 @@
 // so in both an operand reaches the matrix cores across its rows.  Both run on the K loop of gemm_core.h, which reads
 // such an operand from LDS with the transposing read: the data gradients as the forward's persistent kernel with
 // weights by rows (gemm_fast.hip), the weight gradients as weight_gradient_kernel below.  What those do not take
-// (contractions of the data gradient that are no multiple of 64; weight matrices of too few tiles) goes to a plain kernel
+// (contractions of the data gradient that are no multiple of 64; too few tiles) goes to a plain kernel
 // with 128 x 128 x 64 tiles (two blocks per CU, scheduled by the compiler; MODE 0: data gradient, MODE 1: weight
 // gradient): four wavefronts (2 x 2), each a quarter of the tile as MFMA 32x32x16 blocks; operand
 // tiles go through LDS as [row][k] with k contiguous (rows 144 bytes apart, 16-byte chunks
@@ -300,9 +300,10 @@ __device__ __forceinline__ void accumulate_tile(const TileInfo& ti, int kt_begin
 template <int MODE, int DT, int BM, int BN>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ C,
-    const int32_t* __restrict__ offsets, int n_exp, int M, int N, int K) {
+    const int32_t* __restrict__ offsets, int n_exp, int M, int N, int K, int pick_cus) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   TileInfo ti;
+  if (MODE == 0 && pick_cus > 0 && !few_big_tiles(offsets, n_exp, N, K, pick_cus)) return;
   if (!locate_tile<MODE, BM, BN>(A, B, offsets, n_exp, M, N, K, ti)) return;
   f32x16 acc[BM / 64][BN / 64];
   accumulate_tile<MODE, DT, BM, BN>(ti, 0, ti.kt_count, acc, lds);
@@ -633,18 +634,28 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
     return hipSuccess;
   });
   if (attrs != hipSuccess) return attrs;
-  // cc[rows, n] = a[rows, k] b[i][k, n].  The persistent kernel takes contractions of whole k-tiles.
+  // cc[rows, n] = a[rows, k] b[i][k, n].  The persistent kernel takes contractions of whole k-tiles, unless that
+  // would leave more than half of the CUs without a tile; then 128 x 128 tiles, two blocks per CU.  The host knows the row
+  // count only as a bound (the counts live on the device).  Where the rank holds some of the experts that is every
+  // assignment there is: if an even share of them would be too few tiles, both shapes are launched and the row counts decide
+  // (few_big_tiles; the launch that leaves costs about 5 us).
   auto data_gradient = [&](const bf16_t* a, const bf16_t* b, bf16_t* cc, int n, int k) -> hipError_t {
     if (rows == 0) return hipSuccess;
-    if (k % BK == 0 && k < (1 << 22))
-      return launch_grouped_gemm_fast(c.in_dtype, false, a, b, cc, offsets, N, 0, n, k, gemm_ws, s, 0, nullptr, nullptr, 1,
-                                      nullptr, nullptr, true);
-    const int64_t tiles = ((rows + 127) / 128 + N) * ((n + 127) / 128);   // (the row counts are on the device: a bound)
+    auto few = [&](int64_t r) { return 2 * ((r + 255) / 256 + N) * ((n + 255) / 256) < n_cus; };
+    const bool big = k % BK == 0 && k < (1 << 22) && !few(rows);
+    const int pick_cus = big && N < c.E && few(rows * N / c.E) ? n_cus : 0;
+    if (big) {
+      const hipError_t e = launch_grouped_gemm_fast(c.in_dtype, false, a, b, cc, offsets, N, 0, n, k, gemm_ws, s, 0, nullptr,
+                                                    nullptr, 1, nullptr, nullptr, true, pick_cus);
+      if (e != hipSuccess || pick_cus == 0) return e;
+    }
+    // (as a second shape it has fewer than n_cus / 2 tiles of 256 x 256 to do, each four of its own)
+    const int64_t tiles = big ? 2 * n_cus : ((rows + 127) / 128 + N) * ((n + 127) / 128);
     const unsigned grid = static_cast<unsigned>((tiles + 7) / 8 * 8);
     if (c.in_dtype == MOE_F16)
-      grouped_gemm_bwd_kernel<0, MOE_F16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, 0, n, k);
+      grouped_gemm_bwd_kernel<0, MOE_F16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, 0, n, k, pick_cus);
     else
-      grouped_gemm_bwd_kernel<0, MOE_BF16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, 0, n, k);
+      grouped_gemm_bwd_kernel<0, MOE_BF16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, 0, n, k, pick_cus);
     return hipGetLastError();
   };
   // cc[i][m, n] = sum over the rows of expert i of a[r, m] b[r, n].  The persistent kernel (one block per CU) unless
@@ -660,9 +671,9 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
     const int64_t small_tiles = static_cast<int64_t>(N) * ((m + 127) / 128) * ((n + 127) / 128);
     const unsigned grid = static_cast<unsigned>((small_tiles + 7) / 8 * 8);
     if (c.in_dtype == MOE_F16)
-      grouped_gemm_bwd_kernel<1, MOE_F16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, m, n, 0);
+      grouped_gemm_bwd_kernel<1, MOE_F16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, m, n, 0, 0);
     else
-      grouped_gemm_bwd_kernel<1, MOE_BF16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, m, n, 0);
+      grouped_gemm_bwd_kernel<1, MOE_BF16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, m, n, 0, 0);
     return hipGetLastError();
   };
 

@@ -145,7 +145,12 @@ struct Fragments<false> {
     lds_read16<SLOT * kHalfTile + (I & 3) * 2048>(v[I], base[I >> 2]);
   }
   __device__ __forceinline__ u32x4 get(int r) const { return v[r]; }
-  __device__ __forceinline__ void tie() { asm volatile("" : PPMOE_TIE8(v) : : "memory"); }
+  template <int H>   // the fragments of k-step H
+  __device__ __forceinline__ void tie_half() { asm volatile("" : PPMOE_TIE4(v + 4 * H) : : "memory"); }
+  __device__ __forceinline__ void tie() {
+    tie_half<0>();
+    tie_half<1>();
+  }
 };
 template <>
 struct Fragments<true> {
@@ -156,9 +161,11 @@ struct Fragments<true> {
     lds_read_transposed<SLOT * kHalfTile + (I >> 3) * 8192 + (I & 1) * 1024>(v[I], base[(I >> 1) & 3]);
   }
   __device__ __forceinline__ u32x4 get(int r) const { return __builtin_shufflevector(v[2 * r], v[2 * r + 1], 0, 1, 2, 3); }
+  template <int H>
+  __device__ __forceinline__ void tie_half() { asm volatile("" : PPMOE_TIE8(v + 8 * H) : : "memory"); }
   __device__ __forceinline__ void tie() {
-    asm volatile("" : PPMOE_TIE8(v) : : "memory");
-    asm volatile("" : PPMOE_TIE8(v + 8) : : "memory");
+    tie_half<0>();
+    tie_half<1>();
   }
 };
 
@@ -207,7 +214,7 @@ __device__ __forceinline__ void k_loop(f32x4 (&acc)[8][8], const uint32_t (&a_ba
   Fragments<A_BY_ROWS> fa[2];   // by half
   Fragments<B_BY_ROWS> fb[2];
   uint32_t par = 0;
-  const int behind = stores_behind ? 2 : 0;
+  const int behind = __builtin_amdgcn_readfirstlane(stores_behind ? 2 : 0);
   wait_loads<24, up_to_63(24 + STORES)>(0, behind);
   __builtin_amdgcn_s_barrier();
   each<RA>([&](auto i) __attribute__((always_inline)) { fa[0].template read<0, i.value>(a_base); });
@@ -222,13 +229,6 @@ __device__ __forceinline__ void k_loop(f32x4 (&acc)[8][8], const uint32_t (&a_ba
     acc[mi][ni] = Elem16<DT>::mfma16(__builtin_bit_cast(vec8, fb[hb].get(ks * 4 + k)),
                                      __builtin_bit_cast(vec8, fa[ha].get(ks * 4 + i)), acc[mi][ni]);
     __builtin_amdgcn_sched_barrier(0);
-  };
-  auto landed = [&]() __attribute__((always_inline)) {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    fa[0].tie();
-    fa[1].tie();
-    fb[0].tie();
-    fb[1].tie();
   };
 #pragma clang loop unroll(disable)
   for (int t = 0; t < tiles; ++t) {
@@ -247,7 +247,9 @@ __device__ __forceinline__ void k_loop(f32x4 (&acc)[8][8], const uint32_t (&a_ba
     // B1 and A1 of this k-tile have landed (younger: the 16 loads of the next one), and every wavefront has read
     // A0 of this one and (but for k-step 1) B0.
     wait_loads<16, up_to_63(16 + STORES)>(t, behind);
-    landed();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    fa[0].tie();   // (the ties keep the MFMAs that use these fragments behind the wait)
+    fb[0].template tie_half<0>();
     __builtin_amdgcn_s_barrier();
     each<32>([&](auto x) __attribute__((always_inline)) {
       constexpr int X = decltype(x)::value;
@@ -259,11 +261,12 @@ __device__ __forceinline__ void k_loop(f32x4 (&acc)[8][8], const uint32_t (&a_ba
       if constexpr (X == 15) {
         if constexpr (B_BY_ROWS) asm volatile("s_waitcnt lgkmcnt(8)" ::: "memory");
         else asm volatile("s_waitcnt lgkmcnt(6)" ::: "memory");
-        fb[0].tie();
+        fb[0].template tie_half<1>();
       }
       if constexpr (X % 8 == 3) load(IC<0>{}, IC<X / 8>{}, t + 2);
     });
-    landed();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    fb[1].tie();
     each<32>([&](auto x) __attribute__((always_inline)) {
       constexpr int X = decltype(x)::value;
       mfma(IC<0>{}, IC<1>{}, x);
@@ -272,7 +275,8 @@ __device__ __forceinline__ void k_loop(f32x4 (&acc)[8][8], const uint32_t (&a_ba
     // A0 and B0 of the next k-tile have landed (younger: its B1 and A1 and A0 of the one after), and every
     // wavefront has read all of this one.
     wait_loads<12, up_to_63(12 + STORES)>(t + 1, behind);
-    landed();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    fa[1].tie();
     __builtin_amdgcn_s_barrier();
     each<32>([&](auto x) __attribute__((always_inline)) {
       constexpr int X = decltype(x)::value;
@@ -280,7 +284,6 @@ __device__ __forceinline__ void k_loop(f32x4 (&acc)[8][8], const uint32_t (&a_ba
       if constexpr (X < 16 && X % SA == 0) fa[0].template read<0, (X < 16 ? X / SA : 0)>(an);
       if constexpr (X < 24 && X % 4 == 3) load(IC<1 + X / 16>{}, IC<(X / 4) & 3>{}, t + 2);
     });
-    landed();
     each<32>([&](auto x) __attribute__((always_inline)) {
       constexpr int X = decltype(x)::value;
       mfma(IC<1>{}, IC<0>{}, x);
@@ -290,9 +293,15 @@ __device__ __forceinline__ void k_loop(f32x4 (&acc)[8][8], const uint32_t (&a_ba
     });
     par = nx;
   }
-  // (the fragments read last are not used; they land before the registers die, and the phantom loads before their slots are reused)
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  landed();
+  // (the fragments read last are not used; they land before the registers die, and the phantom loads before their slots are
+  // reused.  The accumulators are named as such: left to itself the register allocator keeps some of them elsewhere.)
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  fa[0].tie();
+  fb[0].template tie_half<0>();
+#pragma unroll
+  for (int mi = 0; mi < 8; ++mi)
+    asm volatile("" : "+a"(acc[mi][0]), "+a"(acc[mi][1]), "+a"(acc[mi][2]), "+a"(acc[mi][3]), "+a"(acc[mi][4]),
+                 "+a"(acc[mi][5]), "+a"(acc[mi][6]), "+a"(acc[mi][7]));
 }
 
 }  // namespace core

@@ -76,6 +76,17 @@ struct Segment {
   bool valid;
 };
 
+// Inclusive prefix sum over the wavefront.
+__device__ __forceinline__ int sum_over_lanes_up_to(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // Scratch for tiles cut between CUs: per block one slot of 256 x 256 float accumulators for the
 // partial sums it hands over and one flag, plus a second slot where it parks its own partial sums
 // when a hand-over it waited for did not arrive (the first slot may still be unread by its reader).
@@ -118,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
     const int32_t* __restrict__ offsets, int n_exp, int few_most, int Nout, int K, float* __restrict__ slots,
     uint32_t* __restrict__ flags, uint32_t epoch, int same_l2, int spin_limit,
     const int32_t* __restrict__ aux_rows, const float* __restrict__ aux_w, int aux_div,
-    const int32_t* __restrict__ aux_inv, bf16_t* __restrict__ C2) {
+    const int32_t* __restrict__ aux_inv, bf16_t* __restrict__ C2, int pick_cus) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
   __shared__ int contrib[kMaxPersistentBlocks / 8 + 1];   // [0] = how many, then the block ids whose slots to add
   __shared__ int contrib_failed;
@@ -129,6 +140,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // of C2) and its weight.
   __shared__ uint32_t row_list[FUSE == 0 ? 1 : 2 * BM], row_weight[FUSE == 2 ? 2 * BM : 1];
   if (few_most > 0 && no_expert_above(offsets, n_exp, few_most)) return;   // (the kernel for few rows has done it)
+  if (B_BY_ROWS && few_big_tiles(offsets, n_exp, Nout, K, pick_cus)) return;   // (the 128 x 128 tiles do it)
   const uint32_t my_xcc = xcc_id();
   // A block's flag is down before it can be looked at: whatever the caller's workspace held, a stale
   // word cannot pass for this launch's epoch (the readers poll tens of microseconds from now).
@@ -157,15 +169,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       hi = offsets[tid + 1];
       expert_tiles(hi - lo, kSmallRows, big_m, small);
     }
-    int big_sum = big_m, small_sum = small;   // over the lanes up to this one
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int bs = __shfl_up(big_sum, d, 64), ss = __shfl_up(small_sum, d, 64);
-      if (lane >= d) {
-        big_sum += bs;
-        small_sum += ss;
-      }
-    }
+    int big_sum = sum_over_lanes_up_to(big_m), small_sum = sum_over_lanes_up_to(small);
     if (lane == 63) {
       wave_sums[0][wave] = big_sum;
       wave_sums[1][wave] = small_sum;
@@ -245,13 +249,16 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   const int stream_big = cut_big ? lx1 - lx0 : 0;                  // big tiles at the head of the stream
   const int stream_tiles = stream_big + sx1 - sx0;
   const int64_t units = static_cast<int64_t>(stream_tiles) * KT;
-  // Rows of no whole k-tiles come with short contractions, where a hand-over costs more than the rest of the
-  // tile: the stream is then dealt out in whole tiles.  Up to 20 k-tiles always; up to 32 where a partial round keeps
-  // the other CUs from their shares; up to 40 where big tiles are in it.  3000 rows of 520 x 1000 over 4 experts 83 -> 26 us
-  // (few CUs had all the tiles: shares of kMinShare k-tiles), 700 of 1304 x 4000 67 -> 38, 1500 of 1608 x 328 over 2 experts 61 -> 39, 3000
-  // of 1992 x 4000 over 12 93 -> 63; beyond the lines: 136 of 1992 x 1000 over 12 cut 33, whole 46, 12000 of 1800 x 4000 over
-  // 12 cut 241, whole 255, 1500 of 3528 x 1000 over 2 cut 68, whole 80.
-  const bool whole = RAGGED && KT <= (stream_big > 0 ? 40 : full_rounds == 0 && rounds > 0 ? 32 : 20);
+  // With a short contraction a hand-over costs more than the rest of the tile, and a share of kMinShare k-tiles is
+  // several tiles one after another while other CUs idle: the stream is then dealt out in whole tiles.  Up to 20 k-tiles
+  // always; up to 32 where a partial round keeps the other CUs from their shares; up to 40 where big tiles are in it.  FFN
+  // backward, 8 experts of about 256 rows of 512 x 2048 (8 k-tiles): first product 42 us cut, 20 whole; the layers of
+  // 40 to 6000 tokens, 1 to 12 experts of 64 x 128 to 2048 x 8192: 0.74 of the time before in the mean, 0.83 where streams with big
+  // tiles are cut.  3000 rows of 520 x 1000 over 4 experts 83 -> 26 us, 700 of 1304 x 4000 67 -> 38, 1500 of 1608 x 328 over 2
+  // experts 61 -> 39, 3000 of 1992 x 4000 over 12 93 -> 63; beyond the lines: 136 of 1992 x 1000 over 12 cut 33, whole 46, 12000
+  // of 1800 x 4000 over 12 cut 241, whole 255, 1500 of 3528 x 1000 over 2 cut 68, whole 80.
+  // (A spin limit of 0 is the diagnostic setting in which nobody waits for a hand-over: it cuts all the same.)
+  const bool whole = spin_limit > 0 && KT <= (stream_big > 0 ? 40 : full_rounds == 0 && rounds > 0 ? 32 : 20);
   // Shares shorter than kMinShare k-tiles are not worth their hand-over: fewer CUs then take part.
   const int64_t worth = whole ? static_cast<int64_t>(stream_tiles) : units / kMinShare;
   const int takers = static_cast<int>(max(static_cast<int64_t>(1), min(static_cast<int64_t>(cus), worth)));
@@ -300,12 +307,11 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   auto small_tile = [&](int tile, Segment& s) {
     const int nth = tile / n_tiles;
     const Expert e = find_expert(IC<3>{}, nth);
-    const int lo = e.lo, hi = e.hi;
-    s.expert = e.index;
     int big_m, small;
-    expert_tiles(hi - lo, kSmallRows, big_m, small);
-    s.row0 = lo + big_m * BM;
-    s.rows = hi - s.row0;
+    expert_tiles(e.hi - e.lo, kSmallRows, big_m, small);
+    s.expert = e.index;
+    s.row0 = e.lo + big_m * BM;
+    s.rows = e.hi - s.row0;
     s.col0 = (tile - nth * n_tiles) * BN;
     s.kind = tile_kind(s.rows);
   };
@@ -622,7 +628,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
         contrib_failed = failed;
       }
       __syncthreads();
-      if (contrib_failed) {
+      if (__builtin_amdgcn_readfirstlane(contrib_failed)) {
         mode = 2;
         pending = nxt;
         nxt = cur;
@@ -638,7 +644,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         else
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        n_contrib = contrib[0];
+        n_contrib = __builtin_amdgcn_readfirstlane(contrib[0]);
       }
     }
 
@@ -656,13 +662,12 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       asm volatile("" : "+v"(tid_l));
       const int lane_l = tid_l & 63, fr_l = tid_l & 15, fq_l = lane_l >> 4;
       // Where this wavefront's accumulator blocks sit in the tile (see tile_kind).
-      const int row_base = NI == 4 ? 0 : wm * 128, col_base = NI == 4 ? wave * 64 : wn * 128;
+      const int row_base = NI == 8 ? wm * 128 : 0, col_base = NI == 8 ? wn * 128 : wave * 64;
       const int cols = min(BN, Nout - cur.col0);
       const int ncol = min(cols - col_base, NI * 16);   // valid columns of this wavefront's part (may be <= 0)
       const int nrow = cur.rows - row_base;               // valid rows of it (may be <= 0)
       const bool full = NI == 8 && cur.rows == BM && cols == BN;
-      int my_slot_id = (mode == 2 ? kMaxPersistentBlocks : 0) + static_cast<int>(blockIdx.x);
-      asm volatile("" : "+s"(my_slot_id));
+      const int my_slot_id = __builtin_amdgcn_readfirstlane((mode == 2 ? kMaxPersistentBlocks : 0) + static_cast<int>(blockIdx.x));
       f32x4* my_slot = reinterpret_cast<f32x4*>(slots + static_cast<size_t>(my_slot_id) * kSlotFloats) + tid_l;
       // The accumulators leave 16 rows at a time (all 128, or 64, columns of the wavefront) through 4 KiB of LDS of
       // the wavefront's own: rows of 256 bytes, 16-byte chunk c of row r at chunk c ^ r, written 8 bytes per lane,
@@ -1031,7 +1036,7 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
                                     const int32_t* offsets, int n_exp, int few_most, int Nout,
                                     int K, void* workspace, hipStream_t s, int fuse,
                                     const int32_t* aux_rows, const float* aux_w, int aux_div,
-                                    const int32_t* aux_inv, bf16_t* C2, bool b_by_rows) {
+                                    const int32_t* aux_inv, bf16_t* C2, bool b_by_rows, int pick_cus) {
   using namespace fast;
   int blocks = 0, same_l2 = 0;
   hipError_t e = set_up_for_launch(s, &blocks, &same_l2);
@@ -1057,7 +1062,7 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
 #define PPMOE_LAUNCH_KERNEL(...)                                                      \
   __VA_ARGS__<<<blocks, kThreads, kLdsBytes, s>>>(     \
       A, B, C, offsets, n_exp, few_most, Nout, K, slots, flags, epoch, same_l2, spin_limit, aux_rows, aux_w, aux_div, \
-      aux_inv, C2)
+      aux_inv, C2, pick_cus)
 #define PPMOE_LAUNCH_DT(G, F, DT, R) PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<G, F, DT, R, false>)
 #define PPMOE_LAUNCH(G, F)                            \
   do {                                                \
