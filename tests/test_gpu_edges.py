@@ -370,3 +370,57 @@ def test_data_gradient_tiles_with_tail_launches(dtype, counts):
         assert_close(to_np(dX[rows]), to_np(du @ w1), TOL[dtype], "dX_sliced", et)
         assert_close(to_np(dW1[i]), to_np(du.t() @ xs), TOL[dtype], "dW1", many)
         assert_close(to_np(dW2[i]), to_np(dy.t() @ h.detach()), TOL[dtype], "dW2", many)
+
+
+# ---------------------------------------------------------------- the persistent kernels' tiles
+
+@pytest.mark.parametrize("dtype,d,F,counts", [
+    ("bf16", 64, 320, [3] * 130 + [300]),              # lookups past 64 experts; one k-tile; a last column tile of 64
+    ("bf16", 128, 264, [32, 33, 64, 65, 128, 129]),    # every kind of small tile at its last size; a column tile of 8
+    ("bf16", 192, 256, [288, 289, 320, 321, 384, 385, 512, 0, 513]),    # the same behind whole tiles; three k-tiles
+    ("f16", 1280, 512, [257, 256, 0, 255]),            # 20 k-tiles, the last dealt whole
+    ("bf16", 1344, 2560, [256, 40, 300]),              # 21, and 40 in the second product: the last with big tiles in the stream
+    ("f16", 2624, 256, [700, 1]),                      # 41: cut again
+    ("bf16", 64, 8192, [5000, 3300, 41]),              # more than a round of one k-tile each, 128 k-tiles in the second product
+])
+def test_tiles_of_the_persistent_kernel(dtype, d, F, counts):
+    check_ffn(dtype, d, F, counts)
+
+
+@pytest.mark.parametrize("dtype,d,F,counts", [
+    ("bf16", 512, 2048, [0, 1, 63, 64, 65, 300, 1000, 700]),   # dH with weights by rows, all kinds of tiles; 128 tiles of weight gradients
+    ("f16", 512, 2048, [513, 0, 255, 128, 127, 33, 1100, 0]),
+    ("bf16", 520, 2056, [0, 1, 63, 64, 65, 191]),              # weight gradients: 3 x 9 tiles, the last ones of 8 columns
+    ("f16", 2112, 1032, [1200, 0, 130, 700]),                  # K of no whole k-tiles for dX, 33 k-tiles for dH; tiles of 8 and 64 columns
+])
+def test_gradient_tiles_by_rows(dtype, d, F, counts):
+    """Expert-FFN backward against the chain rule in float64 (torch); rows past the last packed one hold NaN."""
+    import torch
+    n, A = len(counts), int(sum(counts))
+    T = A + 70
+    lc = small_cfg(T=T, d=d, F=F, E=n, top_k=1, in_dtype=dtype, out_dtype=dtype)
+    cfg = B.config_from(lc)
+    g = torch.Generator(device="cuda").manual_seed(d + F)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch_dtype(dtype), device="cuda").normal_(0.0, std, generator=g)
+    x, dY, W1, W2 = draw(1.0, T, d), draw(1.0, T, d), draw(0.02, n, F, d), draw(0.02, n, d, F)
+    offsets = ragged_offsets(counts)
+    x[A:], dY[A:] = float("nan"), float("nan")
+    dX = torch.full_like(x, 5.0)
+    dW1, dW2 = (torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in ((n, F, d), (n, d, F)))
+    ws = torch.full((B.moe_ffn_backward_workspace_bytes(cfg),), 0xFF, dtype=torch.uint8, device="cuda")
+    B.moe_expert_ffn_backward(cfg, x, torch.from_numpy(offsets).cuda(), W1, W2, dY, dX, dW1, dW2, ws)
+    assert bool((dX[A:] == 5.0).all()), "rows past the last packed row were written"
+    et = GRAD_ELEM_FACTOR * TOL[dtype]
+    for i in range(n):
+        rows = slice(int(offsets[i]), int(offsets[i + 1]))
+        if counts[i] == 0:
+            assert float(dW1[i].abs().max()) == 0.0 and float(dW2[i].abs().max()) == 0.0
+            continue
+        xs, dy, w1, w2 = x[rows].double(), dY[rows].double(), W1[i].double(), W2[i].double()
+        u = (xs @ w1.t()).requires_grad_()
+        h = torch.nn.functional.gelu(u, approximate="tanh")
+        (du,) = torch.autograd.grad(h, u, dy @ w2)
+        many = et if counts[i] >= 256 else 1.0   # (elementwise only over many rows: see test_router_gradients)
+        assert_close(to_np(dX[rows]), to_np(du @ w1), TOL[dtype], "dX_sliced", et)
+        assert_close(to_np(dW1[i]), to_np(du.t() @ xs), TOL[dtype], "dW1", many)
+        assert_close(to_np(dW2[i]), to_np(dy.t() @ h.detach()), TOL[dtype], "dW2", many)
