@@ -333,11 +333,11 @@ def main():
                            "ffn_down_frac_of_roof": round(max(t_mfma, t_hbm) / (st["ffn_down"] * 1e-3), 4)}
     if t_hbm > t_mfma:
         dom_gbs = gemm_bytes / (st[dom] * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": f"grouped_gemm_bf16_fast_kernel ({dom})", "achieved": dom_gbs,
+        roofline = {"bound": "hbm", "kernel": f"grouped_gemm_fast_kernel ({dom})", "achieved": dom_gbs,
                     "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": dom_gbs / PEAK_HBM_GBS,
                     "traffic": measured_traffic(lc.name, dom)}
     else:
-        roofline = {"bound": "mfma", "kernel": f"grouped_gemm_bf16_fast_kernel ({dom})", "achieved": dom_tflops,
+        roofline = {"bound": "mfma", "kernel": f"grouped_gemm_fast_kernel ({dom})", "achieved": dom_tflops,
                     "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": dom_tflops / PEAK_BF16_TFLOPS,
                     "traffic": measured_traffic(lc.name, dom)}
 
