@@ -522,11 +522,19 @@ int moe_layer_forward_train(const moe_config* cfg, const void* x, const void* Wg
       PPMOE_TRY(launch_aux_loss(c, logits, expert_idx, l_aux, mean_prob, first_counts, ws + L.aux, s));
   }
   // The sliced tokens and both sides of the activation stay for the backward: the first GEMM stores
-  // U = X A, a pass over it H = GeLU(U).
+  // U = X A and H = GeLU(U) from its accumulators; with few rows or d not a multiple of 64 (kernels that store
+  // one result) it stores U, and a pass over it H.
   PPMOE_TRY(launch_slice(c, x, perm, offsets, x_sliced, rows, s));
-  PPMOE_TRY(launch_grouped_gemm(c.in_dtype, false, x_sliced, W1, U, offsets, c.local_count, rows, c.F, c.d,
-                                ws + L.gemm, s));
-  PPMOE_TRY(launch_gelu_rows(c, U, H, offsets, rows, s));
+  if (rows > 0 && c.d % 64 == 0 && grouped_gemm_is_fast(c.in_dtype, c.d) &&
+      grouped_gemm_few_rows_most(c.in_dtype, c.F, c.d, rows, c.local_count) == 0) {
+    PPMOE_TRY(launch_grouped_gemm_fast(c.in_dtype, true, static_cast<const bf16_t*>(x_sliced), static_cast<const bf16_t*>(W1),
+                                       static_cast<bf16_t*>(H), offsets, c.local_count, 0, c.F, c.d, ws + L.gemm, s, 0, nullptr,
+                                       nullptr, 1, nullptr, static_cast<bf16_t*>(U)));
+  } else {
+    PPMOE_TRY(launch_grouped_gemm(c.in_dtype, false, x_sliced, W1, U, offsets, c.local_count, rows, c.F, c.d,
+                                  ws + L.gemm, s));
+    PPMOE_TRY(launch_gelu_rows(c, U, H, offsets, rows, s));
+  }
   const int fuses = layer_fuses(c);
   if ((fuses & MOE_FUSE_COMBINE) && c.top_k == 1) {
     if (c.local_count < c.E || c.capacity_factor > 0.f)

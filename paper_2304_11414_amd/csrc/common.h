@@ -50,9 +50,9 @@ __device__ __forceinline__ f32x4 gelu_tanh4(f32x4 u) {
   // (the sched_barriers keep the compiler from folding the stages back into four serial chains)
   f32x4 z, e, r;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) z[i] = fmaf(0.044715f * u[i], u[i], 1.0f);
+  for (int i = 0; i < 4; ++i) z[i] = u[i] * u[i];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) z[i] = (-2.302208198f * u[i]) * z[i];   // -2 sqrt(2/pi) log2(e) (u + 0.044715 u^3)
+  for (int i = 0; i < 4; ++i) z[i] = u[i] * fmaf(-0.102943240f, z[i], -2.302208198f);   // -2 sqrt(2/pi) log2(e) (u + 0.044715 u^3)
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) e[i] = __builtin_amdgcn_exp2f(z[i]);
@@ -328,7 +328,8 @@ hipError_t grouped_gemm_set_up(hipStream_t s);
 // (0 = never wait).
 void grouped_gemm_fast_set_handover(int force_device_scope, int spin_limit);
 // few_most > 0: leaves, nothing done, if no expert has more rows than that.  b_by_rows: B is [n_exp, K, Nout] (K a multiple of
-// 64, no activation, no fuse); pick_cus (with it only): see few_big_tiles.
+// 64, no activation, no fuse); pick_cus (with it only): see few_big_tiles.  gelu without fuse and with C2: the pre-activations are
+// stored there (K a multiple of 64).
 hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, const bf16_t* B, bf16_t* C,
                                     const int32_t* offsets, int n_exp, int few_most, int Nout,
                                     int K, void* workspace, hipStream_t s, int fuse,

@@ -184,6 +184,16 @@ __device__ __forceinline__ void fragment_base(uint32_t lds0, int lane, int w, ui
   for (int b = 0; b < 4; ++b) base[b] = lds0 + (fq * 8 + j) * 256 + (((w * 4 + b) ^ (j + 4 * (fq & 1))) << 5) + sub * 8;
 }
 
+// A value that is the same in all lanes, in a scalar register.  (The builtin is dropped where the compiler sees that its
+// operand is uniform, and the value may then reach a scalar operand of inline assembly in a vector register.  The wait
+// states that the instruction needs after a write of its operand, and its result before a read, are written out: the compiler
+// does not look into inline assembly for them.)
+__device__ __forceinline__ int in_scalar(int v) {
+  int s;
+  asm volatile("s_nop 4\n\tv_readfirstlane_b32 %0, %1\n\ts_nop 4" : "=s"(s) : "v"(v));
+  return s;
+}
+
 // At most N vector memory operations outstanding; only M while t < behind.  (One branch, not taken in the steady state:
 // a taken one costs some 40 cycles of a wavefront that has nobody to hide them behind.)
 template <int N, int M>
@@ -214,7 +224,7 @@ __device__ __forceinline__ void k_loop(f32x4 (&acc)[8][8], const uint32_t (&a_ba
   Fragments<A_BY_ROWS> fa[2];   // by half
   Fragments<B_BY_ROWS> fb[2];
   uint32_t par = 0;
-  const int behind = __builtin_amdgcn_readfirstlane(stores_behind ? 2 : 0);
+  const int behind = in_scalar(stores_behind ? 2 : 0);
   wait_loads<24, up_to_63(24 + STORES)>(0, behind);
   __builtin_amdgcn_s_barrier();
   each<RA>([&](auto i) __attribute__((always_inline)) { fa[0].template read<0, i.value>(a_base); });

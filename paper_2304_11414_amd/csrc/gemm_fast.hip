@@ -123,7 +123,8 @@ __global__ __launch_bounds__(kThreads) void xcc_probe_kernel() {
 // end of a row belong to the next row: their loads get an offset no descriptor covers and read zeros,
 // which costs one vector OR per load (a variant of its own, so that the other one does not pay it).
 // B_BY_ROWS: B is [n_exp, K, Nout] (its contraction index is its row): the data gradients of the backward pass.
-template <bool GELU, int FUSE, int DT, bool RAGGED, bool B_BY_ROWS>
+// ACT: 0: no activation; 1: GeLU; 2: GeLU, and the pre-activations are stored as C2 (no FUSE): a training step keeps both.
+template <int ACT, int FUSE, int DT, bool RAGGED, bool B_BY_ROWS>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, int n_exp, int few_most, int Nout, int K, float* __restrict__ slots,
@@ -157,6 +158,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   const int wm = wave >> 1, wn = wave & 1;
   const int fr = lane & 15, fq = lane >> 4;
   const uint32_t lds0 = lds_address(lds);
+
+  constexpr int kStores = ACT == 2 ? 64 : 32;   // of a wavefront, for a whole tile
 
   // ---- the tile list ---------------------------------------------------------------------------
   const int n_tiles = (Nout + BN - 1) / BN;
@@ -497,12 +500,12 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       for (int b = 0; b < 4; ++b)
         wb[B_BY_ROWS ? b : 0] = lds0 + wave * 8192 + (fq * 8 + j) * 128 + ((b ^ ((j >> 1) + 2 * (fq & 1))) << 5) + (lane & 3) * 8;
     }
+    const int behind = in_scalar(stores_behind ? 1 : 0);
     int stage = 0;
 #pragma clang loop unroll(disable)
     for (int t = 0; t < tiles; ++t) {
       // the weights and tokens of k-tile t have landed (younger: the 8 weight loads of the next one)
-      if (stores_behind && t == 0) asm volatile("s_waitcnt vmcnt(40)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      wait_loads<8, (8 + kStores < 63 ? 8 + kStores : 63)>(t, behind);
       __builtin_amdgcn_s_barrier();
       const uint32_t ws = stage * kSmallWeights, ts = (t & 1) * kSmallTokens;
       const uint32_t t0 = tb[0] + ts, t1 = tb[1] + ts;
@@ -559,7 +562,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // the rest of the k range went there (their first segment, which they finished long ago).  If
   // those do not arrive it takes nobody's: it parks its own partial sums in its own slot (mode 2,
   // no flag) and runs the rest of the k range as one more segment, which ends by adding them back.
-  bool stores_behind = false;   // exactly 32 stores per wavefront were issued after the loads of a segment's first two k-tiles
+  bool stores_behind = false;   // exactly kStores stores per wavefront were issued after the loads of a segment's first two k-tiles
   bool begun = false;           // the loads of the next segment's first two k-tiles are under way
   while (nxt.valid) {
     // ---- a segment's products --------------------------------------------------------------------
@@ -679,8 +682,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       const int ec = lane_l & 15, er = fq_l;              // (read back: row i * 4 + er, chunk ec)
       const uint32_t list = lds_address(row_list) + cur.list * (BM * 4), weight = lds_address(row_weight) + cur.list * (BM * 4);
       u32x4 back[4];
-      // stores block mi (rows mi * 16 ..) of this wavefront's part from `back`
-      auto store_rows = [&](auto mi_c, auto full_c) __attribute__((always_inline)) {
+      // stores block mi (rows mi * 16 ..) of this wavefront's part from `back`, as rows of C or (pre) of the pre-activations
+      auto store_rows = [&](auto mi_c, auto full_c, bool pre) __attribute__((always_inline)) {
         constexpr int mi = decltype(mi_c)::value;
         int dst[4];
         if (FUSE == 2) {
@@ -693,18 +696,21 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int r = mi * 16 + i * 4 + er;
-          bf16_t* base = FUSE == 2 && dst[i] < 0 ? C2 : C;
+          bf16_t* base = (FUSE == 2 && dst[i] < 0) || (ACT == 2 && pre) ? C2 : C;
           const int row = FUSE == 2 ? (dst[i] >= 0 ? dst[i] : ~dst[i]) : cur.row0 + row_base + r;
           bf16_t* at = base + static_cast<size_t>(row) * Nout + cur.col0 + col_base + ec * 8;
           if (decltype(full_c)::value || (r < nrow && ec * 8 < ncol)) *reinterpret_cast<u32x4*>(at) = back[i];
         }
       };
-      // the final values of 16 x 16 block (mi, ni) as 16-bit elements
-      auto finish = [&](f32x4 y, float w) __attribute__((always_inline)) -> uint64_t {
-        if (GELU) y = gelu_tanh4(y);
-        if (FUSE == 2) y *= w;
+      auto as_is = [&](f32x4 y) __attribute__((always_inline)) -> uint64_t {
         return static_cast<uint64_t>(Elem16<DT>::pack2(y[0], y[1])) |
                (static_cast<uint64_t>(Elem16<DT>::pack2(y[2], y[3])) << 32);
+      };
+      // the final values of 16 x 16 block (mi, ni) as 16-bit elements
+      auto finish = [&](f32x4 y, float w) __attribute__((always_inline)) -> uint64_t {
+        if (ACT != 0) y = gelu_tanh4(y);
+        if (FUSE == 2) y *= w;
+        return as_is(y);
       };
       auto weight_of = [&](int mi) __attribute__((always_inline)) -> float {
         return FUSE == 2 ? __int_as_float(lds_read_word(weight + (row_base + mi * 16 + fr_l) * 4)) : 1.f;
@@ -749,7 +755,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
         // (no branches: they cost a wavefront that is alone on its SIMD more than the work they would skip)
         each<8>([&](auto mi_c) __attribute__((always_inline)) {
           constexpr int mi = decltype(mi_c)::value;
-          uint64_t packed[8];
+          uint64_t packed[8], before[8];   // (before: ACT 2)
           const float w = weight_of(mi);
           each<8>([&](auto ni_c) __attribute__((always_inline)) {
             constexpr int ni = decltype(ni_c)::value;
@@ -759,21 +765,27 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
             v[2] = read_acc(acc[mi][ni][2]);
             v[3] = read_acc(acc[mi][ni][3]);
             packed[ni] = finish(v, w);
+            if (ACT == 2) before[ni] = as_is(v);
           });
           __builtin_amdgcn_sched_barrier(0);
-          if constexpr (mi > 0) store_rows(IC<(mi > 0 ? mi - 1 : 0)>{}, std::true_type{});
+          if constexpr (mi > 0) store_rows(IC<(mi > 0 ? mi - 1 : 0)>{}, std::true_type{}, false);
+          if constexpr (ACT == 2) {
+            each<8>([&](auto ni_c) __attribute__((always_inline)) { write_block(ni_c.value, before[ni_c.value]); });
+            read_back();
+            store_rows(mi_c, std::true_type{}, true);
+          }
           each<8>([&](auto ni_c) __attribute__((always_inline)) { write_block(ni_c.value, packed[ni_c.value]); });
           read_back();
           __builtin_amdgcn_sched_barrier(0);
         });
-        store_rows(IC<7>{}, std::true_type{});
+        store_rows(IC<7>{}, std::true_type{}, false);
         }
       } else {
       each<8>([&](auto mi_c) __attribute__((always_inline)) {
         constexpr int mi = decltype(mi_c)::value;
         const bool live = mi * 16 < nrow;   // (blocks of 16 rows with no valid row are neither sent nor fetched)
         f32x4 v[NI];
-        uint64_t packed[NI];
+        uint64_t packed[NI], before[NI];
         if (live) {
 #pragma unroll
           for (int ni = 0; ni < NI; ++ni)
@@ -785,7 +797,10 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
             if (n_contrib > 0) add_partials(mi, v);
             const float w = weight_of(mi);
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) packed[ni] = finish(v[ni], w);
+            for (int ni = 0; ni < NI; ++ni) {
+              packed[ni] = finish(v[ni], w);
+              if (ACT == 2) before[ni] = as_is(v[ni]);
+            }
           } else {
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) my_slot[(mi * 8 + ni) * kThreads] = v[ni];
@@ -794,8 +809,14 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
         __builtin_amdgcn_sched_barrier(0);   // one block at a time keeps the register footprint small
         if (mode == 0) {
           if constexpr (mi > 0)
-            if ((mi - 1) * 16 < nrow) store_rows(IC<(mi > 0 ? mi - 1 : 0)>{}, std::false_type{});
+            if ((mi - 1) * 16 < nrow) store_rows(IC<(mi > 0 ? mi - 1 : 0)>{}, std::false_type{}, false);
           if (live) {
+            if constexpr (ACT == 2) {
+#pragma unroll
+              for (int ni = 0; ni < NI; ++ni) write_block(ni, before[ni]);
+              read_back();
+              store_rows(mi_c, std::false_type{}, true);
+            }
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) write_block(ni, packed[ni]);
             read_back();
@@ -803,7 +824,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
         }
         __builtin_amdgcn_sched_barrier(0);
       });
-        if (mode == 0 && 7 * 16 < nrow) store_rows(IC<7>{}, std::false_type{});
+        if (mode == 0 && 7 * 16 < nrow) store_rows(IC<7>{}, std::false_type{}, false);
       }
       if (mode == 0) {
         stores_behind = plain;
@@ -846,7 +867,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       for (int mi = 0; mi < 8; ++mi)
 #pragma unroll
         for (int ni = 0; ni < 8; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-      k_loop<DT, false, B_BY_ROWS, 32>(acc, a_base, b_base, tiles, stores_behind, load_big);
+      k_loop<DT, false, B_BY_ROWS, kStores>(acc, a_base, b_base, tiles, stores_behind, load_big);
       finish_segment(acc, IC<8>{});
     } else {
       f32x4 acc[8][4];
@@ -943,14 +964,16 @@ hipError_t setup_attrs(FastSetup& st, int dev) {
   using namespace fast;
   if (st.attrs) return hipSuccess;
 #define PPMOE_KERNELS(DT, R)                                                               \
-  reinterpret_cast<const void*>(grouped_gemm_fast_kernel<true, 0, DT, R, false>),          \
-      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 0, DT, R, false>),     \
-      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<true, 1, DT, R, false>),      \
-      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 2, DT, R, false>)
+  reinterpret_cast<const void*>(grouped_gemm_fast_kernel<1, 0, DT, R, false>),          \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<0, 0, DT, R, false>),     \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<1, 1, DT, R, false>),      \
+      reinterpret_cast<const void*>(grouped_gemm_fast_kernel<0, 2, DT, R, false>)
   const void* kernels[] = {PPMOE_KERNELS(MOE_BF16, false), PPMOE_KERNELS(MOE_BF16, true),
                            PPMOE_KERNELS(MOE_F16, false), PPMOE_KERNELS(MOE_F16, true),
-                           reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 0, MOE_BF16, false, true>),
-                           reinterpret_cast<const void*>(grouped_gemm_fast_kernel<false, 0, MOE_F16, false, true>)};
+                           reinterpret_cast<const void*>(grouped_gemm_fast_kernel<2, 0, MOE_BF16, false, false>),
+                           reinterpret_cast<const void*>(grouped_gemm_fast_kernel<2, 0, MOE_F16, false, false>),
+                           reinterpret_cast<const void*>(grouped_gemm_fast_kernel<0, 0, MOE_BF16, false, true>),
+                           reinterpret_cast<const void*>(grouped_gemm_fast_kernel<0, 0, MOE_F16, false, true>)};
 #undef PPMOE_KERNELS
   for (const void* k : kernels) {
     hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
@@ -1073,12 +1096,16 @@ hipError_t launch_grouped_gemm_fast(int in_dtype, bool gelu, const bf16_t* A, co
   } while (0)
   if (b_by_rows) {
     if (gelu || fuse != 0 || ragged) return hipErrorInvalidValue;
-    if (in_dtype == MOE_F16) PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<false, 0, MOE_F16, false, true>);
-    else PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<false, 0, MOE_BF16, false, true>);
-  } else if (fuse == 1) PPMOE_LAUNCH(true, 1);
-  else if (fuse == 2) PPMOE_LAUNCH(false, 2);
-  else if (gelu) PPMOE_LAUNCH(true, 0);
-  else PPMOE_LAUNCH(false, 0);
+    if (in_dtype == MOE_F16) PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<0, 0, MOE_F16, false, true>);
+    else PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<0, 0, MOE_BF16, false, true>);
+  } else if (fuse == 1) PPMOE_LAUNCH(1, 1);
+  else if (fuse == 2) PPMOE_LAUNCH(0, 2);
+  else if (gelu && C2 != nullptr) {   // (the pre-activations as well)
+    if (ragged) return hipErrorInvalidValue;
+    if (in_dtype == MOE_F16) PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<2, 0, MOE_F16, false, false>);
+    else PPMOE_LAUNCH_KERNEL(grouped_gemm_fast_kernel<2, 0, MOE_BF16, false, false>);
+  } else if (gelu) PPMOE_LAUNCH(1, 0);
+  else PPMOE_LAUNCH(0, 0);
 #undef PPMOE_LAUNCH_DT
 #undef PPMOE_LAUNCH_KERNEL
 #undef PPMOE_LAUNCH
