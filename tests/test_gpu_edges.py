@@ -424,3 +424,33 @@ def test_gradient_tiles_by_rows(dtype, d, F, counts):
         assert_close(to_np(dX[rows]), to_np(du @ w1), TOL[dtype], "dX_sliced", et)
         assert_close(to_np(dW1[i]), to_np(du.t() @ xs), TOL[dtype], "dW1", many)
         assert_close(to_np(dW2[i]), to_np(dy.t() @ h.detach()), TOL[dtype], "dW2", many)
+
+
+@pytest.mark.parametrize("dtype,T,d,F,E,k", [
+    ("bf16", 300, 64, 328, 2, 1),       # both sides of the activation from one product: one k-tile, a column tile of 72
+    ("f16", 1100, 256, 512, 4, 2),      # whole tiles and tails
+    ("bf16", 700, 2688, 256, 2, 1),     # 42 k-tiles: tiles cut between CUs
+    ("bf16", 24, 128, 256, 4, 1),       # few rows: the pass over U
+    ("f16", 300, 72, 136, 2, 1),        # d no multiple of 64: the pass over U
+])
+def test_training_pair_against_the_recomputing_calls(dtype, T, d, F, E, k):
+    """out of moe_layer_forward_train against moe_layer_forward, gradients from its kept intermediates against
+    moe_layer_backward (same routing, bit for bit): they differ by where U and H are rounded."""
+    import torch
+    lc = small_cfg(T=T, d=d, F=F, E=E, top_k=k, renorm_topk=k > 1, in_dtype=dtype, out_dtype=dtype)
+    cfg = B.config_from(lc)
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch_dtype(dtype), device="cuda").normal_(0.0, std, generator=g)
+    x, Wg, W1, W2, d_out = draw(1.0, T, d), draw(0.1, E, d), draw(0.05, E, F, d), draw(0.05, E, d, F), draw(1.0, T, d)
+    raw = lambda n: torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+    ws, bws, saved = raw(B.moe_workspace_bytes(cfg)), raw(B.moe_layer_backward_workspace_bytes(cfg)), raw(B.moe_layer_saved_bytes(cfg))
+    out = [torch.empty_like(x) for _ in range(2)]
+    grads = [[torch.empty_like(x)] + [torch.empty(s, device="cuda") for s in ((E, d), (E,), (E, F, d), (E, d, F))] for _ in range(2)]
+    B.moe_layer_forward(cfg, x, Wg, None, W1, W2, out[0], ws)
+    B.moe_layer_backward(cfg, x, Wg, None, W1, W2, d_out, *grads[0], bws)
+    B.moe_layer_forward_train(cfg, x, Wg, None, W1, W2, out[1], None, None, None, saved, ws)
+    B.moe_layer_backward_saved(cfg, x, Wg, W1, W2, d_out, saved, *grads[1], bws)
+    for name, a, b in [("out", *out)] + [(n, *p) for n, p in zip(("dx", "dWg", "dbias", "dW1", "dW2"), zip(*grads))]:
+        a, b = a.double(), b.double()
+        err = float((a - b).norm() / a.norm().clamp_min(1e-30))
+        assert err < TOL[dtype], f"{name}: {err:.2e}"   # (a rounding of U and of H is TOL / 8 at most in the 2-norm)
