@@ -262,8 +262,8 @@ int moe_layer_backward(const moe_config* cfg, const void* x, const void* Wg, con
  * moe_layer_forward_train is moe_layer_forward_aux (same `out`, l_aux, mean_prob, first_counts) that
  * also leaves in `saved` (>= moe_layer_saved_bytes(cfg) bytes of device memory, 16-byte aligned) the
  * routing (picks, gate weights, offsets, permutation and its inverse, the float32 logits), the
- * sliced tokens, U = x_sliced A and H = GeLU(U), both in in_dtype.  With few rows or d not a multiple of 64 the activation
- * is applied by a pass over the stored U, so H, and with it `out`, is rounded once more than in moe_layer_forward.
+ * sliced tokens, U = x_sliced A and H = GeLU(U), both in in_dtype.  H is GeLU of U as stored, so it, and with it `out`,
+ * is rounded once more than in moe_layer_forward, and has the bits that moe_layer_backward computes again.
  * moe_layer_backward_saved computes what moe_layer_backward computes (same outputs, same formulas)
  * from `saved` as the forward call with the same cfg, x, Wg, bias, W1 and W2 left it; it reads `saved`
  * and does not change it.  Neither call allocates or synchronises: a step can be captured into a

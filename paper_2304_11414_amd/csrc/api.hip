@@ -522,7 +522,7 @@ int moe_layer_forward_train(const moe_config* cfg, const void* x, const void* Wg
       PPMOE_TRY(launch_aux_loss(c, logits, expert_idx, l_aux, mean_prob, first_counts, ws + L.aux, s));
   }
   // The sliced tokens and both sides of the activation stay for the backward: the first GEMM stores
-  // U = X A and H = GeLU(U) from its accumulators; with few rows or d not a multiple of 64 (kernels that store
+  // U = X A and H = GeLU(U) (of U as stored); with few rows or d not a multiple of 64 (kernels that store
   // one result) it stores U, and a pass over it H.
   PPMOE_TRY(launch_slice(c, x, perm, offsets, x_sliced, rows, s));
   if (rows > 0 && c.d % 64 == 0 && grouped_gemm_is_fast(c.in_dtype, c.d) &&

@@ -503,8 +503,7 @@ __global__ __launch_bounds__(256) void act_backward_kernel(const bf16_t* __restr
         Elem16<DT>::widen2(gw[j], g[0], g[1]);
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          const float z2 = 1.5957691216057308f * u[e] * fmaf(0.044715f * u[e], u[e], 1.0f);   // 2 z
-          const float sg = 1.0f / (1.0f + __expf(-z2));
+          const float sg = gelu_sigmoid(u[e]);
           h[e] = u[e] * sg;
           const float dz2 = 1.5957691216057308f * fmaf(3.0f * 0.044715f * u[e], u[e], 1.0f);  // d(2 z)/du
           du[e] = g[e] * (sg + h[e] * (1.0f - sg) * dz2);
@@ -542,10 +541,7 @@ __global__ __launch_bounds__(256) void gelu_rows_kernel(const bf16_t* __restrict
       float u[2], h[2];
       Elem16<DT>::widen2(uw[j], u[0], u[1]);
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const float z2 = 1.5957691216057308f * u[e] * fmaf(0.044715f * u[e], u[e], 1.0f);
-        h[e] = u[e] * (1.0f / (1.0f + __expf(-z2)));
-      }
+      for (int e = 0; e < 2; ++e) h[e] = u[e] * gelu_sigmoid(u[e]);
       hw[j] = Elem16<DT>::pack2(h[0], h[1]);
     }
     reinterpret_cast<u32x4*>(H)[at] = u32x4{hw[0], hw[1], hw[2], hw[3]};

@@ -123,7 +123,8 @@ __global__ __launch_bounds__(kThreads) void xcc_probe_kernel() {
 // end of a row belong to the next row: their loads get an offset no descriptor covers and read zeros,
 // which costs one vector OR per load (a variant of its own, so that the other one does not pay it).
 // B_BY_ROWS: B is [n_exp, K, Nout] (its contraction index is its row): the data gradients of the backward pass.
-// ACT: 0: no activation; 1: GeLU; 2: GeLU, and the pre-activations are stored as C2 (no FUSE): a training step keeps both.
+// ACT: 0: no activation; 1: GeLU; 2: the pre-activations are stored as C2, and GeLU of them as stored (see gelu_sigmoid) as C
+// (no FUSE): a training step keeps both.
 template <int ACT, int FUSE, int DT, bool RAGGED, bool B_BY_ROWS>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
@@ -706,9 +707,19 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
         return static_cast<uint64_t>(Elem16<DT>::pack2(y[0], y[1])) |
                (static_cast<uint64_t>(Elem16<DT>::pack2(y[2], y[3])) << 32);
       };
+      // GeLU of pre-activations as they are stored (ACT 2)
+      auto gelu_of_stored = [&](uint64_t pre) __attribute__((always_inline)) -> uint64_t {
+        float a[4];
+        Elem16<DT>::widen2(static_cast<uint32_t>(pre), a[0], a[1]);
+        Elem16<DT>::widen2(static_cast<uint32_t>(pre >> 32), a[2], a[3]);
+        f32x4 y;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] = a[i] * gelu_sigmoid(a[i]);
+        return as_is(y);
+      };
       // the final values of 16 x 16 block (mi, ni) as 16-bit elements
       auto finish = [&](f32x4 y, float w) __attribute__((always_inline)) -> uint64_t {
-        if (ACT != 0) y = gelu_tanh4(y);
+        if (ACT == 1) y = gelu_tanh4(y);
         if (FUSE == 2) y *= w;
         return as_is(y);
       };
@@ -764,8 +775,12 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
             v[1] = read_acc(acc[mi][ni][1]);
             v[2] = read_acc(acc[mi][ni][2]);
             v[3] = read_acc(acc[mi][ni][3]);
-            packed[ni] = finish(v, w);
-            if (ACT == 2) before[ni] = as_is(v);
+            if (ACT == 2) {
+              before[ni] = as_is(v);
+              packed[ni] = gelu_of_stored(before[ni]);
+            } else {
+              packed[ni] = finish(v, w);
+            }
           });
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (mi > 0) store_rows(IC<(mi > 0 ? mi - 1 : 0)>{}, std::true_type{}, false);
@@ -798,8 +813,12 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
             const float w = weight_of(mi);
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
-              packed[ni] = finish(v[ni], w);
-              if (ACT == 2) before[ni] = as_is(v[ni]);
+              if (ACT == 2) {
+                before[ni] = as_is(v[ni]);
+                packed[ni] = gelu_of_stored(before[ni]);
+              } else {
+                packed[ni] = finish(v[ni], w);
+              }
             }
           } else {
 #pragma unroll

@@ -434,8 +434,8 @@ def test_gradient_tiles_by_rows(dtype, d, F, counts):
     ("f16", 300, 72, 136, 2, 1),        # d no multiple of 64: the pass over U
 ])
 def test_training_pair_against_the_recomputing_calls(dtype, T, d, F, E, k):
-    """out of moe_layer_forward_train against moe_layer_forward, gradients from its kept intermediates against
-    moe_layer_backward (same routing, bit for bit): they differ by where U and H are rounded."""
+    """out of moe_layer_forward_train against moe_layer_forward: they differ by the rounding of U (tests/gpu_util.py).  Gradients from
+    its kept intermediates against moe_layer_backward, which computes the same U and H again: the same bits."""
     import torch
     lc = small_cfg(T=T, d=d, F=F, E=E, top_k=k, renorm_topk=k > 1, in_dtype=dtype, out_dtype=dtype)
     cfg = B.config_from(lc)
@@ -450,7 +450,7 @@ def test_training_pair_against_the_recomputing_calls(dtype, T, d, F, E, k):
     B.moe_layer_backward(cfg, x, Wg, None, W1, W2, d_out, *grads[0], bws)
     B.moe_layer_forward_train(cfg, x, Wg, None, W1, W2, out[1], None, None, None, saved, ws)
     B.moe_layer_backward_saved(cfg, x, Wg, W1, W2, d_out, saved, *grads[1], bws)
-    for name, a, b in [("out", *out)] + [(n, *p) for n, p in zip(("dx", "dWg", "dbias", "dW1", "dW2"), zip(*grads))]:
-        a, b = a.double(), b.double()
-        err = float((a - b).norm() / a.norm().clamp_min(1e-30))
-        assert err < TOL[dtype], f"{name}: {err:.2e}"   # (a rounding of U and of H is TOL / 8 at most in the 2-norm)
+    assert_close(to_np(out[1]), to_np(out[0]), TOL[dtype], "out", GRAD_ELEM_FACTOR * TOL[dtype])
+    for name, a, b in zip(("dx", "dWg", "dbias", "dW1", "dW2"), *grads):
+        differ = int((a != b).sum())
+        assert differ == 0, f"{name}: {differ} elements"
