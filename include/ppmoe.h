@@ -285,8 +285,8 @@ int moe_layer_backward_saved(const moe_config* cfg, const void* x, const void* W
  * bounded wait.  The persistent kernel expects one block per compute unit to be resident at once,
  * i.e. the device not to be shared with another stream's kernels while it runs; if a block starts
  * late, the unit waiting for its partial sums gives up after the spin limit and computes that part
- * of the tile itself.  The OUTPUT IS COMPLETE AND CORRECT EITHER WAY (only the float32 summation
- * order of that tile differs from an undisturbed run, and time was lost); this call tells whether
+ * of the tile itself.  The OUTPUT IS COMPLETE AND HAS THE SAME BITS EITHER WAY (the missing sums are computed
+ * as their owners would have and added in the same order; only time was lost); this call tells whether
  * it happened.  It copies the kernel's word to the host (it SYNCHRONISES the stream) and sets
  * *status (host) to 0: every hand-over went through; 1: at least one partial sum did not arrive
  * within the spin limit; 2: writer and reader of a partial sum ran on different XCDs although the

@@ -22,8 +22,8 @@
 //
 // A hand-over that does not arrive within the spin limit (the persistent blocks were not all resident:
 // another kernel held compute units), or that would come from another XCD's L2, is not waited for:
-// the reading CU computes the missing k range itself, so the output tile is always complete and the
-// error word only reports lost time.
+// the reading CU computes the missing shares itself, each as its owner would have and added in the same order, so
+// the output tile is always complete, has the same bits, and the error word only reports lost time.
 //
 // A CU goes from one tile to the next without draining: the next tile is looked up while the current one
 // starts, its first two k-tiles are requested (the ring of the K loop is free by then) before the current tile's
@@ -72,7 +72,7 @@ struct Segment {
   int expert, row0, rows, col0, kind;
   int kb, ke, stream;
   int list;        // which of the two row lists in LDS is its
-  bool resumed;    // the rest of a tile whose hand-over did not arrive
+  bool resumed;    // another CU's share of a tile whose hand-over did not arrive
   bool valid;
 };
 
@@ -562,7 +562,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // holds it writes the output tile (mode 0), after adding the partial sums of the CUs after it, if
   // the rest of the k range went there (their first segment, which they finished long ago).  If
   // those do not arrive it takes nobody's: it parks its own partial sums in its own slot (mode 2,
-  // no flag) and runs the rest of the k range as one more segment, which ends by adding them back.
+  // no flag) and runs the other CUs' shares of the tile as segments of its own, one after another, each of
+  // which ends by adding the parked sums: the same sums in the same order, so the result has the same bits.
   bool stores_behind = false;   // exactly kStores stores per wavefront were issued after the loads of a segment's first two k-tiles
   bool begun = false;           // the loads of the next segment's first two k-tiles are under way
   while (nxt.valid) {
@@ -587,6 +588,18 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
 
     int mode = (cur.kb > 0 && !cur.resumed) ? 1 : 0;
     int n_contrib = 0;
+    // The next CU's share of the tile is computed here as well: its k range follows cur's.
+    auto resume = [&]() {
+      mode = 2;
+      pending = nxt;
+      nxt = cur;
+      nxt.kb = cur.ke;
+      const int64_t first = static_cast<int64_t>(cur.stream) * KT;   // of the tile in the stream
+      int c2 = share + 1;
+      while (share_begin(c2) <= first + cur.ke) ++c2;   // (the shares end with the stream, behind the tile)
+      nxt.ke = static_cast<int>(min(static_cast<int64_t>(KT), share_begin(c2) - first));
+      nxt.resumed = true;
+    };
     if (cur.resumed) {
       if (tid == 0) {
         contrib[0] = 1;
@@ -594,6 +607,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       }
       __syncthreads();
       n_contrib = 1;   // (this CU's own stores, complete since the barrier that followed them)
+      if (cur.ke < KT) resume();
     } else if (mode == 0 && cur.ke < KT) {
       if (tid == 0) {
         // One thread lists the CUs of the shares after this one that begin inside this tile (skipping empty
@@ -633,12 +647,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       }
       __syncthreads();
       if (__builtin_amdgcn_readfirstlane(contrib_failed)) {
-        mode = 2;
-        pending = nxt;
-        nxt = cur;
-        nxt.kb = cur.ke;
-        nxt.ke = KT;
-        nxt.resumed = true;
+        resume();
       } else {
         // Once per thread, after the flags are up.  Within an XCD the partial sums are in the shared L2
         // (stores write through the L1, and this CU has never read these lines since its L1 was
@@ -806,10 +815,10 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
           for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[ni][e] = read_acc(acc[mi][ni][e]);
+          // Partial sums are added in CU order (fixed summation order); the loads of several CUs' slots go out
+          // together, so that the wait is one memory latency for them all.
+          if (n_contrib > 0) add_partials(mi, v);
           if (mode == 0) {
-            // Partial sums are added in CU order (fixed summation order); the loads of several CUs' slots go out
-            // together, so that the wait is one memory latency for them all.
-            if (n_contrib > 0) add_partials(mi, v);
             const float w = weight_of(mi);
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
@@ -856,8 +865,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
               __hip_atomic_store(flags + contrib[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       } else if (mode == 2) {
-        // Parked: the stores are in the L2 once vmcnt is 0 (this CU's L1 holds no line of its own
-        // slot: it has not read it in this launch); the block meets, then goes on with the same tile.
+        // Parked: a thread reads back what it stored itself, once vmcnt is 0; the block meets, then goes on with
+        // the same tile.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
       } else {

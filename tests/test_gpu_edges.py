@@ -454,3 +454,104 @@ def test_training_pair_against_the_recomputing_calls(dtype, T, d, F, E, k):
     for name, a, b in zip(("dx", "dWg", "dbias", "dW1", "dW2"), *grads):
         differ = int((a != b).sum())
         assert differ == 0, f"{name}: {differ} elements"
+
+
+# ---------------------------------------------------------------- hand-over of partial sums between CUs
+
+def expert_chain(x, dY, W1, W2, offsets):
+    """H, y and the gradients of the expert FFN in float64 (torch), expert by expert."""
+    import torch
+    H, y, dX = (torch.zeros((x.shape[0], n), dtype=torch.float64, device="cuda") for n in (W1.shape[1], x.shape[1], x.shape[1]))
+    dW1, dW2 = (torch.zeros(W.shape, dtype=torch.float64, device="cuda") for W in (W1, W2))
+    for i in range(W1.shape[0]):
+        rows = slice(int(offsets[i]), int(offsets[i + 1]))
+        xs, dy, w1, w2 = x[rows].double(), dY[rows].double(), W1[i].double(), W2[i].double()
+        u = (xs @ w1.t()).requires_grad_()
+        h = torch.nn.functional.gelu(u, approximate="tanh")
+        (du,) = torch.autograd.grad(h, u, dy @ w2)
+        H[rows], y[rows], dX[rows] = h.detach(), h.detach() @ w2.t(), du @ w1
+        dW1[i], dW2[i] = du.t() @ xs, dy.t() @ h.detach()
+    return H, y, dX, dW1, dW2
+
+
+HANDOVER_SETTINGS = [(B.MOE_OPT_HANDOVER_DEVICE_SCOPE, 1, 0), (B.MOE_OPT_HANDOVER_SPIN_LIMIT, 0, 1 << 17)]   # (option, value, default)
+
+
+@pytest.mark.parametrize("dtype,counts", [
+    ("bf16", [300, 3, 0, 257, 40, 100]),   # big and small tiles in one cut stream, up to four CUs a tile
+    ("f16", [2048, 2048, 2048]),           # 24 x 11 big tiles: a round of 256 CUs, then one cut big tile per XCD
+])
+def test_cut_tiles_have_the_same_bits_however_they_are_handed_over(dtype, counts):
+    """Partial sums through the shared L2, with device-scope fences, or never waited for and computed by the CU that needs
+    them: the expert FFN and its backward (weights by columns and by rows) give the same bits.  42 and 43 k-tiles, past every
+    line below which a stream is dealt out in whole tiles, so all settings cut the same tiles."""
+    import torch
+    d, F, n, A = 2688, 2752, len(counts), sum(counts)
+    T = A + 800                              # (the data gradients go to the persistent kernel by this bound)
+    cfg = B.config_from(small_cfg(T=T, d=d, F=F, E=n, top_k=1, in_dtype=dtype, out_dtype=dtype))
+    g = torch.Generator(device="cuda").manual_seed(A)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch_dtype(dtype), device="cuda").normal_(0.0, std, generator=g)
+    x, dY, W1, W2 = draw(1.0, T, d), draw(1.0, T, d), draw(0.02, n, F, d), draw(0.02, n, d, F)
+    offsets = ragged_offsets(counts)
+    off = torch.from_numpy(offsets).cuda()
+
+    def run():
+        ws = torch.full((B.moe_ffn_workspace_bytes(cfg),), 0x11, dtype=torch.uint8, device="cuda")
+        bws = torch.full((B.moe_ffn_backward_workspace_bytes(cfg),), 0x11, dtype=torch.uint8, device="cuda")
+        H, y, dX = (torch.zeros((T, w), dtype=torch_dtype(dtype), device="cuda") for w in (F, d, d))
+        dW1, dW2 = torch.empty(W1.shape, device="cuda"), torch.empty(W2.shape, device="cuda")
+        B.moe_expert_ffn(cfg, x, off, W1, W2, H, y, ws)
+        B.moe_expert_ffn_backward(cfg, x, off, W1, W2, dY, dX, dW1, dW2, bws)
+        return [t[:A] for t in (H, y, dX)] + [dW1, dW2], B.moe_ffn_check(cfg, ws, False)
+
+    names = ("H", "y_sliced", "dX_sliced", "dW1", "dW2")
+    first, status = run()
+    assert status == 0
+    for name, a, b in zip(names, first, expert_chain(x[:A], dY[:A], W1, W2, offsets)):
+        et = TOL[dtype] if name in ("H", "y_sliced") else GRAD_ELEM_FACTOR * TOL[dtype] if min(counts) >= 256 else 1.0
+        assert_close(to_np(a), to_np(b), TOL[dtype], name, et)   # (weight gradients elementwise only over many rows)
+    for option, value, default in HANDOVER_SETTINGS:
+        B.moe_set_option(option, value)
+        try:
+            again, status = run()
+        finally:
+            B.moe_set_option(option, default)
+        assert status == (1 if option == B.MOE_OPT_HANDOVER_SPIN_LIMIT else 0)
+        for name, a, b in zip(names, first, again):
+            assert bool((a == b).all()), f"{name}, option {option}: {int((a != b).sum())} elements"
+
+
+@pytest.mark.parametrize("dtype,k", [("bf16", 1), ("f16", 2)])
+def test_layers_with_cut_tiles_have_the_same_bits_however_they_are_handed_over(dtype, k):
+    """The same for the products of a layer (rows gathered by the loads, placed by the stores) and of a training step, whose
+    first product stores two results."""
+    import torch
+    T, d, F, E = 1100, 2688, 2752, 4
+    cfg = B.config_from(small_cfg(T=T, d=d, F=F, E=E, top_k=k, renorm_topk=k > 1, in_dtype=dtype, out_dtype=dtype))
+    g = torch.Generator(device="cuda").manual_seed(k)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch_dtype(dtype), device="cuda").normal_(0.0, std, generator=g)
+    x, Wg, W1, W2, d_out = draw(1.0, T, d), draw(0.02, E, d), draw(0.02, E, F, d), draw(0.02, E, d, F), draw(1.0, T, d)
+
+    def run():
+        raw = lambda n: torch.full((n,), 0x11, dtype=torch.uint8, device="cuda")
+        ws, tws, bws, saved = (raw(f(cfg)) for f in (B.moe_workspace_bytes, B.moe_workspace_bytes,
+                                                     B.moe_layer_backward_workspace_bytes, B.moe_layer_saved_bytes))
+        out, out_t, dx = (torch.empty_like(x) for _ in range(3))
+        dWg, dbias, dW1, dW2 = (torch.empty(s, device="cuda") for s in ((E, d), (E,), (E, F, d), (E, d, F)))
+        B.moe_layer_forward(cfg, x, Wg, None, W1, W2, out, ws)
+        B.moe_layer_forward_train(cfg, x, Wg, None, W1, W2, out_t, None, None, None, saved, tws)
+        B.moe_layer_backward_saved(cfg, x, Wg, W1, W2, d_out, saved, dx, dWg, dbias, dW1, dW2, bws)
+        return [out, out_t, saved, dx, dWg, dbias, dW1, dW2], [B.moe_ffn_check(cfg, w, True) for w in (ws, tws)]
+
+    first, status = run()
+    assert status == [0, 0]
+    assert_close(to_np(first[1]), to_np(first[0]), TOL[dtype], "out", GRAD_ELEM_FACTOR * TOL[dtype])
+    for option, value, default in HANDOVER_SETTINGS:
+        B.moe_set_option(option, value)
+        try:
+            again, status = run()
+        finally:
+            B.moe_set_option(option, default)
+        assert status == ([1, 1] if option == B.MOE_OPT_HANDOVER_SPIN_LIMIT else [0, 0])
+        for name, a, b in zip(("out", "out (train)", "saved", "dx", "dWg", "dbias", "dW1", "dW2"), first, again):
+            assert bool((a == b).all()), f"{name}, option {option}: {int((a != b).sum())} elements"
