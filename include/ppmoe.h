@@ -11,10 +11,10 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).  Work is enqueued
  *     asynchronously; nothing here allocates or frees device memory.  Results are valid once the
  *     caller has synchronised the stream.  The calls that SYNCHRONISE the stream are: moe_init;
- *     moe_ffn_check; moe_ffn_clock; moe_event_elapsed_ms (on its event); and, once per device and only if moe_init
- *     has not been called for that device, the first expert-FFN call (moe_expert_ffn, _up, _down,
- *     moe_layer_forward, moe_expert_ffn_backward) with bf16/fp16 input -- unless that call is made
- *     under stream capture, where nothing synchronises (see moe_init).
+ *     moe_ffn_check; moe_backward_check; moe_ffn_clock; moe_event_elapsed_ms (on its event); and, once per
+ *     device and only if moe_init has not been called for that device, the first call that runs an expert
+ *     product (moe_expert_ffn, _up, _down and _backward, the moe_layer_* calls) with bf16/fp16 input --
+ *     unless that call is made under stream capture, where nothing synchronises (see moe_init).
  *   - Return value: MOE_OK (0) or a negative moe_status.  Arguments are validated on the host
  *     before anything is launched; on error nothing has been enqueued.
  *   - Weights are stored [out, in] (the contraction index is contiguous):
@@ -295,6 +295,11 @@ int moe_layer_backward_saved(const moe_config* cfg, const void* x, const void* W
  * moe_layer_forward; 0: the one given to moe_expert_ffn / _up / _down. */
 int moe_ffn_check(const moe_config* cfg, const void* workspace, int layer_workspace,
                   int32_t* status, void* stream);
+/* The same for the products of the backward calls.  layer_workspace != 0: `workspace` is the one given to
+ * moe_layer_backward or moe_layer_backward_saved; 0: the one given to moe_expert_ffn_backward.
+ * in_dtype BF16 or F16 only (MOE_ERR_DTYPE otherwise). */
+int moe_backward_check(const moe_config* cfg, const void* workspace, int layer_workspace,
+                       int32_t* status, void* stream);
 
 /* Combine (Sections 3.3.1/3.3.3, the index assignment that replaces the second all-to-all;
  * Algorithm 1: zeros_like + placement):

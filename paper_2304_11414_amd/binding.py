@@ -60,6 +60,7 @@ _PROTOTYPES = {
     "moe_layer_backward_saved": (c_int, [POINTER(MoeConfig)] + [c_void_p] * 6 + [c_size_t] + [c_void_p] * 6 +
                                  [c_size_t, c_void_p]),
     "moe_ffn_check": (c_int, [POINTER(MoeConfig), c_void_p, c_int, POINTER(c_int32), c_void_p]),
+    "moe_backward_check": (c_int, [POINTER(MoeConfig), c_void_p, c_int, POINTER(c_int32), c_void_p]),
     "moe_ffn_clock": (c_int, [POINTER(MoeConfig), c_void_p, c_int, POINTER(c_double), POINTER(c_double), c_void_p]),
     "moe_combine": (c_int, [POINTER(MoeConfig)] + [c_void_p] * 5),
     "moe_layer_forward": (c_int, [POINTER(MoeConfig)] + [c_void_p] * 7 + [c_size_t, POINTER(c_void_p), c_void_p]),
@@ -270,6 +271,14 @@ def moe_ffn_check(cfg, workspace, layer_workspace, stream=None) -> int:
     status = c_int32(-1)
     _check(load_library().moe_ffn_check(byref(cfg), _ptr(workspace), int(bool(layer_workspace)),
                                         byref(status), _stream(stream)), "moe_ffn_check")
+    return status.value
+
+
+def moe_backward_check(cfg, workspace, layer_workspace, stream=None) -> int:
+    """moe_ffn_check for the workspace of moe_layer_backward(_saved) or, layer_workspace false, moe_expert_ffn_backward."""
+    status = c_int32(-1)
+    _check(load_library().moe_backward_check(byref(cfg), _ptr(workspace), int(bool(layer_workspace)),
+                                             byref(status), _stream(stream)), "moe_backward_check")
     return status.value
 
 

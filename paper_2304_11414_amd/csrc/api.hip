@@ -1,6 +1,6 @@
 // Host side of libppmoe.so: argument validation, workspace layout and the launch sequence of
 // Algorithm 1 (without its closing all-reduce).  Nothing here allocates; what may synchronise is
-// listed in ppmoe.h (moe_init, moe_ffn_check, moe_event_elapsed_ms, and the first expert-FFN call on
+// listed in ppmoe.h (moe_init, moe_ffn_check, moe_backward_check, moe_event_elapsed_ms, and the first expert-FFN call on
 // a device that moe_init has not prepared).
 
 #include <cmath>
@@ -602,6 +602,14 @@ int moe_layer_backward_saved(const moe_config* cfg, const void* x, const void* W
   return MOE_OK;
 }
 
+// The error word of the persistent GEMM's scratch `gemm`, as a status.
+static int gemm_check(const unsigned char* gemm, int32_t* status, void* stream) {
+  uint32_t word = 0;
+  if (read_gemm_error_word(gemm, &word, static_cast<hipStream_t>(stream)) != hipSuccess) return MOE_ERR_HIP;
+  *status = (word & 0xffffff00u) == kGemmErrorMagic ? static_cast<int32_t>(word & 0xffu) : 0;
+  return MOE_OK;
+}
+
 int moe_ffn_check(const moe_config* cfg, const void* workspace, int layer_workspace,
                   int32_t* status, void* stream) {
   int st = check_config(cfg);
@@ -614,11 +622,22 @@ int moe_ffn_check(const moe_config* cfg, const void* workspace, int layer_worksp
     layout_of(*cfg, &L, &total);
     ws += L.gemm;
   }
-  uint32_t word = 0;
-  if (read_gemm_error_word(ws, &word, static_cast<hipStream_t>(stream)) != hipSuccess)
-    return MOE_ERR_HIP;
-  *status = (word & 0xffffff00u) == kGemmErrorMagic ? static_cast<int32_t>(word & 0xffu) : 0;
-  return MOE_OK;
+  return gemm_check(ws, status, stream);
+}
+
+int moe_backward_check(const moe_config* cfg, const void* workspace, int layer_workspace, int32_t* status, void* stream) {
+  int st = check_config(cfg);
+  if (st != MOE_OK) return st;
+  if (!is_16bit(cfg->in_dtype)) return MOE_ERR_DTYPE;
+  if (workspace == nullptr || status == nullptr) return MOE_ERR_NULL;
+  const unsigned char* ws = static_cast<const unsigned char*>(workspace);
+  if (layer_workspace) {
+    backward_layout L;
+    size_t total = 0;
+    backward_layout_of(*cfg, &L, &total);
+    ws += L.ffn;
+  }
+  return gemm_check(ws + expert_ffn_backward_gemm_offset(*cfg, max_rows_of(*cfg)), status, stream);
 }
 
 int moe_ffn_clock(const moe_config* cfg, const void* workspace, int layer_workspace, double* shader_ghz,

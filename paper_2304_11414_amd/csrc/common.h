@@ -220,6 +220,7 @@ hipError_t launch_grouped_gemm(int in_dtype, bool gelu, const void* A, const voi
 // Backward of the expert FFN on the packed rows (16-bit types only): dX [rows, d] 16-bit,
 // dW1 [n_exp, F, d] and dW2 [n_exp, d, F] float32; scratch: expert_ffn_backward_scratch_bytes bytes.
 size_t expert_ffn_backward_scratch_bytes(const moe_config& c, int64_t rows);
+size_t expert_ffn_backward_gemm_offset(const moe_config& c, int64_t rows);   // of the persistent GEMM's part of it
 hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const void* x_sliced,
                                       const int32_t* offsets, const void* W1, const void* W2,
                                       const void* dY, void* dX, float* dW1, float* dW2, void* scratch,

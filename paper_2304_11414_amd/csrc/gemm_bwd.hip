@@ -577,10 +577,13 @@ static int cus_of_current_device() {
   return cus;
 }
 
+size_t expert_ffn_backward_gemm_offset(const moe_config& c, int64_t rows) {
+  // U, H, dU: three [rows, F] 16-bit buffers (256-byte aligned), then the persistent GEMM's scratch
+  return 3 * ((static_cast<size_t>(rows) * c.F * 2 + 255) & ~size_t(255));
+}
+
 size_t expert_ffn_backward_scratch_bytes(const moe_config& c, int64_t rows) {
-  // U, H, dU: three [rows, F] 16-bit buffers (256-byte aligned), the persistent GEMM's scratch
-  const size_t one = (static_cast<size_t>(rows) * c.F * 2 + 255) & ~size_t(255);
-  return 3 * one + ((grouped_gemm_workspace_bytes() + 255) & ~size_t(255));
+  return expert_ffn_backward_gemm_offset(c, rows) + ((grouped_gemm_workspace_bytes() + 255) & ~size_t(255));
 }
 
 hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const void* x_sliced,
@@ -597,7 +600,7 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
   const bf16_t* H = saved ? static_cast<const bf16_t*>(H_saved) : reinterpret_cast<const bf16_t*>(ws + one);
   bf16_t* H_out = saved ? nullptr : reinterpret_cast<bf16_t*>(ws + one);
   bf16_t* dU = reinterpret_cast<bf16_t*>(ws + 2 * one);
-  void* gemm_ws = ws + 3 * one;
+  void* gemm_ws = ws + expert_ffn_backward_gemm_offset(c, rows);
   const int N = c.local_count;
   const bf16_t* xs = static_cast<const bf16_t*>(x_sliced);
   const bf16_t* w1 = static_cast<const bf16_t*>(W1);

@@ -103,6 +103,9 @@ def test_invalid_arguments_are_rejected_before_any_launch(lib):
     assert lib.moe_slice_dispatch(ctypes.byref(ok), p, p, p, p, p, p, p, p, 0, None) == -5
     assert lib.moe_layer_forward(ctypes.byref(ok), p, p, None, p, p, p, p, 16, None, None) == -5
     assert lib.moe_layer_forward(None, p, p, None, p, p, p, p, 16, None, None) == -1
+    assert lib.moe_backward_check(ctypes.byref(ok), None, 1, None, None) == -1
+    f32 = B.make_config(64, 64, 64, 4, 1, in_dtype="f32", out_dtype="f32")
+    assert lib.moe_backward_check(ctypes.byref(f32), p, 1, ctypes.byref(ctypes.c_int32()), None) == -3   # no backward
     assert lib.moe_status_string(-5) == b"workspace too small"
     assert lib.moe_status_string(0) == b"ok"
     with pytest.raises(B.MoeError):

@@ -936,8 +936,14 @@ def test_ffn_check_reads_and_clears_the_error_word():
     ws = torch.empty(B.moe_ffn_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
     ws.fill_(0x11)                                   # small integers everywhere: not an error
     assert B.moe_ffn_check(cfg, ws, False) == 0
+    bws = torch.full((B.moe_ffn_backward_workspace_bytes(cfg),), 0x11, dtype=torch.uint8, device="cuda")
     word = (2 * 256 * 256 * 256 + 256) * 4           # two slots of 256 x 256 floats per block, then the flags
     for code in (1, 2):
         ws[word:word + 4] = torch.tensor([code, 0x45, 0x6f, 0x4d], dtype=torch.uint8, device="cuda")
         assert B.moe_ffn_check(cfg, ws, False) == code
         assert B.moe_ffn_check(cfg, ws, False) == 0  # reported once
+        assert B.moe_backward_check(cfg, bws, False) == 0
+        at = word + 3 * 256 * 128 * 2                # behind three buffers of 256 rows of 128 elements
+        bws[at:at + 4] = torch.tensor([code, 0x45, 0x6f, 0x4d], dtype=torch.uint8, device="cuda")
+        assert B.moe_backward_check(cfg, bws, False) == code
+        assert B.moe_backward_check(cfg, bws, False) == 0
