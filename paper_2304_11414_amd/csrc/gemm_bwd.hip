@@ -633,6 +633,9 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
     return hipSuccess;
   });
   if (attrs != hipSuccess) return attrs;
+  // An operand by rows on the persistent kernels: 32-bit offsets up to 63 rows past a k-tile's first (63 * 2^25 + 512 < 2^31,
+  // where the descriptors end); beyond that the 128 x 128 tiles, whose offsets have 64 bits.
+  constexpr int kColumnsByRows = 1 << 24;
   // cc[rows, n] = a[rows, k] b[i][k, n].  The persistent kernel takes contractions of whole k-tiles, unless that
   // would leave more than half of the CUs without a tile; then 128 x 128 tiles, two blocks per CU.  The host knows the row
   // count only as a bound (the counts live on the device).  Where the rank holds some of the experts that is every
@@ -641,7 +644,7 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
   auto data_gradient = [&](const bf16_t* a, const bf16_t* b, bf16_t* cc, int n, int k) -> hipError_t {
     if (rows == 0) return hipSuccess;
     auto few = [&](int64_t r) { return 2 * ((r + 255) / 256 + N) * ((n + 255) / 256) < n_cus; };
-    const bool big = k % BK == 0 && k < (1 << 22) && !few(rows);
+    const bool big = k % BK == 0 && k < (1 << 22) && n < kColumnsByRows && !few(rows);
     const int pick_cus = big && N < c.E && few(rows * N / c.E) ? n_cus : 0;
     if (big) {
       const hipError_t e = launch_grouped_gemm_fast(c.in_dtype, false, a, b, cc, offsets, N, 0, n, k, gemm_ws, s, 0, nullptr,
@@ -661,7 +664,7 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
   // that would leave more than half of the CUs without a tile; then 128 x 128 tiles, two blocks per CU.
   auto weight_gradient = [&](const bf16_t* a, const bf16_t* b, float* cc, int m, int n) -> hipError_t {
     const int64_t tiles = static_cast<int64_t>(N) * ((m + 255) / 256) * ((n + 255) / 256);
-    if (2 * tiles >= n_cus) {
+    if (2 * tiles >= n_cus && m < kColumnsByRows && n < kColumnsByRows) {
       const unsigned grid = static_cast<unsigned>(tiles < n_cus ? (tiles + 7) / 8 * 8 : n_cus);
       if (c.in_dtype == MOE_F16) weight_gradient_kernel<MOE_F16><<<grid, kThreads, kWgradLdsBytes, s>>>(a, b, cc, offsets, N, m, n);
       else weight_gradient_kernel<MOE_BF16><<<grid, kThreads, kWgradLdsBytes, s>>>(a, b, cc, offsets, N, m, n);

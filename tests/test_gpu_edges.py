@@ -306,6 +306,34 @@ def test_weight_gradients_over_more_than_two_to_the_31_elements():
     assert_close(to_np(dW2[0]), to_np(ref2), TOL["bf16"], "dW2", GRAD_ELEM_FACTOR * TOL["bf16"])
 
 
+def test_gradients_past_2_24_columns():
+    """Operands by rows of so many columns that 63 of them pass 2^31 bytes: the persistent kernels' 32-bit offsets do not
+    reach the last rows of a k-tile.  Reference: the chain rule in float64, at some of the columns, dX at all."""
+    import torch
+    T, d, F = 64, 64, 17_200_000
+    cfg = B.config_from(small_cfg(T=T, d=d, F=F, E=1, top_k=1))
+    g = torch.Generator(device="cuda").manual_seed(24)
+    draw = lambda std, *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, dY, W1, W2 = draw(1.0, T, d), draw(1.0, T, d), draw(0.1, 1, F, d), draw(0.1, 1, d, F)
+    dX = torch.empty_like(x)
+    dW1, dW2 = torch.empty(W1.shape, device="cuda"), torch.empty(W2.shape, device="cuda")
+    ws = torch.empty(B.moe_ffn_backward_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    B.moe_expert_ffn_backward(cfg, x, torch.tensor([0, T], dtype=torch.int32, device="cuda"), W1, W2, dY, dX, dW1, dW2, ws)
+
+    def columns(f):
+        u = (x.double() @ W1[0, f].double().t()).requires_grad_()
+        h = torch.nn.functional.gelu(u, approximate="tanh")
+        (du,) = torch.autograd.grad(h, u, dY.double() @ W2[0, :, f].double())
+        return h.detach(), du
+
+    ref = sum(columns(slice(f, f + (1 << 20)))[1] @ W1[0, f:f + (1 << 20)].double() for f in range(0, F, 1 << 20))
+    assert_close(to_np(dX), to_np(ref), TOL["bf16"], "dX_sliced", GRAD_ELEM_FACTOR * TOL["bf16"])
+    f = torch.cat([torch.arange(512), torch.randint(0, F, (2000,)), torch.arange(F - 512, F)]).cuda()
+    h, du = columns(f)
+    assert_close(to_np(dW1[0, f]), to_np(du.t() @ x.double()), TOL["bf16"], "dW1", 1.0)   # (elementwise only over many rows)
+    assert_close(to_np(dW2[0][:, f]), to_np(dY.double().t() @ h), TOL["bf16"], "dW2", 1.0)
+
+
 # ---------------------------------------------------------------- data gradient of a rank with some of the experts
 
 @pytest.mark.parametrize("counts", [
