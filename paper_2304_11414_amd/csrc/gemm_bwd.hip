@@ -34,8 +34,10 @@ constexpr int BK = 64;
 constexpr int kThreads = 256;
 constexpr int kRowBytes = 144;                // one tile row in LDS: 64 k-values (128 bytes) + 16 bytes of skew
 constexpr int kStages = 2;
-// Block tile BM x BN (each 128 or 256): two stages of (BM + BN) rows; 144 KiB for 256 x 256.
-constexpr int lds_bytes(int bm, int bn) { return kStages * (bm + bn) * kRowBytes; }
+constexpr int kTile = 128;                    // rows and columns of a block's tile
+constexpr int kTileBytes = kTile * kRowBytes;
+constexpr int kStageBytes = 2 * kTileBytes;
+constexpr int kPlainLdsBytes = kStages * kStageBytes;   // 72 KiB: two blocks per CU
 
 // Byte offset of 16-byte chunk `ch` (8 k-values) of tile row `row`: chunks are XOR-swizzled with the
 // row's group of 16, so that the eight rows a thread writes after its in-register transpose, 16 rows
@@ -55,19 +57,19 @@ struct Operand {
   int rows, ks;
 };
 
-// One operand tile is R rows (128 or 256) x 64 k = 8 R chunks of 16 bytes, staged by two wavefronts
-// (half: which of the two), R / 16 chunks per thread.
+// One operand tile is 128 rows x 64 k = 1024 chunks of 16 bytes, staged by two wavefronts
+// (half: which of the two), eight chunks per thread.
 //  * k contiguous in memory: lane = (row % 8) * 8 + chunk; eight lanes read one whole 128-byte line.
-//  * rows contiguous in memory: a thread reads an 8 (k) x 8 (rows) block per group of 128 rows, one
-//    16-byte piece from each of eight consecutive memory rows (16 lanes read 256 contiguous bytes of
+//  * rows contiguous in memory: a thread reads an 8 (k) x 8 (rows) block, one 16-byte piece from each of
+//    eight consecutive memory rows (16 lanes read 256 contiguous bytes of
 //    each), transposes it in registers (v_perm_b32) and writes eight 16-byte chunks, one per tile row.
-template <bool K_CONTIGUOUS, int R>
+template <bool K_CONTIGUOUS>
 __device__ __forceinline__ void load_tile(const Operand& op, int k0, int half, int lane, u32x4* v) {
   const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
   if (K_CONTIGUOUS) {
     const int ch = lane & 7;
 #pragma unroll
-    for (int i = 0; i < R / 16; ++i) {
+    for (int i = 0; i < 8; ++i) {
       const int row = (lane >> 3) + 8 * half + 16 * i;
       const bool ok = row < op.rows && k0 + ch * 8 < op.ks;
       v[i] = ok ? *reinterpret_cast<const u32x4*>(op.base + static_cast<int64_t>(row) * op.ld + k0 + ch * 8) : zero;
@@ -75,42 +77,36 @@ __device__ __forceinline__ void load_tile(const Operand& op, int k0, int half, i
   } else {
     const int rg = lane & 15, kg = half * 4 + (lane >> 4);
 #pragma unroll
-    for (int g = 0; g < R / 128; ++g) {
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        const int k = k0 + kg * 8 + kk;
-        const bool ok = k < op.ks && g * 128 + rg * 8 < op.rows;
-        v[g * 8 + kk] = ok ? *reinterpret_cast<const u32x4*>(op.base + static_cast<int64_t>(k) * op.ld + g * 128 + rg * 8) : zero;
-      }
+    for (int kk = 0; kk < 8; ++kk) {
+      const int k = k0 + kg * 8 + kk;
+      const bool ok = k < op.ks && rg * 8 < op.rows;
+      v[kk] = ok ? *reinterpret_cast<const u32x4*>(op.base + static_cast<int64_t>(k) * op.ld + rg * 8) : zero;
     }
   }
 }
 
-template <bool K_CONTIGUOUS, int R>
+template <bool K_CONTIGUOUS>
 __device__ __forceinline__ void store_tile(unsigned char* lds_tile, int half, int lane, const u32x4* v) {
   if (K_CONTIGUOUS) {
     const int ch = lane & 7;
 #pragma unroll
-    for (int i = 0; i < R / 16; ++i) {
+    for (int i = 0; i < 8; ++i) {
       const int row = (lane >> 3) + 8 * half + 16 * i;
       *reinterpret_cast<u32x4*>(lds_tile + lds_chunk(row, ch)) = v[i];
     }
   } else {
     const int rg = lane & 15, kg = half * 4 + (lane >> 4);
-    // v[g * 8 + kk] dword q holds tile rows 2q (low half) and 2q + 1 (high half) at k = kk; the chunk
+    // v[kk] dword q holds tile rows 2q (low half) and 2q + 1 (high half) at k = kk; the chunk
     // of tile row r wants, in dword q, k = 2q (low) and 2q + 1 (high).
 #pragma unroll
-    for (int g = 0; g < R / 128; ++g) {
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        u32x4 o;
-        const uint32_t sel = (r & 1) ? 0x07060302u : 0x05040100u;
-        o.x = __builtin_amdgcn_perm(v[g * 8 + 1][r >> 1], v[g * 8 + 0][r >> 1], sel);
-        o.y = __builtin_amdgcn_perm(v[g * 8 + 3][r >> 1], v[g * 8 + 2][r >> 1], sel);
-        o.z = __builtin_amdgcn_perm(v[g * 8 + 5][r >> 1], v[g * 8 + 4][r >> 1], sel);
-        o.w = __builtin_amdgcn_perm(v[g * 8 + 7][r >> 1], v[g * 8 + 6][r >> 1], sel);
-        *reinterpret_cast<u32x4*>(lds_tile + lds_chunk(g * 128 + rg * 8 + r, kg)) = o;
-      }
+    for (int r = 0; r < 8; ++r) {
+      u32x4 o;
+      const uint32_t sel = (r & 1) ? 0x07060302u : 0x05040100u;
+      o.x = __builtin_amdgcn_perm(v[1][r >> 1], v[0][r >> 1], sel);
+      o.y = __builtin_amdgcn_perm(v[3][r >> 1], v[2][r >> 1], sel);
+      o.z = __builtin_amdgcn_perm(v[5][r >> 1], v[4][r >> 1], sel);
+      o.w = __builtin_amdgcn_perm(v[7][r >> 1], v[6][r >> 1], sel);
+      *reinterpret_cast<u32x4*>(lds_tile + lds_chunk(rg * 8 + r, kg)) = o;
     }
   }
 }
@@ -121,11 +117,11 @@ struct TileInfo {
   Operand opA, opB;   // opA: the operand whose tile rows are the output rows; opB: the output columns
 };
 
-template <int MODE, int BM, int BN>
+template <int MODE>
 __device__ __forceinline__ bool locate_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                             const int32_t* __restrict__ offsets, int n_exp, int M, int N,
                                             int K, TileInfo& ti) {
-  const int n_tiles = (N + BN - 1) / BN;
+  const int n_tiles = (N + kTile - 1) / kTile;
   ti.expert = ti.row0 = ti.rows = ti.col0 = ti.m0 = ti.kt_count = 0;
   // Consecutive block ids land on different XCDs (round robin over 8): remap so that each XCD works on
   // a contiguous run of the tile list and its L2 sees the same panels from many CUs.
@@ -137,21 +133,21 @@ __device__ __forceinline__ bool locate_tile(const bf16_t* __restrict__ A, const 
   if (MODE == 0) {
     // tiles ordered expert-major, then n-tile, then m-tile; blocks past the last tile leave
     int total = 0;
-    for (int i = 0; i < n_exp; ++i) total += (offsets[i + 1] - offsets[i] + BM - 1) / BM * n_tiles;
+    for (int i = 0; i < n_exp; ++i) total += (offsets[i + 1] - offsets[i] + kTile - 1) / kTile * n_tiles;
     int tile = xcd_tile(blockIdx.x, total);
     if (tile < 0) return false;
     bool found = false;
     int lo = offsets[0];
     for (int i = 0; i < n_exp && !found; ++i) {
       const int hi = offsets[i + 1];
-      const int m_tiles = (hi - lo + BM - 1) / BM;
+      const int m_tiles = (hi - lo + kTile - 1) / kTile;
       const int here = m_tiles * n_tiles;
       if (tile < here) {
         const int nt = tile / m_tiles, mt = tile - nt * m_tiles;
         ti.expert = i;
-        ti.row0 = lo + mt * BM;
-        ti.rows = min(BM, hi - ti.row0);
-        ti.col0 = nt * BN;
+        ti.row0 = lo + mt * kTile;
+        ti.rows = min(kTile, hi - ti.row0);
+        ti.col0 = nt * kTile;
         found = true;
       } else {
         tile -= here;
@@ -160,10 +156,10 @@ __device__ __forceinline__ bool locate_tile(const bf16_t* __restrict__ A, const 
     }
     if (!found) return false;
     ti.opA = Operand{A + static_cast<int64_t>(ti.row0) * K, K, ti.rows, K};
-    ti.opB = Operand{B + static_cast<int64_t>(ti.expert) * K * N + ti.col0, N, min(BN, N - ti.col0), K};
+    ti.opB = Operand{B + static_cast<int64_t>(ti.expert) * K * N + ti.col0, N, min(kTile, N - ti.col0), K};
     ti.kt_count = (K + BK - 1) / BK;
   } else {
-    const int m_tiles = (M + BM - 1) / BM;
+    const int m_tiles = (M + kTile - 1) / kTile;
     int tile = xcd_tile(blockIdx.x, n_exp * m_tiles * n_tiles);
     if (tile < 0) return false;
     // Tiles ordered in blocks of up to 32 (ba row tiles x bb column tiles of one expert: what the 32
@@ -179,13 +175,13 @@ __device__ __forceinline__ bool locate_tile(const bf16_t* __restrict__ A, const 
     ti.expert = tile / per_block;
     const int w = tile - ti.expert * per_block;
     const int mt = (blk / blocks_n) * ba + w / bb, nt = (blk % blocks_n) * bb + w % bb;
-    ti.m0 = mt * BM;
-    ti.col0 = nt * BN;
+    ti.m0 = mt * kTile;
+    ti.col0 = nt * kTile;
     const int lo = offsets[ti.expert], hi = offsets[ti.expert + 1];
-    ti.rows = min(BM, M - ti.m0);
+    ti.rows = min(kTile, M - ti.m0);
     // the contraction runs over the expert's packed rows: k = r - lo
     ti.opA = Operand{A + static_cast<int64_t>(lo) * M + ti.m0, M, ti.rows, hi - lo};
-    ti.opB = Operand{B + static_cast<int64_t>(lo) * N + ti.col0, N, min(BN, N - ti.col0), hi - lo};
+    ti.opB = Operand{B + static_cast<int64_t>(lo) * N + ti.col0, N, min(kTile, N - ti.col0), hi - lo};
     ti.kt_count = (hi - lo + BK - 1) / BK;
   }
   return true;
@@ -193,21 +189,20 @@ __device__ __forceinline__ bool locate_tile(const bf16_t* __restrict__ A, const 
 
 // Stores a block's accumulators.  A lane holds output row m = lane & 31 of each 32-row block and, in
 // register v, column n = (v / 4) * 8 + (lane >> 5) * 4 + v % 4: four consecutive columns per group.
-template <int MODE, int DT, int BM, int BN>
-__device__ __forceinline__ void store_tile_output(const f32x16 (&acc)[BM / 64][BN / 64], void* __restrict__ C,
+template <int MODE, int DT>
+__device__ __forceinline__ void store_tile_output(const f32x16 (&acc)[2][2], void* __restrict__ C,
                                                   const TileInfo& ti, int N, int M, int wm, int wn, int frow,
                                                   int half) {
-  constexpr int MI = BM / 64, NI = BN / 64;
-  const int cols = min(BN, N - ti.col0);
+  const int cols = min(kTile, N - ti.col0);
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-    const int m = wm * (BM / 2) + mi * 32 + frow;
+  for (int mi = 0; mi < 2; ++mi) {
+    const int m = wm * 64 + mi * 32 + frow;
     if (m >= ti.rows) continue;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
+    for (int ni = 0; ni < 2; ++ni) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int n = wn * (BN / 2) + ni * 32 + q * 8 + half * 4;
+        const int n = wn * 64 + ni * 32 + q * 8 + half * 4;
         if (n >= cols) continue;   // (N is a multiple of 8: a group of 4 columns is all in or all out)
         const float v0 = acc[mi][ni][q * 4 + 0], v1 = acc[mi][ni][q * 4 + 1];
         const float v2 = acc[mi][ni][q * 4 + 2], v3 = acc[mi][ni][q * 4 + 3];
@@ -226,11 +221,10 @@ __device__ __forceinline__ void store_tile_output(const f32x16 (&acc)[BM / 64][B
   }
 }
 
-// One output tile's products over the k-tiles [kt_begin, kt_end) into `acc`: two LDS stages, the next
-// k-tile's loads in flight while the current one is multiplied. 
-template <int MODE, int DT, int BM, int BN>
-__device__ __forceinline__ void accumulate_tile(const TileInfo& ti, int kt_begin, int kt_end,
-                                                f32x16 (&acc)[BM / 64][BN / 64], unsigned char* lds) {
+// One output tile's products into `acc` (2 x 2 blocks of 32 x 32 per wavefront): two LDS stages, the next
+// k-tile's loads in flight while the current one is multiplied.
+template <int MODE, int DT>
+__device__ __forceinline__ void accumulate_tile(const TileInfo& ti, f32x16 (&acc)[2][2], unsigned char* lds) {
   typedef typename Elem16<DT>::vec8 vec8;
   const Operand opA = ti.opA, opB = ti.opB;
   constexpr bool kAContig = MODE == 0;   // A[r, k]: k contiguous only for the data gradient
@@ -243,52 +237,48 @@ __device__ __forceinline__ void accumulate_tile(const TileInfo& ti, int kt_begin
   const bool stage_b = wave >= 2;
   const int stage_half = wave & 1;
 
-  constexpr int MI = BM / 64, NI = BN / 64;      // 32 x 32 blocks per wavefront, along m and along n
-  constexpr int kATileBytes = BM * kRowBytes;
-  constexpr int kStageBytes = (BM + BN) * kRowBytes;
-  constexpr int SR = BM > BN ? BM : BN;          // (the staging registers fit the larger operand tile)
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi)
+  for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+    for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
 
-  u32x4 g[SR / 16];
+  u32x4 g[8];
   auto load = [&](int kt) {
-    if (stage_b) load_tile<false, BN>(opB, kt * BK, stage_half, lane, g);
-    else load_tile<kAContig, BM>(opA, kt * BK, stage_half, lane, g);
+    if (stage_b) load_tile<false>(opB, kt * BK, stage_half, lane, g);
+    else load_tile<kAContig>(opA, kt * BK, stage_half, lane, g);
   };
   auto store = [&](unsigned char* buf) {
-    if (stage_b) store_tile<false, BN>(buf + kATileBytes, stage_half, lane, g);
-    else store_tile<kAContig, BM>(buf, stage_half, lane, g);
+    if (stage_b) store_tile<false>(buf + kTileBytes, stage_half, lane, g);
+    else store_tile<kAContig>(buf, stage_half, lane, g);
   };
-  if (kt_end > kt_begin) {
-    load(kt_begin);
+  if (ti.kt_count > 0) {
+    load(0);
     store(lds);
   }
   __syncthreads();
-  for (int kt = kt_begin; kt < kt_end; ++kt) {
-    unsigned char* cur = lds + ((kt - kt_begin) & 1) * kStageBytes;
-    unsigned char* nxt = lds + ((kt - kt_begin + 1) & 1) * kStageBytes;
-    if (kt + 1 < kt_end) load(kt + 1);
+  for (int kt = 0; kt < ti.kt_count; ++kt) {
+    unsigned char* cur = lds + (kt & 1) * kStageBytes;
+    unsigned char* nxt = lds + ((kt + 1) & 1) * kStageBytes;
+    if (kt + 1 < ti.kt_count) load(kt + 1);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      vec8 fa[MI], fb[NI];
+      vec8 fa[2], fb[2];
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi)
-        fa[mi] = *reinterpret_cast<const vec8*>(cur + lds_chunk(wm * (BM / 2) + mi * 32 + frow, ks * 2 + half));
+      for (int mi = 0; mi < 2; ++mi)
+        fa[mi] = *reinterpret_cast<const vec8*>(cur + lds_chunk(wm * 64 + mi * 32 + frow, ks * 2 + half));
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-        fb[ni] = *reinterpret_cast<const vec8*>(cur + kATileBytes + lds_chunk(wn * (BN / 2) + ni * 32 + frow, ks * 2 + half));
+      for (int ni = 0; ni < 2; ++ni)
+        fb[ni] = *reinterpret_cast<const vec8*>(cur + kTileBytes + lds_chunk(wn * 64 + ni * 32 + frow, ks * 2 + half));
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
+      for (int mi = 0; mi < 2; ++mi) {
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+        for (int ni = 0; ni < 2; ++ni)
           acc[mi][ni] = Elem16<DT>::mfma32(fb[ni], fa[mi], acc[mi][ni]);   // D[n][m]: lane = row m, registers = columns n
       }
     }
-    if (kt + 1 < kt_end) store(nxt);
+    if (kt + 1 < ti.kt_count) store(nxt);
     __syncthreads();
   }
 }
@@ -297,18 +287,18 @@ __device__ __forceinline__ void accumulate_tile(const TileInfo& ti, int kt_begin
 //                           A [rows, K] 16-bit, B [n_exp, K, N] 16-bit, C [rows, N] 16-bit
 // MODE 1 (weight gradient): C[i][m, n] = sum_{r in expert i} A[r, m] * B[r, n]
 //                           A [rows, M] 16-bit, B [rows, N] 16-bit, C [n_exp, M, N] float32
-template <int MODE, int DT, int BM, int BN>
+template <int MODE, int DT>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_bwd_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, void* __restrict__ C,
     const int32_t* __restrict__ offsets, int n_exp, int M, int N, int K, int pick_cus) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   TileInfo ti;
   if (MODE == 0 && pick_cus > 0 && !few_big_tiles(offsets, n_exp, N, K, pick_cus)) return;
-  if (!locate_tile<MODE, BM, BN>(A, B, offsets, n_exp, M, N, K, ti)) return;
-  f32x16 acc[BM / 64][BN / 64];
-  accumulate_tile<MODE, DT, BM, BN>(ti, 0, ti.kt_count, acc, lds);
+  if (!locate_tile<MODE>(A, B, offsets, n_exp, M, N, K, ti)) return;
+  f32x16 acc[2][2];
+  accumulate_tile<MODE, DT>(ti, acc, lds);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  store_tile_output<MODE, DT, BM, BN>(acc, C, ti, N, M, wave >> 1, wave & 1, lane & 31, lane >> 5);
+  store_tile_output<MODE, DT>(acc, C, ti, N, M, wave >> 1, wave & 1, lane & 31, lane >> 5);
 }
 
 // The weight gradients C[i][m, n] = sum_{r in expert i} A[r, m] * B[r, n] on 256 x 256 tiles: persistent, one block per CU,
@@ -616,14 +606,14 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
   const int n_cus = cus_of_current_device() & ~7;
   static std::atomic<uint64_t> attrs_done{0};
   const hipError_t attrs = once_per_device(attrs_done, [] {
-    const void* small[] = {reinterpret_cast<const void*>(grouped_gemm_bwd_kernel<0, MOE_BF16, 128, 128>),
-                           reinterpret_cast<const void*>(grouped_gemm_bwd_kernel<1, MOE_BF16, 128, 128>),
-                           reinterpret_cast<const void*>(grouped_gemm_bwd_kernel<0, MOE_F16, 128, 128>),
-                           reinterpret_cast<const void*>(grouped_gemm_bwd_kernel<1, MOE_F16, 128, 128>)};
+    const void* small[] = {reinterpret_cast<const void*>(grouped_gemm_bwd_kernel<0, MOE_BF16>),
+                           reinterpret_cast<const void*>(grouped_gemm_bwd_kernel<1, MOE_BF16>),
+                           reinterpret_cast<const void*>(grouped_gemm_bwd_kernel<0, MOE_F16>),
+                           reinterpret_cast<const void*>(grouped_gemm_bwd_kernel<1, MOE_F16>)};
     const void* big[] = {reinterpret_cast<const void*>(weight_gradient_kernel<MOE_BF16>),
                          reinterpret_cast<const void*>(weight_gradient_kernel<MOE_F16>)};
     for (const void* k : small) {
-      hipError_t err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(128, 128));
+      hipError_t err = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kPlainLdsBytes);
       if (err != hipSuccess) return err;
     }
     for (const void* k : big) {
@@ -655,9 +645,9 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
     const int64_t tiles = big ? 2 * n_cus : ((rows + 127) / 128 + N) * ((n + 127) / 128);
     const unsigned grid = static_cast<unsigned>((tiles + 7) / 8 * 8);
     if (c.in_dtype == MOE_F16)
-      grouped_gemm_bwd_kernel<0, MOE_F16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, 0, n, k, pick_cus);
+      grouped_gemm_bwd_kernel<0, MOE_F16><<<grid, kThreads, kPlainLdsBytes, s>>>(a, b, cc, offsets, N, 0, n, k, pick_cus);
     else
-      grouped_gemm_bwd_kernel<0, MOE_BF16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, 0, n, k, pick_cus);
+      grouped_gemm_bwd_kernel<0, MOE_BF16><<<grid, kThreads, kPlainLdsBytes, s>>>(a, b, cc, offsets, N, 0, n, k, pick_cus);
     return hipGetLastError();
   };
   // cc[i][m, n] = sum over the rows of expert i of a[r, m] b[r, n].  The persistent kernel (one block per CU) unless
@@ -673,9 +663,9 @@ hipError_t launch_expert_ffn_backward(const moe_config& c, int64_t rows, const v
     const int64_t small_tiles = static_cast<int64_t>(N) * ((m + 127) / 128) * ((n + 127) / 128);
     const unsigned grid = static_cast<unsigned>((small_tiles + 7) / 8 * 8);
     if (c.in_dtype == MOE_F16)
-      grouped_gemm_bwd_kernel<1, MOE_F16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, m, n, 0, 0);
+      grouped_gemm_bwd_kernel<1, MOE_F16><<<grid, kThreads, kPlainLdsBytes, s>>>(a, b, cc, offsets, N, m, n, 0, 0);
     else
-      grouped_gemm_bwd_kernel<1, MOE_BF16, 128, 128><<<grid, kThreads, lds_bytes(128, 128), s>>>(a, b, cc, offsets, N, m, n, 0, 0);
+      grouped_gemm_bwd_kernel<1, MOE_BF16><<<grid, kThreads, kPlainLdsBytes, s>>>(a, b, cc, offsets, N, m, n, 0, 0);
     return hipGetLastError();
   };
 
