@@ -360,18 +360,19 @@ def test_data_gradient_tiles_follow_the_rows(counts):
 
 
 @pytest.mark.parametrize("counts", [
-    [2000, 0, 31, 33],       # both data gradients on the 128 x 128 launch; the tail launches leave
+    [1200, 0, 31, 33],       # dX (8 column tiles, 64 k-tiles) and dH (16, 32) on the 128 x 128 launch: 7 row tiles
+    [2000, 0, 31, 33],       # 10 row tiles: dX on the 128 x 128 launch, dH on the 256 x 256 one
     [60, 100, 128, 9],       # dX: mostly empty tiles, 256 x 256 all the same; dH (K = 2048): 128 x 128
-    [3840, 0, 0, 0],         # dX: 15 row tiles x 8 column tiles, the last size there; dH (16 column tiles) on 256 x 256
-    [4000, 60, 0, 36],       # 256 x 256, no round saved by the tail launches
-    [8192, 20, 0, 0],        # 33 x 8 tiles, one round more than 256 CUs: the 20 rows are a tail
-    [8192, 0, 200, 0],       # the same with a remainder past 128
-    [44, 8000, 0, 300],      # remainders of 44 each side of a whole tile
+    [3840, 0, 0, 0],         # dX: 15 row tiles, the last size on the 128 x 128 launch; dH on 256 x 256
+    [4000, 60, 0, 36],       # 18 row tiles, both on 256 x 256; two small tiles
+    [8192, 20, 0, 0],        # dX: a round of 256 CUs; the 20 rows are small tiles, one an XCD
+    [8192, 0, 200, 0],       # dX: 33 x 8 big tiles: one an XCD behind the round, cut into the stream (64 k-tiles)
+    [44, 8000, 0, 300],      # small tiles of 44, 64 and 44 rows beside 32 row tiles
 ])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-def test_data_gradient_tiles_with_tail_launches(dtype, counts):
-    """A long contraction on a rank with some of the experts: four launches (256 x 256, 128 x 128, tails, their sums) take
-    one decision from the row counts, each by itself.  Reference: the chain rule in float64 (torch)."""
+def test_data_gradient_tiles_of_a_long_contraction(dtype, counts):
+    """A long contraction on a rank with some of the experts: two launches (256 x 256, 128 x 128) take one decision from
+    the row counts, each by itself.  Reference: the chain rule in float64 (torch)."""
     import torch
     d, F, T = 2048, 4096, 8448
     lc = small_cfg(T=T, d=d, F=F, E=64, top_k=1, local_begin=4, local_count=4, in_dtype=dtype, out_dtype=dtype)
@@ -419,7 +420,11 @@ def test_tiles_of_the_persistent_kernel(dtype, d, F, counts):
     ("bf16", 512, 2048, [0, 1, 63, 64, 65, 300, 1000, 700]),   # dH with weights by rows, all kinds of tiles; 128 tiles of weight gradients
     ("f16", 512, 2048, [513, 0, 255, 128, 127, 33, 1100, 0]),
     ("bf16", 520, 2056, [0, 1, 63, 64, 65, 191]),              # weight gradients: 3 x 9 tiles, the last ones of 8 columns
-    ("f16", 2112, 1032, [1200, 0, 130, 700]),                  # K of no whole k-tiles for dX, 33 k-tiles for dH; tiles of 8 and 64 columns
+    ("f16", 2112, 1032, [1200, 0, 130, 700]),                  # 128 x 128 data gradients: 65 x 5 tiles for dH, K of no whole k-tiles for dX
+    # dH on the persistent kernel with a last column tile of 8 (its loads run on into the next k-row, and past the expert's last
+    # one at the end), whole tiles and small ones of up to 32, 64 and 128 rows; dX of no whole k-tiles
+    ("bf16", 1088, 2056, [1044, 0, 1080, 1124, 1500, 1]),
+    ("f16", 2752, 1288, [2324, 60, 128, 1, 4000]),             # the same, 43 k-tiles: the small tiles are cut
 ])
 def test_gradient_tiles_by_rows(dtype, d, F, counts):
     """Expert-FFN backward against the chain rule in float64 (torch); rows past the last packed one hold NaN."""

@@ -209,7 +209,7 @@ def ragged_offsets(counts):
     ("bf16", 8192, 256, [33, 64, 65, 32]),        # only small tiles, each cut between eight CUs
     ("bf16", 2048, 512, [32, 33, 64, 65, 128, 129, 0, 1]),   # every small-tile height boundary
     # 33 row tiles x 8 column tiles: one round of the whole chip and one big tile left per XCD, which is
-    # cut into the stream (hand-over of a big tile's partial sums after whole rounds)
+    # dealt out whole with a contraction of 32 k-tiles
     ("bf16", 2048, 2048, [2304, 2048, 2048, 2048]),
     ("f32", 64, 136, [70, 0, 64, 1]),
     ("f32", 256, 1024, [64, 64, 64, 64]),
@@ -234,12 +234,16 @@ def test_expert_ffn_on_oracle_rows(dtype, d, F, counts):
     assert_close(y, y_ref, TOL[dtype], "y_sliced")
 
 
+# Tiles are cut between CUs past 40 k-tiles where big tiles are in the stream, past 20 where only small ones are; with a
+# spin limit of 0 in any case.
 CUT_TILE_CASES = [
-    (4096, 256, [300, 3, 0, 257]),        # long K: tail tiles go through the cut k-tile stream
-    (256, 4096, [129, 128, 600]),         # long K in the second GEMM
-    (8192, 256, [33, 64, 65, 32]),        # only small tiles, each cut between eight CUs
-    (512, 1024, [1024, 1000, 0, 24]),
-    (2048, 2048, [2304, 2048, 2048, 2048]),   # a round of the whole chip, then one cut big tile per XCD
+    (4096, 256, [300, 3, 0, 257]),        # 64 k-tiles, big and small tiles: cut (the second product has 4)
+    (256, 4096, [129, 128, 600]),         # 64 in the second product: cut
+    (8192, 256, [33, 64, 65, 32]),        # 128, only small tiles, each cut between eight CUs
+    (512, 1024, [1024, 1000, 0, 24]),     # 8 and 16: dealt out whole, no hand-over but with the spin limit of 0
+    (2048, 2048, [2304, 2048, 2048, 2048]),   # 32, one big tile per XCD behind a round of the chip: the same
+    (2688, 2048, [2304, 2048, 2048, 2048]),   # 42 in the first product: the big tile behind the round is cut
+    (1408, 1536, [33, 64, 65, 32]),       # 22 and 24, three small tiles per XCD: cut between four CUs
 ]
 
 
@@ -262,7 +266,8 @@ def run_cut_tile_case(d, F, counts):
 @pytest.mark.parametrize("d,F,counts", CUT_TILE_CASES)
 def test_handover_with_device_scope_fences(d, F, counts):
     """The hand-over of partial sums as a device with another block placement would do it
-    (device-scope release/acquire instead of the shared-L2 shortcut): same result, bit for bit."""
+    (device-scope release/acquire instead of the shared-L2 shortcut): same result, bit for bit
+    (also where tiles are dealt out whole and nothing is handed over)."""
     from paper_2304_11414_amd import binding as B
     H0, y0, st0 = run_cut_tile_case(d, F, counts)
     B.moe_set_option(B.MOE_OPT_HANDOVER_DEVICE_SCOPE, 1)
@@ -277,8 +282,8 @@ def test_handover_with_device_scope_fences(d, F, counts):
 
 @pytest.mark.parametrize("d,F,counts", CUT_TILE_CASES)
 def test_handover_that_never_arrives_is_recomputed(d, F, counts):
-    """Spin limit 0: a compute unit never waits for another one's partial sums and computes the rest
-    of its tile itself.  The output is still complete and within the bar; moe_ffn_check reports that
+    """Spin limit 0: a compute unit never waits for another one's partial sums and computes the other
+    shares of its tile itself.  The output is still complete and within the bar; moe_ffn_check reports that
     hand-overs were skipped (code 1), once.  Every kernel exits normally."""
     from paper_2304_11414_amd import binding as B
     B.moe_set_option(B.MOE_OPT_HANDOVER_SPIN_LIMIT, 0)
@@ -298,15 +303,12 @@ def test_handover_that_never_arrives_is_recomputed(d, F, counts):
     ("bf16", 512, 1024, [1024, 1000, 0, 24]),
     ("bf16", 1024, 256, [129, 128, 600, 3]),
     ("f16", 256, 512, [300, 0, 130, 1]),
-    # large enough for the 256 x 256 pipelined backward kernel in all four products: odd numbers of
+    # large enough for the persistent kernels in all four products: odd numbers of
     # k-tiles (17 and 33), partial column tiles, experts of 0, 1 and 65 rows, ragged contraction lengths
     ("bf16", 1088, 2112, [700, 0, 1, 2500, 65, 2800]),
     ("f16", 576, 4160, [300, 1500, 31, 0, 2000]),
-    # long contraction for dX (F >= 4096): the experts' rows past a multiple of 256 leave the
-    # 256 x 256 launch for the split-contraction tail launches when that saves a round -- 16 full row
-    # tiles x 16 column tiles fill the 256 CUs once, remainders of 3, 188, 128 and 176 rows (one or two
-    # 128-row tail tiles each: only splitting off all of them saves the round); then short tails only
-    # (no 256-row tile at all, remainders up to 128 suffice)
+    # 64 k-tiles in both data gradients: 16 full row tiles x 16 column tiles fill the 256 CUs once; of the remainders of 3, 188,
+    # 128 and 176 rows two are small tiles and two are big ones left behind the round; then small tiles only
     ("bf16", 4096, 4096, [1027, 700, 256, 1408, 1200, 0]),
     ("f16", 4096, 4096, [100, 128, 1, 0, 64, 37]),
 ])
@@ -524,7 +526,7 @@ def test_layer_backward(kw):
 
 def test_layer_backward_headline_size():
     """moe_layer_backward at the headline workload's full size, in the launch configuration the
-    benchmark times (256 x 256 pipelined kernels for all four gradient products, ragged experts of
+    benchmark times (persistent kernels for all four gradient products, ragged experts of
     982 ... 1118 rows): every gradient against the oracle's, element by element."""
     lc = synth.CONFIGS[1]
     inp = synth.make_inputs(lc)
@@ -556,8 +558,8 @@ def test_layer_is_bitwise_reproducible_and_ignores_workspace_contents():
 def test_backward_is_bitwise_reproducible():
     """Every sum of the backward has a fixed order (no atomics; partial sums of cut contractions and of
     token chunks are added in index order): two runs give the same bits.  A layer backward, the train
-    step's backward from kept intermediates, and an expert-FFN backward in the configuration with the
-    256 x 256 kernels and the split-contraction tail launches."""
+    step's backward from kept intermediates, and an expert-FFN backward on the persistent kernels whose
+    data gradients have tiles cut between CUs."""
     lc = small_cfg(T=1500, d=256, F=512, E=8, top_k=2, renorm_topk=True, seed=33)
     inp = synth.make_inputs(lc)
     dl = DeviceLayer(lc, inp)
@@ -573,7 +575,7 @@ def test_backward_is_bitwise_reproducible():
     counts = [1027, 700, 256, 1408, 1200, 0]
     n = len(counts)
     A = int(sum(counts))
-    lc2 = small_cfg(T=A, d=4096, F=4096, E=n, top_k=1, seed=35)   # (16 x 16 + 4 x 16 tiles: the tails go)
+    lc2 = small_cfg(T=A, d=4096, F=4096, E=n, top_k=1, seed=35)   # (18 x 16 big tiles: a round, then 4 cut per XCD)
     inp2 = synth.make_inputs(lc2, parts=("x", "W1_t", "W2_t"))
     dY = np.random.default_rng(8).standard_normal((A, lc2.d)).astype(np.float32)
     dl2 = DeviceLayer(lc2, inp2)
