@@ -234,10 +234,10 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // remainder (fewer than 8 cus tiles), an eighth to each XCD.
   const int chip = 8 * cus;
   const int full_rounds = total_big / chip, rem = total_big - full_rounds * chip;
-  const int lx0 = full_rounds * chip + static_cast<int>(static_cast<int64_t>(rem) * xcd / 8);
-  const int lx1 = full_rounds * chip + static_cast<int>(static_cast<int64_t>(rem) * (xcd + 1) / 8);
-  const int sx0 = static_cast<int>(static_cast<int64_t>(total_small) * xcd / 8);
-  const int sx1 = static_cast<int>(static_cast<int64_t>(total_small) * (xcd + 1) / 8);
+  const int lx0 = full_rounds * chip + ((rem * xcd) >> 3);
+  const int lx1 = full_rounds * chip + ((rem * (xcd + 1)) >> 3);
+  const int sx0 = ((total_small * xcd) >> 3);
+  const int sx1 = ((total_small * (xcd + 1)) >> 3);
   // The XCD's part of the remainder (r tiles) either runs as one more, partial round, in which
   // cus - r CUs idle for a tile's KT k-tiles, or joins the stream and is cut among all CUs, which
   // costs the hand-over of the big tiles' partial sums (256 KiB each, and an epilogue that waits for
@@ -249,11 +249,13 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // 320 k-tiles per XCD costs 6 % of the launch, running them as a round 3 %.
   const int rem_x = lx1 - lx0;
   const bool cut_big = rem_x > 0 && (rem_x * 4 <= cus ||
-                                     (full_rounds == 0 && static_cast<int64_t>(KT) * (cus - rem_x) >= 25 * cus));
+                                     (full_rounds == 0 && KT * (cus - rem_x) >= 25 * cus));
   const int rounds = full_rounds + (!cut_big && lx1 > lx0 ? 1 : 0);
   const int stream_big = cut_big ? lx1 - lx0 : 0;                  // big tiles at the head of the stream
   const int stream_tiles = stream_big + sx1 - sx0;
-  const int64_t units = static_cast<int64_t>(stream_tiles) * KT;
+  // (32 bits: KT <= 2^16, up to cus big tiles, and an eighth of the n_exp * n_tiles panels of weights; these fit the card's
+  // 288 GB, so units * cus stays below 2^31 also with 8 columns.  64-bit divisions are 100 instructions each, before the first load.)
+  const int units = stream_tiles * KT;
   // With a short contraction a hand-over costs more than the rest of the tile, and a share of kMinShare k-tiles is
   // several tiles one after another while other CUs idle: the stream is then dealt out in whole tiles.  Up to 20 k-tiles
   // always; up to 32 where a partial round keeps the other CUs from their shares; up to 40 where big tiles are in it.  FFN
@@ -265,11 +267,12 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // (A spin limit of 0 is the diagnostic setting in which nobody waits for a hand-over: it cuts all the same.)
   const bool whole = spin_limit > 0 && KT <= (stream_big > 0 ? 40 : full_rounds == 0 && rounds > 0 ? 32 : 20);
   // Shares shorter than kMinShare k-tiles are not worth their hand-over: fewer CUs then take part.
-  const int64_t worth = whole ? static_cast<int64_t>(stream_tiles) : units / kMinShare;
-  const int takers = static_cast<int>(max(static_cast<int64_t>(1), min(static_cast<int64_t>(cus), worth)));
+  const int takers = max(1, min(cus, whole ? stream_tiles : units / kMinShare));
   const int deal = whole ? KT : 1;   // k-tiles dealt out together
-  const int64_t deals = whole ? stream_tiles : units;
-  auto share_begin = [&](int c) -> int64_t { return deals * min(c, takers) / takers * deal; };
+  const int deals = whole ? stream_tiles : units;
+  auto share_begin = [&](int c) -> int {
+    return static_cast<int>(static_cast<uint32_t>(deals * min(c, takers)) / static_cast<uint32_t>(takers)) * deal;
+  };
   // When an XCD runs its share of the stream: before big round `stream_slot` (= rounds: after the
   // last one), the XCDs spread over the launch.  The stream's small tiles are bound by the HBM stream
   // of their weight panels and leave CUs without a share idle; the big tiles are bound by the matrix
@@ -280,8 +283,8 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   // The partial round's tiles go to the first CUs of an XCD, so the shares are dealt out from the last one:
   // where there are fewer shares than CUs, a CU with a tile of that round is the last to get one as well.
   const int share = cus - 1 - cu;
-  int64_t u = share_begin(share);
-  const int64_t u_end = share_begin(share + 1);
+  int u = share_begin(share);
+  const int u_end = share_begin(share + 1);
 
   // Big tiles of one expert are listed in blocks of hm row tiles x hn column tiles (hm = up to 8,
   // hm * hn = the CUs of an XCD), row tile fastest inside a block, blocks along the columns first:
@@ -332,9 +335,9 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
         s.kb = 0;
         s.ke = KT;
       } else {
-        s.stream = static_cast<int>(u / KT);
-        s.kb = static_cast<int>(u - static_cast<int64_t>(s.stream) * KT);
-        s.ke = static_cast<int>(min(static_cast<int64_t>(KT), s.kb + (u_end - u)));
+        s.stream = static_cast<int>(static_cast<uint32_t>(u) / static_cast<uint32_t>(KT));
+        s.kb = u - s.stream * KT;
+        s.ke = min(KT, s.kb + (u_end - u));
         u += s.ke - s.kb;
         if (s.stream < stream_big) big_tile(lx0 + s.stream, s);
         else small_tile(sx0 + s.stream - stream_big, s);
@@ -595,10 +598,10 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
       pending = nxt;
       nxt = cur;
       nxt.kb = cur.ke;
-      const int64_t first = static_cast<int64_t>(cur.stream) * KT;   // of the tile in the stream
+      const int first = cur.stream * KT;   // of the tile in the stream
       int c2 = share + 1;
       while (share_begin(c2) <= first + cur.ke) ++c2;   // (the shares end with the stream, behind the tile)
-      nxt.ke = static_cast<int>(min(static_cast<int64_t>(KT), share_begin(c2) - first));
+      nxt.ke = min(KT, share_begin(c2) - first);
       nxt.resumed = true;
     };
     if (cur.resumed) {
@@ -614,7 +617,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
         // One thread lists the CUs of the shares after this one that begin inside this tile (skipping empty
         // shares) and polls their flags (relaxed loads that go to L2, no cache maintenance in the loop).
         int n = 0, failed = 0;
-        for (int c2 = share + 1; c2 < cus && share_begin(c2) < static_cast<int64_t>(cur.stream + 1) * KT; ++c2) {
+        for (int c2 = share + 1; c2 < cus && share_begin(c2) < (cur.stream + 1) * KT; ++c2) {
           if (share_begin(c2 + 1) == share_begin(c2)) continue;
           const int b2 = ((cus - 1 - c2) << 3) | xcd;
           contrib[++n] = b2;
