@@ -10,7 +10,7 @@
 //     takes 22 cycles instead of 16 (2862 cycles per k-tile instead of 2096, no memory traffic);
 //   * operand tiles go from memory to LDS without passing through registers (buffer loads with an LDS
 //     destination): no staging registers, no LDS write instructions.
-// 8192 x 8192 x 8192: 1.37 PFLOP/s with 32x32x16 and register staging, 1.41 with LDS loads, 1.55 with both;
+// 8192 x 8192 x 8192: 1.37 PFLOP/s with 32x32x16 and register staging, 1.41 with LDS loads, 1.47 to 1.55 with both (by card);
 // 2340 cycles per k-tile (2048 are MFMAs, 107 go to the 32 fragment reads of a wavefront, 139 to its 16 loads) at 1.8 GHz.
 //
 // A k-tile of the block is four half-tiles of 16 KiB: A0, B0, B1, A1 (j = 0..3), half h of an operand holding the

@@ -258,12 +258,13 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_fast_kernel(
   const int units = stream_tiles * KT;
   // With a short contraction a hand-over costs more than the rest of the tile, and a share of kMinShare k-tiles is
   // several tiles one after another while other CUs idle: the stream is then dealt out in whole tiles.  Up to 20 k-tiles
-  // always; up to 32 where a partial round keeps the other CUs from their shares; up to 40 where big tiles are in it.  FFN
-  // backward, 8 experts of about 256 rows of 512 x 2048 (8 k-tiles): first product 42 us cut, 20 whole; the layers of
-  // 40 to 6000 tokens, 1 to 12 experts of 64 x 128 to 2048 x 8192: 0.74 of the time before in the mean, 0.83 where streams with big
-  // tiles are cut.  3000 rows of 520 x 1000 over 4 experts 83 -> 26 us, 700 of 1304 x 4000 67 -> 38, 1500 of 1608 x 328 over 2
-  // experts 61 -> 39, 3000 of 1992 x 4000 over 12 93 -> 63; beyond the lines: 136 of 1992 x 1000 over 12 cut 33, whole 46, 12000
-  // of 1800 x 4000 over 12 cut 241, whole 255, 1500 of 3528 x 1000 over 2 cut 68, whole 80.
+  // always; up to 32 where a partial round keeps the other CUs from their shares; up to 40 where big tiles are in it.  Whole
+  // k-tiles, whole against cut: 61 layers of 40 to 900 rows on one expert 0.89 of the time in the mean, 60 of 40 to 6000 tokens over 1 to
+  // 12 experts 0.73, 120 FFN backwards of up to 6000 rows 0.81 (8 experts of about 256 rows of 512 x 2048: first product 42 us
+  // cut, 20 whole); slower in 5 of the 241, by up to 3 % (1300 tokens of 768 x 2112, top-2 over 6 experts: 103 cut, 106 whole).
+  // The lines themselves lie where rows of no whole k-tiles turn: 3000 rows of 520 x 1000 over 4 experts 83 cut, 26 whole, 700 of 1304 x
+  // 4000 67 and 38, 3000 of 1992 x 4000 over 12 93 and 63; beyond them 136 of 1992 x 1000 over 12 33 and 46, 12000
+  // of 1800 x 4000 over 12 241 and 255, 1500 of 3528 x 1000 over 2 68 and 80.
   // (A spin limit of 0 is the diagnostic setting in which nobody waits for a hand-over: it cuts all the same.)
   const bool whole = spin_limit > 0 && KT <= (stream_big > 0 ? 40 : full_rounds == 0 && rounds > 0 ? 32 : 20);
   // Shares shorter than kMinShare k-tiles are not worth their hand-over: fewer CUs then take part.
